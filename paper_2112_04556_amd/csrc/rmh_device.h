@@ -213,7 +213,10 @@ RMH_HD void adjoint_columns(const T* u, T* c1, T* c2) {
 // Row 2 of an SU(3) matrix from rows 0 and 1 (u as in adjoint_matrix): for a unitary matrix of
 // unit determinant each row is the complex conjugate of the cross product of the other two,
 // U_2j = conj(U_0k U_1l - U_0l U_1k) with (j, k, l) a cyclic permutation of (0, 1, 2).
-template <typename T>
+// kFused: each element as one chain of multiply-adds (4 operations instead of 7).  The adjoint forms
+// in FP32 keep the separate products: their Chebyshev moments come back in FP64, where a change of
+// FP32 rounding would show.
+template <typename T, bool kFused = (sizeof(T) == 8)>
 RMH_HD void su3_row2(T* u) {
 #pragma unroll
   for (int j = 0; j < 3; ++j) {
@@ -222,8 +225,13 @@ RMH_HD void su3_row2(T* u) {
     const T br = u[6 + 2 * l], bi = u[6 + 2 * l + 1];    // U_1l
     const T cr = u[2 * l], ci = u[2 * l + 1];            // U_0l
     const T dr = u[6 + 2 * k], di = u[6 + 2 * k + 1];    // U_1k
-    u[12 + 2 * j] = (ar * br - ai * bi) - (cr * dr - ci * di);
-    u[12 + 2 * j + 1] = (cr * di + ci * dr) - (ar * bi + ai * br);
+    if (kFused) {
+      u[12 + 2 * j] = fmadd(ci, di, fmadd(-cr, dr, fmadd(-ai, bi, ar * br)));
+      u[12 + 2 * j + 1] = fmadd(-ai, br, fmadd(-ar, bi, fmadd(ci, dr, cr * di)));
+    } else {
+      u[12 + 2 * j] = (ar * br - ai * bi) - (cr * dr - ci * di);
+      u[12 + 2 * j + 1] = (cr * di + ci * dr) - (ar * bi + ai * br);
+    }
   }
 }
 
@@ -290,28 +298,19 @@ RMH_HD void adj_apply_t(const T* R, const T* phi, T* acc) {
   }
 }
 
-// Fundamental-representation form of the same hop: acc += comps(U Phi U^dag)
-// (dagger = false) or comps(U^dag Phi U) (dagger = true), Phi = sum_a phi^a T^a.
+// Fundamental-representation form of the same hop: acc += U Phi U^dag (kDagger = false) or
+// U^dag Phi U (kDagger = true) with Phi = sum_a phi^a lambda^a = 2 sum_a phi^a T^a.
+//
+// The accumulators hold the matrix elements of the hop's result Y (Hermitian, traceless), not its
+// components: acc[0], acc[1] = Re Y_01, -Im Y_01 (components 1, 2 themselves), acc[3], acc[4] of
+// Y_02, acc[5], acc[6] of Y_12 and acc[2], acc[7] = Y_00, Y_11; mat_components turns the sum of
+// all hops into components once per site.  The off-diagonal elements of sum phi^a lambda^a are
+// the components with no factor, so a hop needs four operations to form Phi (its diagonal) and
+// none on its result: every product is accumulated where it ends.  Rows 0 and 1 of A Phi suffice
+// (Y_22 = -(Y_00 + Y_11)): 60 + 48 multiply-adds per hop and vector.
 template <typename T, bool kDagger>
 RMH_HD void mat_hop(const T* u, const T* phi, T* acc) {
-  // Phi (Hermitian): diagonal d[i], upper off-diagonal o[p] for pairs (0,1),(0,2),(1,2)
-  const T h = T(0.5);
-  T dre[3], ore[3], oim[3];
-  dre[0] = fmadd(h, phi[2], h * T(kInvSqrt3) * phi[7]);
-  dre[1] = fmadd(-h, phi[2], h * T(kInvSqrt3) * phi[7]);
-  dre[2] = -T(kInvSqrt3) * phi[7];
-  ore[0] = h * phi[0]; oim[0] = -h * phi[1];
-  ore[1] = h * phi[3]; oim[1] = -h * phi[4];
-  ore[2] = h * phi[5]; oim[2] = -h * phi[6];
-  // full Phi as 3x3 complex
-  T pre[3][3], pim[3][3];
-  pre[0][0] = dre[0]; pim[0][0] = 0;
-  pre[1][1] = dre[1]; pim[1][1] = 0;
-  pre[2][2] = dre[2]; pim[2][2] = 0;
-  pre[0][1] = ore[0]; pim[0][1] = oim[0]; pre[1][0] = ore[0]; pim[1][0] = -oim[0];
-  pre[0][2] = ore[1]; pim[0][2] = oim[1]; pre[2][0] = ore[1]; pim[2][0] = -oim[1];
-  pre[1][2] = ore[2]; pim[1][2] = oim[2]; pre[2][1] = ore[2]; pim[2][1] = -oim[2];
-  // A = U (or U^dag) as explicit 3x3
+  // A = U (or U^dag)
   T are[3][3], aim[3][3];
 #pragma unroll
   for (int i = 0; i < 3; ++i)
@@ -325,54 +324,45 @@ RMH_HD void mat_hop(const T* u, const T* phi, T* acc) {
         aim[i][j] = -u[2 * (3 * j + i) + 1];
       }
     }
-  // W = A Phi (the diagonal of Phi is real: its imaginary terms are left out)
-  T wre[3][3], wim[3][3];
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      T sr = 0, si = 0;
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        if (k == j) {
-          sr = fmadd(are[i][k], pre[k][j], sr);
-          si = fmadd(aim[i][k], pre[k][j], si);
-        } else {
-          sr = fmadd(are[i][k], pre[k][j], fmadd(-aim[i][k], pim[k][j], sr));
-          si = fmadd(are[i][k], pim[k][j], fmadd(aim[i][k], pre[k][j], si));
-        }
-      }
-      wre[i][j] = sr;
-      wim[i][j] = si;
-    }
-  // Y = W A^dag : Y_ij = sum_k W_ik conj(A_jk); only the diagonal (real) and upper part; Y is
-  // traceless with Phi, so Y_22 = -(Y_00 + Y_11)
-  T yd[3];
+  // Phi: real diagonal d, upper off-diagonal o = ore - i oim for the pairs (0,1), (0,2), (1,2)
+  const T p8 = T(kInvSqrt3) * phi[7];
+  const T d0 = phi[2] + p8, d1 = p8 - phi[2], d2 = T(-2) * p8;
+  const T o01r = phi[0], o01i = phi[1], o02r = phi[3], o02i = phi[4], o12r = phi[5], o12i = phi[6];
+  T wre[2][3], wim[2][3];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    T sr = 0;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) sr = fmadd(wre[i][k], are[i][k], fmadd(wim[i][k], aim[i][k], sr));
-    yd[i] = sr;
+    const T a0r = are[i][0], a0i = aim[i][0], a1r = are[i][1], a1i = aim[i][1], a2r = are[i][2], a2i = aim[i][2];
+    // W_i0 = a0 d0 + a1 conj(o01) + a2 conj(o02), with o = or - i oi
+    wre[i][0] = fmadd(-a2i, o02i, fmadd(a2r, o02r, fmadd(-a1i, o01i, fmadd(a1r, o01r, a0r * d0))));
+    wim[i][0] = fmadd(a2r, o02i, fmadd(a2i, o02r, fmadd(a1r, o01i, fmadd(a1i, o01r, a0i * d0))));
+    // W_i1 = a0 o01 + a1 d1 + a2 conj(o12)
+    wre[i][1] = fmadd(-a2i, o12i, fmadd(a2r, o12r, fmadd(a0i, o01i, fmadd(a0r, o01r, a1r * d1))));
+    wim[i][1] = fmadd(a2r, o12i, fmadd(a2i, o12r, fmadd(-a0r, o01i, fmadd(a0i, o01r, a1i * d1))));
+    // W_i2 = a0 o02 + a1 o12 + a2 d2
+    wre[i][2] = fmadd(a1i, o12i, fmadd(a1r, o12r, fmadd(a0i, o02i, fmadd(a0r, o02r, a2r * d2))));
+    wim[i][2] = fmadd(-a1r, o12i, fmadd(a1i, o12r, fmadd(-a0r, o02i, fmadd(a0i, o02r, a2i * d2))));
   }
-  yd[2] = -(yd[0] + yd[1]);
-  constexpr int pi_[3] = {0, 0, 1};
-  constexpr int pj_[3] = {1, 2, 2};
-  constexpr int ps_[3] = {0, 3, 5};
+  // Y_ij = sum_k W_ik conj(A_jk)
 #pragma unroll
-  for (int p = 0; p < 3; ++p) {
-    const int i = pi_[p], j = pj_[p];
-    T sr = 0, si = 0;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      sr = fmadd(wre[i][k], are[j][k], fmadd(wim[i][k], aim[j][k], sr));
-      si = fmadd(wim[i][k], are[j][k], fmadd(-wre[i][k], aim[j][k], si));
-    }
-    acc[ps_[p]] = fmadd(T(2), sr, acc[ps_[p]]);
-    acc[ps_[p] + 1] = fmadd(T(-2), si, acc[ps_[p] + 1]);
+  for (int k = 0; k < 3; ++k) {
+    acc[2] = fmadd(wim[0][k], aim[0][k], fmadd(wre[0][k], are[0][k], acc[2]));
+    acc[7] = fmadd(wim[1][k], aim[1][k], fmadd(wre[1][k], are[1][k], acc[7]));
+    acc[0] = fmadd(wim[0][k], aim[1][k], fmadd(wre[0][k], are[1][k], acc[0]));
+    acc[1] = fmadd(-wim[0][k], are[1][k], fmadd(wre[0][k], aim[1][k], acc[1]));
+    acc[3] = fmadd(wim[0][k], aim[2][k], fmadd(wre[0][k], are[2][k], acc[3]));
+    acc[4] = fmadd(-wim[0][k], are[2][k], fmadd(wre[0][k], aim[2][k], acc[4]));
+    acc[5] = fmadd(wim[1][k], aim[2][k], fmadd(wre[1][k], are[2][k], acc[5]));
+    acc[6] = fmadd(-wim[1][k], are[2][k], fmadd(wre[1][k], aim[2][k], acc[6]));
   }
-  acc[2] += yd[0] - yd[1];
-  acc[7] = fmadd(fmadd(T(-2), yd[2], yd[0] + yd[1]), T(kInvSqrt3), acc[7]);
+}
+
+// Components of the accumulated matrix (see mat_hop): with Y traceless, component 3 is
+// (Y_00 - Y_11) / 2 and component 8 is (Y_00 + Y_11 - 2 Y_22) / (2 sqrt 3) = sqrt(3)/2 (Y_00 + Y_11).
+template <typename T>
+RMH_HD void mat_components(T* acc) {
+  const T y0 = acc[2], y1 = acc[7];
+  acc[2] = T(0.5) * (y0 - y1);
+  acc[7] = T(0.86602540378443864676) * (y0 + y1);
 }
 
 }  // namespace rmh

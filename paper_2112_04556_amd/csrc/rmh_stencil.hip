@@ -66,49 +66,171 @@ __device__ __forceinline__ void hop_apply(const T* u, const T (*phi)[8], T (*acc
   }
 }
 
-// An element of the z input: read once when each field has its own z (z_div = 1), so it is loaded
-// non-temporally and does not take L2 space from the neighbour fields; a z shared by several
-// fields (z_div > 1) is loaded normally for the others to hit.
+// The sum of all hops in components (the 3x3 form accumulates matrix elements).
+template <typename T, int FORM, int NV>
+__device__ __forceinline__ void hop_finish(T (*acc)[8]) {
+  if (FORM == kFormMatrix) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) mat_components<T>(acc[v]);
+  }
+}
+
+// The rows (components) of an array at one site per lane: row r at base + r * V, with the base address
+// the same for the whole wave, in scalar registers, and an unsigned 32-bit byte offset per lane (at
+// most 2^28 sites of 8 bytes) that the load instruction adds by itself.  The empty asm keeps the base
+// scalar and stepped from row to row: left alone, the compiler computes every row's address as a
+// 64-bit vector add, a quarter of the vector instructions of a hop.  With the 3x3 form's shorter
+// arithmetic (mat_hop) this took FP64 at 32^3x64 from 644 to 569 us per application, FP32 at 24^4 (4 fields)
+// from 211 to 195 us; the streamed form alone, at equal arithmetic, gains 1-7 %.
 template <typename T>
-__device__ __forceinline__ T load_z(const T* p, bool once) {
-  return once ? __builtin_nontemporal_load(p) : *p;
+using Global = __attribute__((address_space(1))) T;
+template <typename T>
+struct Rows {
+  uint64_t b, stride;
+  uint32_t o;
+  __device__ __forceinline__ Rows(const T* base, int64_t V, int32_t s)
+      : b((uint64_t)base), stride((uint64_t)V * sizeof(T)), o((uint32_t)s * (uint32_t)sizeof(T)) {
+    asm volatile("" : "+s"(b), "+v"(o));
+  }
+  __device__ __forceinline__ Global<T>* ptr() const { return (Global<T>*)((Global<char>*)b + o); }
+  __device__ __forceinline__ T get() {
+    const T x = *ptr();
+    next();
+    return x;
+  }
+  __device__ __forceinline__ void next() {
+    b += stride;
+    asm("" : "+s"(b));
+  }
+};
+
+// Row 2 from rows 0 and 1 in the rounding the form uses (su3_row2).
+template <typename T, int FORM>
+__device__ __forceinline__ void link_row2(T* u) {
+  su3_row2<T, sizeof(T) == 8 || FORM == kFormMatrix>(u);
 }
 
 // The link at site s (component c at Um[c V + s]): rows 0 and 1 are loaded, row 2 is rebuilt
-// from them (SU(3)), so a hop moves 12 link reals instead of 18.
-template <typename T>
+// from them (SU(3)), so a hop moves 12 link reals instead of 18.  kUni: Um is the same for the
+// whole wave.
+template <typename T, int FORM, bool kUni = true>
 __device__ __forceinline__ void load_link(const T* __restrict__ Um, int32_t s, int32_t V, T (&u)[18]) {
+  if (kUni) {
+    Rows<T> r(Um, V, s);
 #pragma unroll
-  for (int c = 0; c < 12; ++c) u[c] = (Um + (size_t)c * V)[s];
-  su3_row2<T>(u);
+    for (int c = 0; c < 12; ++c) u[c] = r.get();
+  } else {
+#pragma unroll
+    for (int c = 0; c < 12; ++c) u[c] = (Um + (size_t)c * V)[s];
+  }
+  link_row2<T, FORM>(u);
+}
+
+// The 12 stored reals of rows 0 and 1.
+template <typename T>
+__device__ __forceinline__ void load_rows(const T* __restrict__ Um, int32_t s, int32_t V, T (&u)[12]) {
+  Rows<T> r(Um, V, s);
+#pragma unroll
+  for (int c = 0; c < 12; ++c) u[c] = r.get();
+}
+
+// Directions nu0 .. nu0 + NV - 1 of the field at site s.
+template <typename T, int NV>
+__device__ __forceinline__ void load_field(const T* __restrict__ xf, int32_t s, int nu0, int32_t V, T (*f)[8]) {
+  Rows<T> r(xf + (size_t)(nu0 * 8) * V, V, s);
+#pragma unroll
+  for (int i = 0; i < NV; ++i)
+#pragma unroll
+    for (int b = 0; b < 8; ++b) f[i][b] = r.get();
+}
+
+// The epilogue at one site: out = a h + b x + c z for NV directions from nu0 on, and the partial dot
+// products.  kLoadX: x is read back from the field, else it is handed over in xc.  Per direction the
+// loads of x and z come before the stores (z may be the output itself, each element read and
+// written by this thread only), so they overlap.
+template <typename T, int NV, bool DOTS, bool kLoadX>
+__device__ __forceinline__ void hop_store(const HopArgs<T>& A, int32_t v, const T* __restrict__ xf, const T (*xc)[8],
+                                          int nu0, int32_t s, bool store, const T (*acc)[8], double* dsum) {
+  const int64_t V = A.g.V;
+  const int64_t FV = 32 * V;
+  const T ca = T(A.a);
+  const T cb = T(A.b_rhs ? A.b_rhs[v] : A.b);
+  const T cc = T(A.c);
+  const T* zf = A.z ? A.z + (int64_t)(v / A.z_div) * FV : nullptr;  // may alias out
+  T* outf = A.out + (int64_t)v * FV;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    T xs[8], zv[8];
+    const int64_t r0 = (int64_t)((nu0 + i) * 8) * V;
+    if (kLoadX) {
+      Rows<T> xr(xf + r0, V, s);
+#pragma unroll
+      for (int a = 0; a < 8; ++a) xs[a] = xr.get();
+    } else {
+#pragma unroll
+      for (int a = 0; a < 8; ++a) xs[a] = xc[i][a];
+    }
+    if (zf) {
+      if (A.z_div == 1) {
+        Rows<T> zr(zf + r0, V, s);
+#pragma unroll
+        for (int a = 0; a < 8; ++a) {
+          zv[a] = __builtin_nontemporal_load(zr.ptr());
+          zr.next();
+        }
+      } else {
+        Rows<T> zr(zf + r0, V, s);
+#pragma unroll
+        for (int a = 0; a < 8; ++a) zv[a] = zr.get();
+      }
+    }
+    T w[8];
+#pragma unroll
+    for (int a = 0; a < 8; ++a) w[a] = fmadd(ca, acc[i][a], cb * xs[a]);
+    if (zf) {
+#pragma unroll
+      for (int a = 0; a < 8; ++a) w[a] = fmadd(cc, zv[a], w[a]);
+    }
+    if (DOTS) {
+#pragma unroll
+      for (int a = 0; a < 8; ++a) {
+        const double xd = (double)xs[a], od = (double)w[a];
+        dsum[0] = fma(xd, xd, dsum[0]);
+        dsum[1] = fma(od, xd, dsum[1]);
+        dsum[2] = fma(od, od, dsum[2]);
+      }
+    }
+    if (store) {
+      Rows<T> outr(outf + r0, V, s);
+#pragma unroll
+      for (int a = 0; a < 8; ++a) {
+        __builtin_nontemporal_store(w[a], outr.ptr());
+        outr.next();
+      }
+    }
+  }
 }
 
 // out[v] = a (H x)[v] + b x[v] + c z[v]: a block of B threads covers B * NV / 4 sites; the
 // 4 / NV thread groups of a site (direction subsets) are wave-aligned slices of the block.
 // One backward hop: link and field both read at the neighbour site sb.
-template <typename T, int FORM, int NV, bool kT>
+template <typename T, int FORM, int NV, bool kT, bool kUni = true>
 __device__ __forceinline__ void hop_term(const T* __restrict__ Um, int32_t sb, const T* __restrict__ xf,
                                          int nu0, int32_t V, T (&acc)[NV][8]) {
   T u[18], phi[NV][8];
-  load_link<T>(Um, sb, V, u);
-#pragma unroll
-  for (int i = 0; i < NV; ++i)
-#pragma unroll
-    for (int b = 0; b < 8; ++b) phi[i][b] = (xf + (size_t)((nu0 + i) * 8 + b) * V)[sb];
+  load_link<T, FORM, kUni>(Um, sb, V, u);
+  load_field<T, NV>(xf, sb, nu0, V, phi);
   hop_apply<T, FORM, NV, kT>(u, phi, acc);
 }
 
 // One forward hop: link at s, field at the neighbour sf.
-template <typename T, int FORM, int NV>
+template <typename T, int FORM, int NV, bool kUni = true>
 __device__ __forceinline__ void hop_term_fwd(const T* __restrict__ Um, int32_t s, int32_t sf,
                                              const T* __restrict__ xf, int nu0, int32_t V,
                                              T (&acc)[NV][8]) {
   T u[18], phi[NV][8];
-  load_link<T>(Um, s, V, u);
-#pragma unroll
-  for (int i = 0; i < NV; ++i)
-#pragma unroll
-    for (int b = 0; b < 8; ++b) phi[i][b] = (xf + (size_t)((nu0 + i) * 8 + b) * V)[sf];
+  load_link<T, FORM, kUni>(Um, s, V, u);
+  load_field<T, NV>(xf, sf, nu0, V, phi);
   hop_apply<T, FORM, NV, false>(u, phi, acc);
 }
 
@@ -156,38 +278,8 @@ __global__ void __launch_bounds__(256) k_hop(const HopArgs<T> A, int32_t xcd, in
       hop_term<T, FORM, NV, true>(U + (int64_t)mb * 18 * V, site_shift(A.g, s, xc, mb, -1), xf, nu0, V, acc);
       hop_term_fwd<T, FORM, NV>(U + (int64_t)mu * 18 * V, s, site_shift(A.g, s, xc, mu, +1), xf, nu0, V, acc);
     }
-    // epilogue: out = a H x + b x + c z
-    const T ca = T(A.a);
-    const T cb = T(A.b_rhs ? A.b_rhs[v] : A.b);
-    const T cc = T(A.c);
-    const T* zf = A.z ? A.z + (int64_t)(v / A.z_div) * FV : nullptr;  // may alias out
-    T* outf = A.out + (int64_t)v * FV;
-    // per direction: the 8 z values are loaded before any of the 8 stores (z may be the output
-    // itself, each element read and written by this thread only), so those loads overlap
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      const int64_t e0 = (int64_t)((nu0 + i) * 8) * V + s;
-      T xs[8], zv[8];
-#pragma unroll
-      for (int a = 0; a < 8; ++a) {
-        xs[a] = xf[e0 + (int64_t)a * V];
-        zv[a] = zf ? load_z(&zf[e0 + (int64_t)a * V], A.z_div == 1) : T(0);
-      }
-#pragma unroll
-      for (int a = 0; a < 8; ++a) {
-        const int64_t e = e0 + (int64_t)a * V;
-        const T xv = xs[a];
-        T o = fmadd(ca, acc[i][a], cb * xv);
-        if (zf) o = fmadd(cc, zv[a], o);
-        if (A.store) __builtin_nontemporal_store(o, &outf[e]);
-        if (DOTS) {
-          const double xd = (double)xv, od = (double)o;
-          dsum[0] = fma(xd, xd, dsum[0]);
-          dsum[1] = fma(od, xd, dsum[1]);
-          dsum[2] = fma(od, od, dsum[2]);
-        }
-      }
-    }
+    hop_finish<T, FORM, NV>(acc);
+    hop_store<T, NV, DOTS, true>(A, v, xf, nullptr, nu0, s, A.store != 0, acc, dsum);
   }
   if (DOTS) {
     __shared__ double lds[3][16];
@@ -247,8 +339,8 @@ __global__ void __launch_bounds__(256) k_hop_split(const HopArgs<T> A, int32_t x
     int32_t xc[4];
     site_coords(A.g, s, xc);
     const T* __restrict__ Um = A.U + (int64_t)mu * 18 * V;
-    hop_term<T, FORM, NV, true>(Um, site_shift(A.g, s, xc, mu, -1), xf, nu0, V, acc);
-    hop_term_fwd<T, FORM, NV>(Um, s, site_shift(A.g, s, xc, mu, +1), xf, nu0, V, acc);
+    hop_term<T, FORM, NV, true, false>(Um, site_shift(A.g, s, xc, mu, -1), xf, nu0, V, acc);
+    hop_term_fwd<T, FORM, NV, false>(Um, s, site_shift(A.g, s, xc, mu, +1), xf, nu0, V, acc);
   }
 #pragma unroll
   for (int i = 0; i < NV; ++i)
@@ -257,6 +349,7 @@ __global__ void __launch_bounds__(256) k_hop_split(const HopArgs<T> A, int32_t x
       acc[i][a] += __shfl_xor(acc[i][a], 16, 64);
       acc[i][a] += __shfl_xor(acc[i][a], 32, 64);
     }
+  hop_finish<T, FORM, NV>(acc);
   // lane group mu keeps the components 4q + mu of its direction group (q < 2 NV), picked with
   // bit masks (a select chain here tends to become a lane-indexed array in scratch), then one
   // full-wave load/store per q; every z value is loaded before the first store (z may be the
@@ -280,7 +373,7 @@ __global__ void __launch_bounds__(256) k_hop_split(const HopArgs<T> A, int32_t x
       hs[q] = __builtin_bit_cast(T, hb_);
       const int64_t e = (int64_t)(nu0 * 8 + 4 * q + mu) * V + s;
       xs[q] = xf[e];
-      zv[q] = zf ? load_z(&zf[e], A.z_div == 1) : T(0);
+      zv[q] = !zf ? T(0) : A.z_div == 1 ? __builtin_nontemporal_load(&zf[e]) : zf[e];
     }
 #pragma unroll
     for (int q = 0; q < 2 * NV; ++q) {
@@ -363,11 +456,6 @@ k_hop_walk(const HopArgs<T> A, int32_t xcd, int32_t K, int32_t tile2, int32_t la
     const T* __restrict__ xf = A.x + ((int64_t)v * A.x_mul + A.x_add) * FV;
     const T* __restrict__ U = A.U;
     const T* __restrict__ U3 = U + (int64_t)3 * 18 * V;
-    const T ca = T(A.a);
-    const T cb = T(A.b_rhs ? A.b_rhs[v] : A.b);
-    const T cc = T(A.c);
-    const T* zf = A.z ? A.z + (int64_t)(v / A.z_div) * FV : nullptr;  // may alias out
-    T* outf = A.out + (int64_t)v * FV;
     int32_t xc[4];
     site_coords(A.g, col + x3_0 * P, xc);
     // carried state: the centre field, the x-3 field and the 12 loaded reals of the link U_3(x-3)
@@ -376,15 +464,9 @@ k_hop_walk(const HopArgs<T> A, int32_t xcd, int32_t K, int32_t tile2, int32_t la
     {
       const int32_t s0 = col + x3_0 * P;
       const int32_t sb = (x3_0 == 0) ? s0 + (A.g.L3 - 1) * P : s0 - P;
-#pragma unroll
-      for (int c = 0; c < 12; ++c) l3[c] = (U3 + (size_t)c * V)[sb];
-#pragma unroll
-      for (int i = 0; i < NV; ++i)
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-          cen[i][b] = (xf + (size_t)((nu0 + i) * 8 + b) * V)[s0];
-          bwd[i][b] = (xf + (size_t)((nu0 + i) * 8 + b) * V)[sb];
-        }
+      load_rows<T>(U3, sb, V, l3);
+      load_field<T, NV>(xf, s0, nu0, V, cen);
+      load_field<T, NV>(xf, sb, nu0, V, bwd);
     }
 #pragma unroll 1
     for (int32_t t = 0; t < K; ++t) {
@@ -401,7 +483,7 @@ k_hop_walk(const HopArgs<T> A, int32_t xcd, int32_t K, int32_t tile2, int32_t la
         T u[18];
 #pragma unroll
         for (int c = 0; c < 12; ++c) u[c] = l3[c];
-        su3_row2<T>(u);
+        link_row2<T, FORM>(u);
         hop_apply<T, FORM, NV, true>(u, bwd, acc);
       }
       int32_t mu_begin = 0;
@@ -416,11 +498,10 @@ k_hop_walk(const HopArgs<T> A, int32_t xcd, int32_t K, int32_t tile2, int32_t la
         const int32_t lp = row + (x0 + 1 == A.g.L0 ? 0 : x0 + 1);
         const int32_t lm = row + (x0 == 0 ? A.g.L0 - 1 : x0 - 1);
         T u[18], u12[12], phi[NV][8];
-#pragma unroll
-        for (int c = 0; c < 12; ++c) u12[c] = (U + (size_t)c * V)[s];
+        load_rows<T>(U, s, V, u12);
 #pragma unroll
         for (int c = 0; c < 12; ++c) u[c] = u12[c];
-        su3_row2<T>(u);
+        link_row2<T, FORM>(u);
 #pragma unroll
         for (int i = 0; i < NV; ++i)
 #pragma unroll
@@ -428,7 +509,7 @@ k_hop_walk(const HopArgs<T> A, int32_t xcd, int32_t K, int32_t tile2, int32_t la
         hop_apply<T, FORM, NV, false>(u, phi, acc);
 #pragma unroll
         for (int c = 0; c < 12; ++c) u[c] = __shfl(u12[c], lm, 64);
-        su3_row2<T>(u);
+        link_row2<T, FORM>(u);
 #pragma unroll
         for (int i = 0; i < NV; ++i)
 #pragma unroll
@@ -447,40 +528,15 @@ k_hop_walk(const HopArgs<T> A, int32_t xcd, int32_t K, int32_t tile2, int32_t la
       {
         const int32_t sf = (x3 == A.g.L3 - 1) ? s - (A.g.L3 - 1) * P : s + P;
         T u[18];
-#pragma unroll
-        for (int c = 0; c < 12; ++c) l3[c] = (U3 + (size_t)c * V)[s];
+        load_rows<T>(U3, s, V, l3);
 #pragma unroll
         for (int c = 0; c < 12; ++c) u[c] = l3[c];
-        su3_row2<T>(u);
-#pragma unroll
-        for (int i = 0; i < NV; ++i)
-#pragma unroll
-          for (int b = 0; b < 8; ++b) fwd[i][b] = (xf + (size_t)((nu0 + i) * 8 + b) * V)[sf];
+        link_row2<T, FORM>(u);
+        load_field<T, NV>(xf, sf, nu0, V, fwd);
         hop_apply<T, FORM, NV, false>(u, fwd, acc);
       }
-      // epilogue
-#pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        // the 8 z values before the 8 stores (z may be the output itself, element by element)
-        const int64_t e0 = (int64_t)((nu0 + i) * 8) * V + s;
-        T zv[8];
-#pragma unroll
-        for (int a = 0; a < 8; ++a) zv[a] = zf ? load_z(&zf[e0 + (int64_t)a * V], A.z_div == 1) : T(0);
-#pragma unroll
-        for (int a = 0; a < 8; ++a) {
-          const int64_t e = e0 + (int64_t)a * V;
-          const T xv = cen[i][a];
-          T o = fmadd(ca, acc[i][a], cb * xv);
-          if (zf) o = fmadd(cc, zv[a], o);
-          if (A.store) __builtin_nontemporal_store(o, &outf[e]);
-          if (DOTS) {
-            const double xd = (double)xv, od = (double)o;
-            dsum[0] = fma(xd, xd, dsum[0]);
-            dsum[1] = fma(od, xd, dsum[1]);
-            dsum[2] = fma(od, od, dsum[2]);
-          }
-        }
-      }
+      hop_finish<T, FORM, NV>(acc);
+      hop_store<T, NV, DOTS, false>(A, v, xf, cen, nu0, s, A.store != 0, acc, dsum);
 #pragma unroll
       for (int i = 0; i < NV; ++i)
 #pragma unroll
@@ -516,17 +572,14 @@ template <typename T, int FORM, int NS, bool kT>
 __device__ __forceinline__ void hop_term_ns(const T* __restrict__ Um, int32_t sl, int32_t sn,
                                             const T* const (&xf)[NS], int32_t V, T (&acc)[NS * 4][8]) {
   T u[18];
-  load_link<T>(Um, sl, V, u);
+  load_link<T, FORM>(Um, sl, V, u);
   if (FORM == kFormAdjoint) {
     T R[64];
     adjoint_matrix<T>(u, R);
 #pragma unroll
     for (int f = 0; f < NS; ++f) {
       T phi[4][8];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int b = 0; b < 8; ++b) phi[i][b] = (xf[f] + (size_t)(i * 8 + b) * V)[sn];
+      load_field<T, 4>(xf[f], sn, 0, V, phi);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         if (!kT)
@@ -539,10 +592,7 @@ __device__ __forceinline__ void hop_term_ns(const T* __restrict__ Um, int32_t sl
     T phi[NS * 4][8];
 #pragma unroll
     for (int f = 0; f < NS; ++f)
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int b = 0; b < 8; ++b) phi[f * 4 + i][b] = (xf[f] + (size_t)(i * 8 + b) * V)[sn];
+      load_field<T, 4>(xf[f], sn, 0, V, phi + f * 4);
     adj_stream<T, NS * 4, kT>(u, phi, acc);
   }
 }
@@ -597,39 +647,9 @@ __global__ void __launch_bounds__(256) k_hop_ns(const HopArgs<T> A, int32_t xcd,
       hop_term_ns<T, FORM, NS, true>(U + (int64_t)mb * 18 * V, sb, sb, xf, V, acc);
       hop_term_ns<T, FORM, NS, false>(U + (int64_t)mu * 18 * V, s, site_shift(A.g, s, xc, mu, +1), xf, V, acc);
     }
-    const T ca = T(A.a);
-    const T cc = T(A.c);
 #pragma unroll
-    for (int f = 0; f < NS; ++f) {
-      const int32_t v = v0 + f;
-      const T cb = T(A.b_rhs ? A.b_rhs[v] : A.b);
-      const T* zf = A.z ? A.z + (int64_t)(v / A.z_div) * FV : nullptr;  // may alias out
-      T* outf = A.out + (int64_t)v * FV;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int64_t e0 = (int64_t)(i * 8) * V + s;
-        T xs[8], zv[8];
-#pragma unroll
-        for (int a = 0; a < 8; ++a) {
-          xs[a] = xf[f][e0 + (int64_t)a * V];
-          zv[a] = zf ? load_z(&zf[e0 + (int64_t)a * V], A.z_div == 1) : T(0);
-        }
-#pragma unroll
-        for (int a = 0; a < 8; ++a) {
-          const int64_t e = e0 + (int64_t)a * V;
-          const T xv = xs[a];
-          T o = fmadd(ca, acc[f * 4 + i][a], cb * xv);
-          if (zf) o = fmadd(cc, zv[a], o);
-          if (A.store && runs[f]) __builtin_nontemporal_store(o, &outf[e]);
-          if (DOTS) {
-            const double xd = (double)xv, od = (double)o;
-            dsum[f * 3 + 0] = fma(xd, xd, dsum[f * 3 + 0]);
-            dsum[f * 3 + 1] = fma(od, xd, dsum[f * 3 + 1]);
-            dsum[f * 3 + 2] = fma(od, od, dsum[f * 3 + 2]);
-          }
-        }
-      }
-    }
+    for (int f = 0; f < NS; ++f)
+      hop_store<T, 4, DOTS, true>(A, v0 + f, xf[f], nullptr, 0, s, A.store && runs[f], acc + f * 4, dsum + f * 3);
   }
   if (DOTS) {
     __shared__ double lds[NS * 3][16];

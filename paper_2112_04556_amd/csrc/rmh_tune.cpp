@@ -8,6 +8,7 @@
 #include <string.h>
 
 #include <cstdlib>
+#include <initializer_list>
 #include <map>
 #include <mutex>
 #include <string>
@@ -31,52 +32,63 @@ Key key_of(const Geom& g, int32_t dtype, int32_t n_rhs, int32_t purpose) {
   return Key(g.L0, g.L1, g.L2, g.L3, dtype, n_rhs, purpose);
 }
 
-// Untuned defaults, from the sweeps of the autotuner on MI355X.  Lattices of a million sites and
-// more: one thread per x0-x1-x2 column and all four directions, walking 8 consecutive x3 sites
-// (fewest re-reads past L2: about 1.7 times the algorithmic reads in FP32, against 2.5 for one
-// thread per site); a batch of fields below a million sites, when the batch gives every SIMD
-// several waves: one thread per site, the adjoint matrix streamed two columns at a time; below
-// that the hop-split shape (four lanes per site, one per direction), whose four times as many waves
-// hide the memory latency that one thread per site leaves exposed when the lattice gives only a
-// few waves per SIMD, except FP64 from 2^18 sites on, where one thread per site and direction pair
-// in the x3-fastest order is as fast.
-HopConfig defaults(const Geom& g, int32_t dtype, int32_t n_rhs) {
+// The longest of the given x3 walks that divides L3 (0: none does).
+int32_t walk_of(const Geom& g, std::initializer_list<int> ks) {
+  for (int k : ks)
+    if (g.L3 % k == 0) return k;
+  return 0;
+}
+
+// Untuned defaults, from the sweeps of the autotuner on MI355X.  All use the 3x3 form, which needs the
+// fewest operations per hop.
+//  - 2^20 sites and more: a walk along x3, whose re-reads past L2 are the fewest.  FP64: all four
+//    directions per thread and column tiles two rows of x2 deep (32^3x64: 0.560 ms; without the tile
+//    0.59, one thread per site 0.62); FP32: two directions per thread (0.289 ms against 0.292 tiled with
+//    four and 0.339 for one thread per site).
+//  - a batch of at least 2^19 site-fields below that size: every SIMD has several waves, and the walk
+//    with four directions per thread saves re-reads (16^4, 8 fields: FP64 0.120 ms against 0.137
+//    without a walk; 24^4, 8 fields, FP32 sweep 0.389 against 0.418).
+//  - smaller launches: four lanes per site, one per direction (hop split), whose four times as many
+//    waves hide the memory latency that one thread per site leaves exposed (12^4 FP64: 12.0 us against
+//    15.9; 24^4 FP64 0.089 ms against 0.102).  Above 2^18 sites in FP64 a lane takes all four directions.
+// FP32 Chebyshev moments below 2^20 sites keep the streamed adjoint form: they are FP64 results of FP32
+// sweeps, and another form's rounding moves them by a few 1e-9.
+HopConfig defaults(const Geom& g, int32_t dtype, int32_t n_rhs, int32_t purpose) {
+  const bool f64 = dtype == RMH_F64;
   HopConfig c;
-  if (g.V < (1 << 20) && (int64_t)g.V * n_rhs >= (1 << 19)) {
+  if (!f64 && purpose == RMH_PURPOSE_MOMENTS && g.V < (1 << 20)) {
+    const bool batch = (int64_t)g.V * n_rhs >= (1 << 19);
     c.form = kFormStream;
-    c.block = 64;
-    c.xcd_remap = 1;
     c.nv = 4;
-    c.walk = 0;
-    c.order = 1;
-    if (!hop_order_ok(g, c)) c.order = 0;
-  } else if (g.V >= (1 << 20)) {
-    c.form = dtype == RMH_F64 ? kFormStream : kFormAdjoint;
-    c.block = dtype == RMH_F64 ? 128 : 256;
-    c.xcd_remap = dtype == RMH_F64 ? 0 : 1;
-    c.nv = 4;
-    c.order = 0;
-    c.walk = 0;
-    for (int k : {8, 4, 16, 2})
-      if (g.L3 % k == 0) {
-        c.walk = k;
-        break;
-      }
-  } else if (dtype == RMH_F64 && g.V >= (1 << 18)) {
-    c.form = kFormMatrix;
+    c.block = batch ? 64 : 256;
+    c.xcd_remap = batch ? 1 : 0;
+    c.order = batch ? 1 : 2;
+    if (batch && !hop_order_ok(g, c)) c.order = 0;
+    return c;
+  }
+  c.form = kFormMatrix;
+  c.nv = 4;
+  c.order = 0;
+  if (g.V >= (1 << 20)) {
     c.block = 256;
+    c.xcd_remap = 0;
+    if (f64) {
+      c.walk = walk_of(g, {16, 8, 4, 2});
+      c.tile2 = 2;
+      if (!hop_walk_ok(g, c)) c.tile2 = 1;
+    } else {
+      c.nv = 2;
+      c.walk = walk_of(g, {4, 8, 16, 2});
+    }
+  } else if ((int64_t)g.V * n_rhs >= (1 << 19)) {
+    c.block = f64 ? 128 : 64;
     c.xcd_remap = 1;
-    c.nv = 2;
-    c.walk = 0;
-    c.order = 1;
-    if (!hop_order_ok(g, c)) c.order = 0;
+    c.walk = f64 ? walk_of(g, {8, 4, 2}) : walk_of(g, {4, 8, 2});
   } else {
-    c.form = dtype == RMH_F64 ? kFormMatrix : kFormStream;
-    c.block = dtype == RMH_F64 ? 128 : 256;
-    c.xcd_remap = dtype == RMH_F64 ? 0 : 1;
-    c.nv = dtype == RMH_F64 ? 2 : 4;
-    c.walk = 0;
     c.order = 2;
+    c.xcd_remap = f64 ? 0 : 1;
+    c.nv = f64 && g.V < (1 << 18) ? 2 : 4;
+    c.block = f64 && g.V >= (1 << 18) ? 64 : 256;
   }
   return c;
 }
@@ -134,7 +146,7 @@ HopConfig tune_hop(const Geom& g, int32_t dtype, int32_t n_rhs, int32_t purpose)
   if (it != g_cache.end()) return it->second.cfg;
   if (const HopConfig* c = nearest(g, dtype, n_rhs, purpose)) return fit_batch(*c, n_rhs);
   if (const HopConfig* c = nearest(g, dtype, n_rhs, RMH_PURPOSE_ANY)) return fit_batch(*c, n_rhs);
-  return defaults(g, dtype, n_rhs);
+  return defaults(g, dtype, n_rhs, purpose);
 }
 
 void tune_clear() {
