@@ -406,11 +406,13 @@ rmh_status rmh_leapfrog_step(const int32_t L[4], const double* U0, const double*
  * only) makes each thread apply the operator to ns fields of a batch, so each link and adjoint
  * matrix serves 4 ns vectors (used when ns divides the batch); tile2 = 2 or 4 (with a walk) gives
  * each walking block an L0 x R x tile2 tile of (x0, x1, x2) columns instead of consecutive
- * columns, so part of its x2 neighbours are its own (used when the tile divides the plane).  Every
- * configuration computes the
- * same operator; a form fixes the per-site arithmetic, so results are bitwise identical across
- * block sizes, remaps, nv, ns, orders 0 and 1 and walks of one form (orders 2 and 3 sum the eight
- * hops in another order: equal to rounding). */
+ * columns, so part of its x2 neighbours are its own (used when the tile divides the plane).  Order 1
+ * with walk = K > 0, form 1 and nv = 2 is the tiled walk: a block walks up to K x3 sites with an
+ * L0 x R1 x R2 tile of at most `block` columns (R2 <= tile2) whose plane of the field sits in LDS (used
+ * up to 2^24 sites and where a row of x0 fits `block`; K need not divide L3 nor the tile the plane).
+ * Every configuration computes the same operator; a form fixes the per-site arithmetic, so results
+ * are bitwise identical across block sizes, remaps, nv, ns, orders 0 and 1 and walks of one form
+ * (orders 2 and 3 and the tiled walk sum the eight hops in another order: equal to rounding). */
 typedef struct {
   int32_t form, block, xcd_remap, nv, order, walk, ns, tile2;
 } rmh_hop_config;

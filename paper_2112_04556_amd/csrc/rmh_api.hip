@@ -2403,7 +2403,7 @@ rmh_status rmh_autotune_laplacian(const int32_t L[4], const void* U, int32_t dty
     for (int ns : {1, 2, 4})
     for (int tile2 : {1, 2, 4})
     for (int block : {64, 128, 256})
-    for (int walk : {0, 4, 8, 16})
+    for (int walk : {0, 1, 2, 4, 8, 12, 16, 24, 32})
     for (int order = 0; order < 4 && st == RMH_OK; ++order) {
       for (int xcd = 0; xcd < 2 && st == RMH_OK; ++xcd) {
         HopConfig c;
@@ -2417,8 +2417,13 @@ rmh_status rmh_autotune_laplacian(const int32_t L[4], const void* U, int32_t dty
         c.tile2 = tile2;
         if (hop_config_error(c, dtype)) continue;
         if (ns > 1 && n_rhs % ns) continue;
-        if ((order == 1 || order == 3) && !hop_order_ok(g, c)) continue;
-        if (walk && (order || !hop_walk_ok(g, c))) continue;
+        HopTile tile;
+        if (hop_tile_of(g, c, &tile)) {
+          if (!xcd || walk > g.L3) continue;   // a tile's halo is shared within an XCD
+        } else {
+          if ((order == 1 || order == 3) && !hop_order_ok(g, c)) continue;
+          if (walk && (order || !hop_walk_ok(g, c) || (walk != 4 && walk != 8 && walk != 16))) continue;
+        }
         tune_store(g, dtype, n_rhs, purpose, c, 0.0);
         auto unit = [&]() -> rmh_status {
           const hipError_t e =

@@ -44,6 +44,8 @@ enum HopForm : int32_t { kFormAdjoint = 0, kFormMatrix = 1, kFormStream = 2 };
 // fields are streamed through it one at a time; form 2: its column pairs are built once per hop
 // and applied to all 4 S vectors).  The per-vector arithmetic is that of nv = 4, so results are
 // bitwise those of ns = 1 with the same form.
+// order = 1 with walk > 0, form 1 and nv = 2 is the tiled walk (k_hop_tile): a block walks x3 with an
+// L0 x R1 x R2 tile of columns (at most `block`, R2 <= tile2) whose plane of the field sits in LDS.
 struct HopConfig {
   int32_t form = kFormStream;
   int32_t block = 256;
@@ -76,6 +78,13 @@ struct HopArgs {
   double* partials;         // [n_rhs][3][nblk]: <x,x>, <out,x>, <out,out>
   int32_t dot_mask;         // bit q set -> compute dot q
 };
+
+// Tile of the tiled walk: R1 x R2 rows of x0 per block, n1 x n2 tiles per plane, K planes per walk.
+struct HopTile {
+  int32_t R1, R2, n1, n2, K;
+};
+// the tile of a configuration, false if it is not the tiled walk or the lattice does not fit it
+bool hop_tile_of(const Geom& g, const HopConfig& cfg, HopTile* t);
 
 int hop_num_blocks(const Geom& g, const HopConfig& cfg);
 // whether the x3-fastest block order applies to this lattice and configuration

@@ -85,11 +85,15 @@ __device__ __forceinline__ void hop_finish(T (*acc)[8]) {
 template <typename T>
 using Global = __attribute__((address_space(1))) T;
 template <typename T>
+__device__ __forceinline__ uint32_t byte_off(int32_t s) {
+  return (uint32_t)s * (uint32_t)sizeof(T);
+}
+template <typename T>
 struct Rows {
   uint64_t b, stride;
   uint32_t o;
-  __device__ __forceinline__ Rows(const T* base, int64_t V, int32_t s)
-      : b((uint64_t)base), stride((uint64_t)V * sizeof(T)), o((uint32_t)s * (uint32_t)sizeof(T)) {
+  __device__ __forceinline__ Rows(const T* base, int64_t V, uint32_t byte_offset)
+      : b((uint64_t)base), stride((uint64_t)V * sizeof(T)), o(byte_offset) {
     asm volatile("" : "+s"(b), "+v"(o));
   }
   __device__ __forceinline__ Global<T>* ptr() const { return (Global<T>*)((Global<char>*)b + o); }
@@ -116,7 +120,7 @@ __device__ __forceinline__ void link_row2(T* u) {
 template <typename T, int FORM, bool kUni = true>
 __device__ __forceinline__ void load_link(const T* __restrict__ Um, int32_t s, int32_t V, T (&u)[18]) {
   if (kUni) {
-    Rows<T> r(Um, V, s);
+    Rows<T> r(Um, V, byte_off<T>(s));
 #pragma unroll
     for (int c = 0; c < 12; ++c) u[c] = r.get();
   } else {
@@ -129,7 +133,7 @@ __device__ __forceinline__ void load_link(const T* __restrict__ Um, int32_t s, i
 // The 12 stored reals of rows 0 and 1.
 template <typename T>
 __device__ __forceinline__ void load_rows(const T* __restrict__ Um, int32_t s, int32_t V, T (&u)[12]) {
-  Rows<T> r(Um, V, s);
+  Rows<T> r(Um, V, byte_off<T>(s));
 #pragma unroll
   for (int c = 0; c < 12; ++c) u[c] = r.get();
 }
@@ -137,7 +141,7 @@ __device__ __forceinline__ void load_rows(const T* __restrict__ Um, int32_t s, i
 // Directions nu0 .. nu0 + NV - 1 of the field at site s.
 template <typename T, int NV>
 __device__ __forceinline__ void load_field(const T* __restrict__ xf, int32_t s, int nu0, int32_t V, T (*f)[8]) {
-  Rows<T> r(xf + (size_t)(nu0 * 8) * V, V, s);
+  Rows<T> r(xf + (size_t)(nu0 * 8) * V, V, byte_off<T>(s));
 #pragma unroll
   for (int i = 0; i < NV; ++i)
 #pragma unroll
@@ -163,7 +167,7 @@ __device__ __forceinline__ void hop_store(const HopArgs<T>& A, int32_t v, const 
     T xs[8], zv[8];
     const int64_t r0 = (int64_t)((nu0 + i) * 8) * V;
     if (kLoadX) {
-      Rows<T> xr(xf + r0, V, s);
+      Rows<T> xr(xf + r0, V, byte_off<T>(s));
 #pragma unroll
       for (int a = 0; a < 8; ++a) xs[a] = xr.get();
     } else {
@@ -172,14 +176,14 @@ __device__ __forceinline__ void hop_store(const HopArgs<T>& A, int32_t v, const 
     }
     if (zf) {
       if (A.z_div == 1) {
-        Rows<T> zr(zf + r0, V, s);
+        Rows<T> zr(zf + r0, V, byte_off<T>(s));
 #pragma unroll
         for (int a = 0; a < 8; ++a) {
           zv[a] = __builtin_nontemporal_load(zr.ptr());
           zr.next();
         }
       } else {
-        Rows<T> zr(zf + r0, V, s);
+        Rows<T> zr(zf + r0, V, byte_off<T>(s));
 #pragma unroll
         for (int a = 0; a < 8; ++a) zv[a] = zr.get();
       }
@@ -201,7 +205,7 @@ __device__ __forceinline__ void hop_store(const HopArgs<T>& A, int32_t v, const 
       }
     }
     if (store) {
-      Rows<T> outr(outf + r0, V, s);
+      Rows<T> outr(outf + r0, V, byte_off<T>(s));
 #pragma unroll
       for (int a = 0; a < 8; ++a) {
         __builtin_nontemporal_store(w[a], outr.ptr());
@@ -668,6 +672,342 @@ __global__ void __launch_bounds__(256) k_hop_ns(const HopArgs<T> A, int32_t xcd,
   }
 }
 
+// ------------------------------------------------------------------------------------------
+// the tiled walk
+//
+// A block takes a tile of L0 x R1 x R2 columns (x0 rows whole) and walks n3 values of x3.  The tile's
+// plane of the field sits in LDS, double buffered, so the x0 neighbours and those x1 and x2 neighbours
+// that lie in the tile come from LDS; only the tile's edge rows read theirs from memory, where each
+// halo site is read by one thread only.  What bounds the other shapes is the load path (32 bytes
+// per cycle and CU, measured, from L1 and L2 alike) and the traffic past L2: 384 reals per site go
+// through it in the site-per-thread shapes, 240 in the walk, 160 here.
+//
+// A wave is 32 columns in two halves: lanes 0-31 take directions nu = 0, 1 and lanes 32-63 nu = 2, 3 of
+// the same columns, and each half loads one of the two stored rows of a link, exchanged through the
+// register file (v_permlane32_swap), so a site's links are loaded once.  Two directions per
+// lane keep the kernel at 220 registers in FP64: two waves per SIMD (FP64 instructions issue every 4.4
+// cycles with two or more waves, every 6-9 with one).
+//
+// Every load is issued a hop ahead of its use (pin() keeps the compiler from moving arithmetic across
+// hops, which would need more registers than there are).  The x3 hop uses its link both ways:
+// U phi(x+3) U^dag for this plane, U^dag phi(x) U for the next.  The x1 and x2 hops come first in a
+// step and phi(x+3) is loaded last: the halo rows of a plane were then loaded by the neighbouring blocks
+// moments ago and are still in the XCD's L2 (at 32^3x64 17.6 M misses of 128 bytes instead of 21.0 M with
+// the opposite order, 1.2 times the algorithmic bytes).
+//
+// Measured per application against the walk (same card, both warm): FP64 32^3x64 494 us against 568,
+// 24^4 x 4 fields (recursion step) 357 against 434, 16^4 x 2 35.5 against 41.4, 16^4 x 8 115 against 123;
+// FP32 32^3x64 273 against 292.  At 16^4 x 8 it issues vector instructions 77 % of the time.
+
+// Keeps x in registers here: later arithmetic is not moved before, earlier not after.
+template <typename T, int N>
+__device__ __forceinline__ void pin(T (&x)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" : "+v"(x[i]));
+}
+template <typename T>
+__device__ __forceinline__ void pin(T (&x)[2][8]) {
+  pin(x[0]);
+  pin(x[1]);
+}
+
+template <typename T>
+using Vec16 = T __attribute__((ext_vector_type(16 / sizeof(T))));
+
+// One lane's 16 reals of a column in LDS.  A column takes kTilePitch elements: 32 and 16 bytes more, so
+// that the 16 lanes of a 16-byte access phase fall into distinct banks.
+template <typename T>
+constexpr int kTilePitch = 32 + 16 / sizeof(T);
+template <typename T>
+__device__ __forceinline__ void lds_get(const char* p, T (&f)[2][8]) {
+  constexpr int N = 16 / sizeof(T);
+  const Vec16<T>* q = (const Vec16<T>*)p;
+#pragma unroll
+  for (int i = 0; i < 16 / N; ++i) {
+    const Vec16<T> w = q[i];
+#pragma unroll
+    for (int k = 0; k < N; ++k) f[(i * N + k) >> 3][(i * N + k) & 7] = w[k];
+  }
+}
+template <typename T>
+__device__ __forceinline__ void lds_put(char* p, const T (&f)[2][8]) {
+  constexpr int N = 16 / sizeof(T);
+  Vec16<T>* q = (Vec16<T>*)p;
+#pragma unroll
+  for (int i = 0; i < 16 / N; ++i) {
+    Vec16<T> w;
+#pragma unroll
+    for (int k = 0; k < N; ++k) w[k] = f[(i * N + k) >> 3][(i * N + k) & 7];
+    q[i] = w;
+  }
+}
+
+// 16 rows of a field (two directions), or the 6 reals of one stored row of a link, at a byte offset
+// that includes the lane half's rows.
+template <typename T>
+__device__ __forceinline__ void get_half(const T* base, int64_t V, uint32_t o, T (&f)[2][8]) {
+  Rows<T> r(base, V, o);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) f[i >> 3][i & 7] = r.get();
+}
+template <typename T, bool kOnce = false>
+__device__ __forceinline__ void get_row(const T* base, int64_t V, uint32_t o, T (&u)[6]) {
+  Rows<T> r(base, V, o);
+#pragma unroll
+  for (int i = 0; i < 6; ++i) {
+    u[i] = kOnce ? __builtin_nontemporal_load(r.ptr()) : *r.ptr();
+    r.next();
+  }
+}
+
+// a = the value of lanes 0-31 in both halves, b = that of lanes 32-63.
+__device__ __forceinline__ void both_halves(float x, float& a, float& b) {
+  const uint32_t w = __builtin_bit_cast(uint32_t, x);
+  const auto r = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  a = __builtin_bit_cast(float, (uint32_t)r[0]);
+  b = __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+__device__ __forceinline__ void both_halves(double x, double& a, double& b) {
+  const uint64_t w = __builtin_bit_cast(uint64_t, x);
+  const auto l = __builtin_amdgcn_permlane32_swap((uint32_t)w, (uint32_t)w, false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)(w >> 32), (uint32_t)(w >> 32), false, false);
+  a = __builtin_bit_cast(double, (uint64_t)(uint32_t)l[0] | ((uint64_t)(uint32_t)h[0] << 32));
+  b = __builtin_bit_cast(double, (uint64_t)(uint32_t)l[1] | ((uint64_t)(uint32_t)h[1] << 32));
+}
+
+// The whole link from the half rows of the two lane halves.
+template <typename T>
+__device__ __forceinline__ void whole_link(T (&h)[6], T (&u)[18]) {
+  pin(h);
+#pragma unroll
+  for (int i = 0; i < 6; ++i) both_halves(h[i], u[i], u[6 + i]);
+  su3_row2<T, true>(u);
+}
+
+template <typename T, bool kT>
+__device__ __forceinline__ void hop_pair(const T* u, T (&f)[2][8], T (&acc)[2][8]) {
+  pin(f);
+  mat_hop<T, kT>(u, f[0], acc[0]);
+  pin(acc[0]);
+  mat_hop<T, kT>(u, f[1], acc[1]);
+  pin(acc[1]);
+}
+
+template <typename T, bool DOTS, bool Z>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 4)))
+k_hop_tile(const HopArgs<T> A, const HopTile S, int32_t xcd) {
+  extern __shared__ __align__(16) char smem[];
+  const HopBlock hb = hop_block(xcd, A.n_rhs);
+  const int32_t v = hb.v;
+  if (A.run && A.run[(int64_t)v * A.run_stride] == 0) return;
+  constexpr uint32_t SZ = sizeof(T);
+  constexpr uint32_t PB = kTilePitch<T> * SZ;      // LDS bytes per column
+  const int64_t V = A.g.V;
+  const int32_t L0 = A.g.L0, L1 = A.g.L1, L2 = A.g.L2, L3 = A.g.L3;
+  const int32_t L01 = L0 * L1;
+  const int32_t lb = hb.lb;
+  const int32_t ntile = S.n1 * S.n2;
+  const int32_t tile = lb % ntile;
+  const int32_t x3_0 = (lb / ntile) * S.K;
+  const int32_t n3 = min(S.K, L3 - x3_0);
+  const int32_t y1 = (tile % S.n1) * S.R1, y2 = (tile / S.n1) * S.R2;   // the tile's first row
+  const int32_t m1 = min(S.R1, L1 - y1), m2 = min(S.R2, L2 - y2);       // and its rows (cut at the lattice's end)
+  const int32_t h = (threadIdx.x >> 5) & 1;
+  int32_t tc = (threadIdx.x >> 6) * 32 + (threadIdx.x & 31);
+  int32_t x0 = tc % L0, r1 = (tc / L0) % S.R1, r2 = tc / (L0 * S.R1);
+  // lanes without a column go through the motions of the tile's first one and write nothing
+  const bool live = r1 < m1 && r2 < m2;
+  if (!live) x0 = r1 = r2 = 0;
+  const int32_t x1 = y1 + r1, x2 = y2 + r2;
+  const int32_t col = x0 + L0 * (x1 + L1 * x2);
+  // LDS byte offsets of the neighbours in the tile
+  auto lds_at = [&](int32_t c0, int32_t c1, int32_t c2) {
+    return (uint32_t)(c0 + L0 * (c1 + S.R1 * c2)) * PB + (uint32_t)h * (16 * SZ);
+  };
+  const uint32_t lc = lds_at(x0, r1, r2);
+  const uint32_t l0p = lds_at(x0 + 1 == L0 ? 0 : x0 + 1, r1, r2), l0m = lds_at(x0 == 0 ? L0 - 1 : x0 - 1, r1, r2);
+  const uint32_t l1p = lds_at(x0, r1 + 1 < m1 ? r1 + 1 : 0, r2), l1m = lds_at(x0, r1 > 0 ? r1 - 1 : m1 - 1, r2);
+  const uint32_t l2p = lds_at(x0, r1, r2 + 1 < m2 ? r2 + 1 : 0), l2m = lds_at(x0, r1, r2 > 0 ? r2 - 1 : m2 - 1);
+  // a tile that spans the lattice in a direction holds all its neighbours there
+  const bool i1p = r1 + 1 < m1 || m1 == L1, i1m = r1 > 0 || m1 == L1;
+  const bool i2p = r2 + 1 < m2 || m2 == L2, i2m = r2 > 0 || m2 == L2;
+  // byte offsets in a component of the global neighbours in the plane x3 = 0, and of the lane half's rows
+  const uint32_t gc = (uint32_t)col * SZ;
+  const uint32_t g0m = (uint32_t)(col + (x0 == 0 ? L0 - 1 : -1)) * SZ;
+  const uint32_t g1p = (uint32_t)(col + (x1 + 1 == L1 ? L0 - L01 : L0)) * SZ;
+  const uint32_t g1m = (uint32_t)(col + (x1 == 0 ? L01 - L0 : -L0)) * SZ;
+  const uint32_t g2p = (uint32_t)(col + (x2 + 1 == L2 ? (1 - L2) * L01 : L01)) * SZ;
+  const uint32_t g2m = (uint32_t)(col + (x2 == 0 ? (L2 - 1) * L01 : -L01)) * SZ;
+  const uint32_t hf = (uint32_t)h * (uint32_t)(16 * V * SZ), hl = (uint32_t)h * (uint32_t)(6 * V * SZ);
+  const uint32_t plane = (uint32_t)(L01 * L2) * SZ;
+  const int64_t FV = 32 * V;
+  const T* __restrict__ xf = A.x + ((int64_t)v * A.x_mul + A.x_add) * FV;
+  const T* __restrict__ U0 = A.U;
+  const T* __restrict__ U1 = U0 + 18 * V;
+  const T* __restrict__ U2 = U0 + 36 * V;
+  const T* __restrict__ U3 = U0 + 54 * V;
+  const T ca = T(A.a), cb = T(A.b_rhs ? A.b_rhs[v] : A.b), cc = T(A.c);
+  const T* zf = Z ? A.z + (int64_t)(v / A.z_div) * FV : nullptr;   // may alias out
+  T* outf = A.out + (int64_t)v * FV;
+  const uint32_t buf = (uint32_t)(S.R1 * S.R2 * L0) * PB;          // one plane of the tile in LDS
+  double dsum[3] = {0.0, 0.0, 0.0};
+  uint32_t pl = (uint32_t)x3_0 * plane;
+  // acc: this plane's result; p, q, r: fields; la, lb2: link half rows; u: a link
+  T acc[2][8], p[2][8], q[2][8], r[2][8], la[6], lb2[6], u[18];
+  {
+    // the first plane into LDS, and its x3 backward hop
+    const uint32_t pb = (uint32_t)(x3_0 == 0 ? L3 - 1 : x3_0 - 1) * plane;
+    get_half(xf, V, hf + gc + pl, r);
+    get_row(U3, V, hl + gc + pb, la);
+    get_half(xf, V, hf + gc + pb, q);
+    get_row(U1, V, hl + gc + pl, lb2);
+    pin(r);
+    if (live) lds_put<T>(smem + lc, r);
+#pragma unroll
+    for (int a = 0; a < 8; ++a) acc[0][a] = acc[1][a] = T(0);
+    whole_link(la, u);
+    hop_pair<T, true>(u, q, acc);
+#pragma unroll
+    for (int i = 0; i < 6; ++i) la[i] = lb2[i];
+  }
+  __syncthreads();
+#pragma unroll 1
+  for (int32_t t = 0; t < n3; ++t) {
+    const int32_t x3 = x3_0 + t;
+    const char* cur = smem + (t & 1 ? buf : 0u);
+    char* nxt = smem + (t & 1 ? 0u : buf);
+    const uint32_t pf = (uint32_t)(x3 + 1 == L3 ? 0 : x3 + 1) * plane;
+    // a neighbour: from the tile in LDS or, for an edge row, from memory
+    auto near = [&](bool in, uint32_t l, uint32_t g, T (&f)[2][8]) {
+      if (in)
+        lds_get<T>(cur + l, f);
+      else
+        get_half(xf, V, hf + g + pl, f);
+    };
+    near(i1p, l1p, g1p, r);
+    near(i1m, l1m, g1m, q);
+    get_row(U1, V, hl + g1m + pl, lb2);
+    whole_link(la, u);
+    hop_pair<T, false>(u, r, acc);    // x1 forward
+    get_row(U2, V, hl + gc + pl, la);
+    near(i2p, l2p, g2p, r);
+    whole_link(lb2, u);
+    hop_pair<T, true>(u, q, acc);     // x1 backward
+    get_row(U2, V, hl + g2m + pl, lb2);
+    near(i2m, l2m, g2m, q);
+    whole_link(la, u);
+    hop_pair<T, false>(u, r, acc);    // x2 forward
+    get_row(U0, V, hl + gc + pl, la);
+    lds_get<T>(cur + l0p, r);
+    whole_link(lb2, u);
+    hop_pair<T, true>(u, q, acc);     // x2 backward
+    get_row(U0, V, hl + g0m + pl, lb2);
+    lds_get<T>(cur + l0m, q);
+    get_half(xf, V, hf + gc + pf, p);
+    whole_link(la, u);
+    hop_pair<T, false>(u, r, acc);    // x0 forward
+    get_row<T, true>(U3, V, hl + gc + pl, la);
+    lds_get<T>(cur + lc, r);
+    whole_link(lb2, u);
+    hop_pair<T, true>(u, q, acc);     // x0 backward
+    if (Z) {
+      Rows<T> zr(zf, V, hf + gc + pl);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        q[i >> 3][i & 7] = A.z_div == 1 ? __builtin_nontemporal_load(zr.ptr()) : *zr.ptr();
+        zr.next();
+      }
+    }
+    whole_link(la, u);
+    hop_pair<T, false>(u, p, acc);    // x3 forward; phi(x+3) is the next plane
+    if (live) lds_put<T>(nxt + lc, p);
+    T back[2][8];
+#pragma unroll
+    for (int a = 0; a < 8; ++a) back[0][a] = back[1][a] = T(0);
+    hop_pair<T, true>(u, r, back);    // the next plane's x3 backward hop
+    if (t + 1 < n3) get_row(U1, V, hl + gc + pf, la);
+    mat_components<T>(acc[0]);
+    mat_components<T>(acc[1]);
+    T w[2][8];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      T o = fmadd(ca, acc[i >> 3][i & 7], cb * r[i >> 3][i & 7]);
+      if (Z) o = fmadd(cc, q[i >> 3][i & 7], o);
+      w[i >> 3][i & 7] = o;
+      if (DOTS && live) {
+        const double xd = (double)r[i >> 3][i & 7], od = (double)o;
+        dsum[0] = fma(xd, xd, dsum[0]);
+        dsum[1] = fma(od, xd, dsum[1]);
+        dsum[2] = fma(od, od, dsum[2]);
+      }
+    }
+    if (A.store && live) {
+      Rows<T> outr(outf, V, hf + gc + pl);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        __builtin_nontemporal_store(w[i >> 3][i & 7], outr.ptr());
+        outr.next();
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < 8; ++a) {
+      acc[0][a] = back[0][a];
+      acc[1][a] = back[1][a];
+    }
+    pl = pf;
+    // the next plane is complete in nxt, and nobody reads cur any more
+    __syncthreads();
+  }
+  if (DOTS) {
+    double(*lds)[16] = (double(*)[16])smem;
+    block_sum<3>(dsum, lds);
+    if (threadIdx.x == 0) {
+      const int32_t nblk = hb.nblk;
+      double* pp = A.partials + (int64_t)v * 3 * nblk + lb;
+      if (A.dot_mask & 1) pp[0] = dsum[0];
+      if (A.dot_mask & 2) pp[nblk] = dsum[1];
+      if (A.dot_mask & 4) pp[2 * nblk] = dsum[2];
+    }
+  }
+}
+
+// The tile of a configuration: cfg.tile2 rows of x2 and as many rows of x1 as cfg.block columns
+// allow, evened out over the lattice; segments of cfg.walk planes, the last one shorter where
+// walk does not divide L3.
+bool hop_tile_of(const Geom& g, const HopConfig& cfg, HopTile* t) {
+  if (cfg.order != 1 || cfg.walk < 1 || cfg.form != kFormMatrix || cfg.nv != 2 || cfg.ns != 1) return false;
+  // byte offsets of half a field (17 V elements of 8 bytes) fit 32 bits; a row of columns fits a block
+  if (g.V > (1 << 24) || g.L0 > cfg.block) return false;
+  t->R2 = std::min<int32_t>(cfg.tile2, g.L2);
+  while (g.L0 * t->R2 > cfg.block) --t->R2;
+  t->R1 = std::min<int32_t>(cfg.block / (g.L0 * t->R2), g.L1);
+  t->n1 = (g.L1 + t->R1 - 1) / t->R1;
+  t->R1 = (g.L1 + t->n1 - 1) / t->n1;
+  t->n2 = (g.L2 + t->R2 - 1) / t->R2;
+  t->R2 = (g.L2 + t->n2 - 1) / t->n2;
+  t->K = std::min(cfg.walk, g.L3);
+  return true;
+}
+static int hop_tile_blocks(const Geom& g, const HopTile& t) { return t.n1 * t.n2 * ((g.L3 + t.K - 1) / t.K); }
+
+template <typename T>
+static hipError_t launch_hop_tile(const HopArgs<T>& A, const HopTile& t, int32_t xcd, dim3 grid, hipStream_t s) {
+  const int32_t columns = A.g.L0 * t.R1 * t.R2;
+  dim3 block((columns + 31) / 32 * 64);
+  // two planes; the block sums of the dot products use the same memory at the end
+  const size_t lds = std::max<size_t>(2 * (size_t)columns * kTilePitch<T> * sizeof(T), 3 * 16 * sizeof(double));
+  const bool dots = A.partials && A.dot_mask;
+  if (dots && A.z)
+    hipLaunchKernelGGL((k_hop_tile<T, true, true>), grid, block, lds, s, A, t, xcd);
+  else if (dots)
+    hipLaunchKernelGGL((k_hop_tile<T, true, false>), grid, block, lds, s, A, t, xcd);
+  else if (A.z)
+    hipLaunchKernelGGL((k_hop_tile<T, false, true>), grid, block, lds, s, A, t, xcd);
+  else
+    hipLaunchKernelGGL((k_hop_tile<T, false, false>), grid, block, lds, s, A, t, xcd);
+  return hipGetLastError();
+}
+
 int hop_walk_ok(const Geom& g, const HopConfig& cfg) {
   if (!(cfg.walk > 0 && (g.L3 % cfg.walk) == 0)) return 0;
   if (cfg.tile2 > 1) {
@@ -695,6 +1035,8 @@ int hop_split_ok(const HopConfig& cfg) {
 static int hop_split_spb(const HopConfig& cfg) { return (cfg.block / 64) / (4 / cfg.nv) * 16; }
 
 int hop_num_blocks(const Geom& g, const HopConfig& cfg) {
+  HopTile tile;
+  if (hop_tile_of(g, cfg, &tile)) return hop_tile_blocks(g, tile);
   if (hop_split_ok(cfg)) {
     const int spb = hop_split_spb(cfg);
     return (g.V + spb - 1) / spb;
@@ -745,6 +1087,10 @@ static hipError_t launch_hop_form(const HopArgs<T>& A, const HopConfig& cfg, hip
       }
       return hipGetLastError();
     }
+  }
+  if constexpr (NV == 2 && FORM == kFormMatrix) {
+    HopTile tile;
+    if (hop_tile_of(A.g, cfg, &tile)) return launch_hop_tile<T>(A, tile, cfg.xcd_remap, grid, s);
   }
   if (hop_split_ok(cfg)) {
     const int32_t ord = (cfg.order == 3 && hop_order_ok(A.g, cfg)) ? 1 : 0;

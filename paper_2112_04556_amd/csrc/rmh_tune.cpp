@@ -7,6 +7,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <cstdlib>
 #include <initializer_list>
 #include <map>
@@ -39,25 +40,70 @@ int32_t walk_of(const Geom& g, std::initializer_list<int> ks) {
   return 0;
 }
 
-// Untuned defaults, from the sweeps of the autotuner on MI355X.  All use the 3x3 form, which needs the
-// fewest operations per hop.
-//  - 2^20 sites and more: a walk along x3, whose re-reads past L2 are the fewest.  FP64: all four
-//    directions per thread and column tiles two rows of x2 deep (32^3x64: 0.560 ms; without the tile
-//    0.59, one thread per site 0.62); FP32: two directions per thread (0.289 ms against 0.292 tiled with
-//    four and 0.339 for one thread per site).
-//  - a batch of at least 2^19 site-fields below that size: every SIMD has several waves, and the walk
-//    with four directions per thread saves re-reads (16^4, 8 fields: FP64 0.120 ms against 0.137
-//    without a walk; 24^4, 8 fields, FP32 sweep 0.389 against 0.418).
-//  - smaller launches: four lanes per site, one per direction (hop split), whose four times as many
-//    waves hide the memory latency that one thread per site leaves exposed (12^4 FP64: 12.0 us against
-//    15.9; 24^4 FP64 0.089 ms against 0.102).  Above 2^18 sites in FP64 a lane takes all four directions.
+// The tiled walk's tile and segment length for a launch: the shape with the least estimated time.  A CU
+// holds 8 waves in FP64 (16 in FP32) and 160 KB of LDS; its time is the number of blocks it gets, each
+// w waves walking K planes after a prologue worth 1.5, lengthened by the halo rows read from memory and
+// by having few waves to hide latency with.  Of the up to 40 best shapes timed on each of 17 lattices
+// (8x12x16x20 to 32^3x64, odd extents among them) the estimate's pick was the fastest or within 5 %.
+bool tile_shape(const Geom& g, int32_t dtype, int32_t n_rhs, HopConfig* out) {
+  const int max_waves = dtype == RMH_F64 ? 8 : 16;
+  const double lds_column = 2.0 * (dtype == RMH_F64 ? 272 : 144);
+  double best = 0.0;
+  for (int R2 = 1; R2 <= g.L2 && g.L0 * R2 <= 256; ++R2)
+    for (int R1 = 1; R1 <= g.L1 && g.L0 * R1 * R2 <= 256; ++R1) {
+      HopConfig c;
+      c.form = kFormMatrix;
+      c.nv = 2;
+      c.order = 1;
+      c.xcd_remap = 1;
+      c.block = g.L0 * R1 * R2;
+      c.tile2 = R2;
+      c.walk = g.L3;
+      HopTile t;
+      if (!hop_tile_of(g, c, &t) || t.R1 != R1 || t.R2 != R2) continue;
+      const int w = (c.block + 31) / 32;
+      const int fit = std::max(1, std::min(max_waves / w, (int)(160 * 1024 / (lds_column * c.block))));
+      const double halo = (R1 < g.L1 ? 0.2 / R1 : 0.0) + (R2 < g.L2 ? 0.2 / R2 : 0.0) + (w < 4 ? 0.08 : 0.0);
+      for (int nseg = 1, K; nseg <= g.L3; nseg = (g.L3 - 1) / (K - 1) + 1) {   // each K = ceil(L3 / nseg) once
+        K = (g.L3 + nseg - 1) / nseg;
+        const int64_t per_cu = ((int64_t)t.n1 * t.n2 * nseg * n_rhs + 255) / 256;
+        const double waves = (double)w * std::min<int64_t>(fit, per_cu);
+        const double cost = (double)per_cu * w * (K + 1.5) * (1.0 + halo) * (1.0 + 0.5 * max_waves / waves);
+        if (best == 0.0 || cost < best) {
+          best = cost;
+          *out = c;
+          out->walk = K;
+        }
+        if (K == 1) break;
+      }
+    }
+  return best > 0.0;
+}
+
+// Untuned defaults, from the sweeps of the autotuner on MI355X.  All but the FP32 moments use the 3x3
+// form, which needs the fewest operations per hop.
+//  - FP64 from 2^16 site-fields on: the tiled walk (32^3x64 0.494 ms against 0.568 for the walk with four
+//    directions per thread; 24^4 84 us against 99 for the hop split, its recursion step 93 against 124;
+//    20x18^3 39 against 51; 16^4 x 2 35 against 41; 16^4 20.0-24.4 against 20.2-24.7).  Below, the tiles
+//    of a launch are few and the hop split wins or loses by how they fall on the 256 CUs (14x12x11x14
+//    17.4 against 14.2 tiled, 16x16x12x12 15.5 against 17.7, 17x15x13x19 27 against 32).
+//  - FP32 from 2^20 sites on: the tiled walk (32^3x64 0.263 ms against 0.292).  In smaller FP32 lattices its
+//    vector work, the link rebuilt by both lane halves, is the bound: a batch of at least 2^19 site-fields
+//    walks with four directions per thread (24^4 x 8 sweep 0.415 ms against 0.417), smaller launches
+//    take one thread per site and direction pair (16^4 13.4 us against 14.9 tiled, 14.3 hop split).
+//  - smaller launches (FP32: below 2^16 site-fields): four lanes per site, one per direction (hop split),
+//    whose four times as many waves hide the latency that one thread per site leaves exposed.  Two
+//    directions per lane (FP32 from 24576 site-fields on: four; 13x11x14x16 8.8 us against 10.9, 8x12x8x8
+//    6.2 against 4.5), in blocks of 128 threads where these give the CUs less work than blocks of 256
+//    (FP64 8^4: 4.8 us against 5.5; 8x12x8x8: 6.4 against 5.5).
 // FP32 Chebyshev moments below 2^20 sites keep the streamed adjoint form: they are FP64 results of FP32
 // sweeps, and another form's rounding moves them by a few 1e-9.
 HopConfig defaults(const Geom& g, int32_t dtype, int32_t n_rhs, int32_t purpose) {
   const bool f64 = dtype == RMH_F64;
+  const int64_t work = (int64_t)g.V * n_rhs;
   HopConfig c;
   if (!f64 && purpose == RMH_PURPOSE_MOMENTS && g.V < (1 << 20)) {
-    const bool batch = (int64_t)g.V * n_rhs >= (1 << 19);
+    const bool batch = work >= (1 << 19);
     c.form = kFormStream;
     c.nv = 4;
     c.block = batch ? 64 : 256;
@@ -66,31 +112,37 @@ HopConfig defaults(const Geom& g, int32_t dtype, int32_t n_rhs, int32_t purpose)
     if (batch && !hop_order_ok(g, c)) c.order = 0;
     return c;
   }
+  if ((f64 ? work >= (1 << 16) : g.V >= (1 << 20)) && tile_shape(g, dtype, n_rhs, &c)) return c;
   c.form = kFormMatrix;
-  c.nv = 4;
-  c.order = 0;
-  if (g.V >= (1 << 20)) {
-    c.block = 256;
-    c.xcd_remap = 0;
-    if (f64) {
-      c.walk = walk_of(g, {16, 8, 4, 2});
-      c.tile2 = 2;
-      if (!hop_walk_ok(g, c)) c.tile2 = 1;
-    } else {
-      c.nv = 2;
-      c.walk = walk_of(g, {4, 8, 16, 2});
-    }
-  } else if ((int64_t)g.V * n_rhs >= (1 << 19)) {
+  c.xcd_remap = 1;
+  if (work >= (1 << 19)) {
+    // (also the lattices too large for the tile: more than 2^24 sites, or rows longer than a block)
+    c.nv = 4;
     c.block = f64 ? 128 : 64;
-    c.xcd_remap = 1;
     c.walk = f64 ? walk_of(g, {8, 4, 2}) : walk_of(g, {4, 8, 2});
+  } else if (!f64 && work >= (1 << 16)) {
+    c.nv = 2;
+    c.block = 128;
   } else {
+    // a block of 128 threads holds 16 sites' two direction pairs, one of 256 threads 32
+    const int64_t small = (work + 16 * 256 - 1) / (16 * 256), large = 2 * ((work + 32 * 256 - 1) / (32 * 256));
+    c.nv = f64 || work < 24576 ? 2 : 4;
+    c.block = c.nv == 2 && small < large ? 128 : 256;
     c.order = 2;
-    c.xcd_remap = f64 ? 0 : 1;
-    c.nv = f64 && g.V < (1 << 18) ? 2 : 4;
-    c.block = f64 && g.V >= (1 << 18) ? 64 : 256;
+    c.xcd_remap = 0;
   }
   return c;
+}
+
+// The shapes found so far (the search takes microseconds to tens of them, a small launch as much), by
+// lattice, dtype, batch and purpose; dropped when it grows past 256 entries.
+std::map<Key, HopConfig> g_shapes;
+HopConfig defaults_kept(const Geom& g, int32_t dtype, int32_t n_rhs, int32_t purpose) {
+  const Key k = key_of(g, dtype, n_rhs, purpose);
+  const auto it = g_shapes.find(k);
+  if (it != g_shapes.end()) return it->second;
+  if (g_shapes.size() >= 256) g_shapes.clear();
+  return g_shapes[k] = defaults(g, dtype, n_rhs, purpose);
 }
 
 // nearest batch size among the entries of (L, dtype, purpose)
@@ -146,7 +198,7 @@ HopConfig tune_hop(const Geom& g, int32_t dtype, int32_t n_rhs, int32_t purpose)
   if (it != g_cache.end()) return it->second.cfg;
   if (const HopConfig* c = nearest(g, dtype, n_rhs, purpose)) return fit_batch(*c, n_rhs);
   if (const HopConfig* c = nearest(g, dtype, n_rhs, RMH_PURPOSE_ANY)) return fit_batch(*c, n_rhs);
-  return defaults(g, dtype, n_rhs, purpose);
+  return defaults_kept(g, dtype, n_rhs, purpose);  // under the lock
 }
 
 void tune_clear() {

@@ -311,3 +311,65 @@ def test_laplacian_full_size_16():
     U, P, Ud, Pd = setup(L, "eps", 0.5, 2, n=1)
     y = api.laplacian_apply(L, Ud, Pd).cpu().numpy()
     assert rel_max(y, olap.laplacian(U, P, L)) <= 1e-12
+
+
+# (L, n, block, tile2, walk): tiles cut at the lattice's end, tiles that span a direction (their
+# neighbours wrap inside them), one-row tiles, extents of 2, walks that do not divide L3, columns that
+# do not fill a wave, one plane per walk, walks longer than L3
+TILES = [((4, 5, 6, 7), 2, 128, 4, 3), ((6, 7, 5, 4), 1, 256, 4, 4), ((3, 9, 4, 5), 3, 128, 2, 2),
+         ((2, 2, 2, 2), 2, 128, 2, 1), ((16, 4, 6, 3), 1, 128, 1, 8), ((13, 5, 3, 6), 2, 256, 2, 5),
+         ((31, 3, 2, 4), 1, 128, 4, 64), ((8, 8, 8, 2), 8, 256, 4, 2), ((128, 2, 3, 2), 1, 128, 1, 1)]
+
+
+@pytest.mark.parametrize("L,n,block,tile2,walk", TILES)
+def test_laplacian_tiled_walk(L, n, block, tile2, walk):
+    """The tiled walk (form 1, nv 2, order 1 with a walk): FP64 within 1e-12 and FP32 within 1e-5 of the
+    oracle, and its fused epilogues (dot products, z over the output) against the hop-split kernel's."""
+    announce(f"tiled walk {L} n={n} block={block} tile2={tile2} walk={walk}")
+    U, P, Ud, Pd = setup(L, "haar", 0.5, 11, n=n)
+    ref = olap.laplacian(U, P, L, 0.7)
+    split = (1, 256, 1, 2, 2, 0)
+    tile = dict(form=1, block=block, xcd_remap=1, nv=2, order=1, walk=walk, tile2=tile2)
+    res = {}
+    try:
+        for dtype, tol in ((torch.float64, 1e-12), (torch.float32, 1e-5)):
+            u, x = Ud.to(dtype), Pd.to(dtype)
+            for name in ("tile", "split"):
+                api.tune_clear()
+                if name == "tile":
+                    api.tune_set(L, dtype, n, **tile)
+                else:
+                    api.tune_set(L, dtype, n, *split)
+                y = api.laplacian_apply(L, u, x, 0.7).double().cpu().numpy()
+                assert np.abs(y - ref).max() <= tol * np.abs(ref).max(), (name, dtype)
+                mom, pw = api.power_spectrum(L, u, x, 9, 3)
+                res[name] = (mom, pw, api.cheb_filter(L, u, x, 9, 3).double().cpu().numpy())
+            scale = np.abs(res["split"][0][:, :1])
+            assert np.all(np.abs(res["tile"][0] - res["split"][0]) <= 10 * tol * scale)
+            assert np.all(np.abs(res["tile"][1] - res["split"][1]) <= 10 * tol * scale)
+            assert rel_max(res["tile"][2], res["split"][2]) <= 10 * tol
+        # a solve: fields that stop at different iterations leave their blocks at once
+        rat = api.rational_kappa(0.8, 3)
+        Ps = Pd * torch.logspace(0, -3, n, dtype=torch.float64, device=Pd.device)[:, None, None, None]
+        api.tune_clear()
+        api.tune_set(L, torch.float64, n, **tile)
+        a = api.rational_apply(L, Ud, Ps, rat, api.Solver(tol=1e-11))
+        api.tune_clear()
+        api.tune_set(L, torch.float64, n, *split)
+        b = api.rational_apply(L, Ud, Ps, rat, api.Solver(tol=1e-11))
+        assert a["stats"]["true_relres_max"] <= 1e-11
+        assert rel_max(a["y"].cpu().numpy(), b["y"].cpu().numpy()) <= 1e-9
+    finally:
+        api.tune_clear()
+
+
+@pytest.mark.parametrize("L,n", [((10, 9, 13, 15), 4), ((16, 16, 16, 16), 1), ((66, 5, 7, 30), 1), ((7, 8, 9, 11), 12)])
+def test_laplacian_default_shapes(L, n):
+    """The shapes chosen without tuning for launches of 2^16 site-fields and more, odd extents among them."""
+    announce(f"default shapes {L} n={n}")
+    U, P, Ud, Pd = setup(L, "eps", 0.5, 12, n=n)
+    api.tune_clear()
+    assert rel_max(api.laplacian_apply(L, Ud, Pd).cpu().numpy(), olap.laplacian(U, P, L)) <= 1e-12
+    y32 = api.laplacian_apply(L, Ud.float(), Pd.float()).double().cpu().numpy()
+    ref = olap.laplacian(U, P, L)
+    assert np.abs(y32 - ref).max() <= 1e-5 * np.abs(ref).max()
