@@ -315,7 +315,7 @@ struct Engine {
   double* ring = nullptr;  // [n_rhs][nslot] seed residuals of the FP64 phase
   float* ring32 = nullptr; // [n_rhs][nslot32] seed residuals of the FP32 phase (mixed)
   double* pj = nullptr;    // [n_rhs][n_shift] shift directions at the segment start (n_shift > 1)
-  double* coef = nullptr;  // [n_rhs][n_shift][2 + 2 nslot32]
+  double* coef = nullptr;  // [n_rhs][n_shift][2 + 2 coef_slots]
   // scalar state, contiguous so one copy brings it to the host: sc then flags
   double* sc = nullptr;
   int32_t* flags = nullptr;
@@ -332,7 +332,8 @@ struct Engine {
   double* b_true = nullptr;  // [n_rhs][n_shift]  -(8 + sigma_j)
   double* tol_rhs = nullptr; // [n_rhs]
   int32_t* seed = nullptr;   // [n_rhs]
-  double* part = nullptr;      // [n_rhs][max(3 nblk_hop, nblk_e)]
+  double* part = nullptr;      // [n_rhs][max(3 nblk_hop, blocks of a dot product)]
+  double* part_e = nullptr;    // [n_rhs][nblk_e]
   double* part_ru = nullptr;   // [n_rhs][3][nblk_hop]  (mixed precision)
   double* part_true = nullptr; // [n_rhs][n_shift][3][nblk_hop]
   double* sums_true = nullptr; // [n_rhs][n_shift][3]
@@ -341,15 +342,26 @@ struct Engine {
 
 size_t rup(size_t b) { return ((b + 255) / 256) * 256; }
 
-// Residual ring length for a solver: basis iterations per segment + 1 (single-shift engines
-// keep only the current and the next residual).  Default segments: 32 iterations in FP64 engines
-// (a solve of up to 32 iterations folds its shifts once), 16 in mixed ones (whose FP64 phase
-// ends near there; the open segment then goes on in the FP32 ring).
-int32_t ring_slots(int32_t n_shift, int32_t basis, int32_t mode) {
+// Residual ring lengths for a solver: basis iterations per segment + 1 in FP64 (single-shift engines
+// keep only the current and the next residual), and in mixed engines min(2 (basis + 1), 33) in FP32.
+// Default segments: 32 iterations in FP64 engines (a solve of up to 32 iterations folds its shifts
+// once), 16 in mixed ones (whose FP64 phase ends near there; the open segment then goes on in the
+// FP32 ring).  On small lattices, where 15 more residuals are cheap, 47: a fold writes and reads back
+// the solution and direction of every shift, and the usual solves to 1e-10 take 31 to 36 iterations
+// (16^4, 12 poles, FP64: 35 iterations in one fold of 185 us instead of two of 333 together).
+int32_t ring_slots(const Geom& g, int32_t n_shift, int32_t basis, int32_t mode) {
   if (n_shift <= 1) return 2;
-  const int32_t m = basis > 0 ? basis : (mode ? 16 : 32);
-  return std::min<int32_t>(m, kMaxSlots - 1) + 1;
+  const int32_t m = basis > 0 ? basis : mode ? 16 : g.V <= kLongSegmentSites ? kMaxSlots - 1 : 32;
+  return std::min<int32_t>(m, basis > 0 ? kMaxBasis : kMaxSlots - 1) + 1;
 }
+int32_t ring_slots32(const Geom& g, int32_t nslot, int32_t n_shift, int32_t basis) {
+  if (n_shift > 1 && basis <= 0 && g.V <= kLongSegmentSites) return kMaxSlots;
+  return std::min<int32_t>(2 * nslot, kMaxBasis + 1);
+}
+
+// coefficient slots per shift: the entries a segment can hold, in whole groups of eight (the fold reads
+// groups; slots past the segment's end hold zeros)
+int32_t coef_slots(const Engine& e) { return (std::max(e.nslot, e.nslot32) + 7) / 8 * 8; }
 
 void plan_engine(Carver& c, Engine& e, const Geom& g, int32_t n_rhs, int32_t n_shift, int32_t mode,
                  int32_t basis) {
@@ -357,8 +369,8 @@ void plan_engine(Carver& c, Engine& e, const Geom& g, int32_t n_rhs, int32_t n_s
   e.n_rhs = n_rhs;
   e.n_shift = n_shift;
   e.mode = mode;
-  e.nslot = ring_slots(n_shift, basis, mode);
-  e.nslot32 = std::min<int32_t>(2 * e.nslot, kMaxSlots);
+  e.nslot = ring_slots(g, n_shift, basis, mode);
+  e.nslot32 = ring_slots32(g, e.nslot, n_shift, basis);
   const int64_t n = field_reals(g);
   const size_t nr = n_rhs, np = (size_t)n_rhs * n_shift;
   e.p64 = c.take<double>(nr * n);
@@ -372,7 +384,7 @@ void plan_engine(Carver& c, Engine& e, const Geom& g, int32_t n_rhs, int32_t n_s
   e.ring = c.take<double>(nr * e.nslot * n);
   if (mode) e.ring32 = c.take<float>(nr * e.nslot32 * n);
   if (n_shift > 1) e.pj = c.take<double>(np * n);
-  e.coef = c.take<double>(np * (2 + 2 * std::max(e.nslot, e.nslot32)));
+  e.coef = c.take<double>(np * (2 + 2 * coef_slots(e)));
   const size_t scb = rup(nr * kScN * 8), flb = rup(nr * kFlN * 4);
   char* st = c.take<char>(scb + flb);
   e.sc = (double*)st;
@@ -394,8 +406,9 @@ void plan_engine(Carver& c, Engine& e, const Geom& g, int32_t n_rhs, int32_t n_s
     e.seed = (int32_t*)q;
   }
   e.nblk_hop = hop_max_blocks(g);
-  e.nblk_e = red_num_blocks(n);
-  e.part = c.take<double>(nr * std::max<int64_t>(3 * e.nblk_hop, e.nblk_e));
+  e.nblk_e = cg_num_blocks(n);
+  e.part = c.take<double>(nr * std::max<int64_t>(3 * e.nblk_hop, red_num_blocks(n)));
+  e.part_e = c.take<double>(nr * e.nblk_e);
   if (mode) e.part_ru = c.take<double>(nr * 3 * e.nblk_hop);
   e.part_true = c.take<double>(np * 3 * e.nblk_hop);
   e.sums_true = c.take<double>(np * 3);
@@ -413,10 +426,11 @@ CgDev cg_view(const Engine& e, int32_t nblk_hop, bool fp32) {
   d.sigma = e.sigma;
   d.seed = e.seed;
   d.part = e.part;
+  d.part_e = e.part_e;
   d.part_ru = e.part_ru;
   d.coef = e.coef;
-  d.cslots = std::max(e.nslot, e.nslot32);
-  d.nslot = fp32 ? d.cslots : e.nslot;
+  d.cslots = coef_slots(e);
+  d.nslot = fp32 ? std::max(e.nslot, e.nslot32) : e.nslot;
   d.ring64 = e.ring;
   d.rb64 = (int64_t)e.nslot * field_reals(e.g) * 8;
   d.nslot64 = e.nslot;
@@ -523,7 +537,7 @@ rmh_status engine_solve(Engine& e, const double* U64, const float* U32, const do
   else
     HIP_TRY(launch_cg_start<double>(b, e.ring, e.p64, nr, cg64.rb64, n, s));
   HIP_TRY(launch_dot<double>(b, b, n, nr, e.part, s));
-  HIP_TRY(launch_cg_init(cg64, e.part, e.nblk_e, e.tol_rhs, delta, maxiter, fp32_phase ? 1 : 0, s));
+  HIP_TRY(launch_cg_init(cg64, e.part, red_num_blocks(n), e.tol_rhs, delta, maxiter, fp32_phase ? 1 : 0, s));
 
   // FP64 stencil on the seed direction: Ap = (8 + sigma0) p - H p, partial <p, Ap>
   HopArgs<double> h64{};
@@ -627,33 +641,29 @@ rmh_status engine_solve(Engine& e, const double* U64, const float* U32, const do
           ProfScope ps(RMH_PROF_STENCIL, hop_bytes(g, nr, 8, false, true), s, nr);
           HIP_TRY(launch_hop<double>(h64, c64, s));
         }
-        HIP_TRY(launch_cg_alpha(cg64, s));
         {
           ProfScope ps(RMH_PROF_CG_RESIDUAL, (double)nr * n * (3 * 8.0 + (multi ? 0.0 : 24.0)), s, nr);
           HIP_TRY(launch_cg_r_update<double>(cg64, e.Ap64, e.p64, multi ? nullptr : x_hi, nullptr, n, s));
         }
-        HIP_TRY(launch_cg_beta(cg64, 0, s));
         {
           ProfScope ps(RMH_PROF_CG_RESIDUAL, (double)nr * n * 3 * 8.0, s, nr);
-          HIP_TRY(launch_cg_p_update<double>(cg64, e.p64, nullptr, nullptr, n, s));
+          HIP_TRY(launch_cg_p_update<double>(cg64, e.p64, nullptr, nullptr, 0, n, s));
         }
       } else {
         {
           ProfScope ps(RMH_PROF_STENCIL, hop_bytes(g, nr, 4, false, true), s, nr);
           HIP_TRY(launch_hop<float>(h32, c32, s));
         }
-        HIP_TRY(launch_cg_alpha(cg32, s));
         {
           ProfScope ps(RMH_PROF_CG_RESIDUAL, (double)nr * n * 3 * 4.0, s, nr);
           HIP_TRY(launch_cg_r_update<float>(cg32, e.Ap32, e.p32, nullptr, e.r64, n, s));
         }
-        HIP_TRY(launch_cg_beta(cg32, 1, s));
         {
           ProfScope ps(RMH_PROF_CG_RESIDUAL, (double)nr * n * 5 * 4.0, s, nr);
-          HIP_TRY(launch_cg_p_update<float>(cg32, e.p32, e.x_lo, x_hi, n, s));
+          HIP_TRY(launch_cg_p_update<float>(cg32, e.p32, e.x_lo, x_hi, 1, n, s));
         }
-        // reliable update decided by this iteration's beta kernel (blocks of rhs without a
-        // pending update exit at once): the p update has folded the seed solution into FP64,
+        // reliable update decided by this iteration's direction update (blocks of rhs without a
+        // pending update exit at once), which has folded the seed solution into FP64,
         // now its FP64 residual; the stencil's bytes are added once the update count is known
         {
           ProfScope ps(RMH_PROF_STENCIL, 0.0, s, 0.0);
@@ -930,8 +940,8 @@ rmh_status check_solver(const rmh_solver* sv) {
     return fail(RMH_E_ARG, "solver delta = %g must lie in (0, 1)", sv->delta);
   if (!(sv->mixed_switch < 1.0) || sv->mixed_switch != sv->mixed_switch)
     return fail(RMH_E_ARG, "solver mixed_switch = %g must be < 1", sv->mixed_switch);
-  if (sv->basis < 0 || sv->basis > kMaxSlots - 1)
-    return fail(RMH_E_ARG, "solver basis = %d outside [0, %d]", sv->basis, kMaxSlots - 1);
+  if (sv->basis < 0 || sv->basis > kMaxBasis)
+    return fail(RMH_E_ARG, "solver basis = %d outside [0, %d]", sv->basis, kMaxBasis);
   if (!(sv->multishift_target >= 0.0 && sv->multishift_target <= 1e6) || !(sv->multishift_target * sv->tol < 1.0))
     return fail(RMH_E_ARG, "solver multishift_target = %g must lie in [0, 1e6] with multishift_target * tol < 1",
                 sv->multishift_target);

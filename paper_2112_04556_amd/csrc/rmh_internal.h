@@ -13,8 +13,6 @@ namespace rmh {
 
 constexpr int kBlock = 256;        // threads per block for site and element kernels
 constexpr int kRedBlock = 256;     // threads of the per-rhs scalar kernels
-constexpr int kCgBlock = 512;      // threads of the CG alpha and beta kernels: one (shift, coefficient)
-                                   // pair each for 12 shifts over segments of up to 40 iterations
 constexpr int kMaxFilterWindows = 64;
 constexpr int kMaxSpectrumWindows = 4096;   // windows of a power spectrum (host-side sums only)
 constexpr int kMaxChebDegree = 100000;
@@ -150,12 +148,13 @@ struct CgDev {
   int32_t* act_next;     // [n_rhs][n_shift]
   const double* sigma;   // [n_rhs][n_shift]
   const int32_t* seed;   // [n_rhs]
-  double* part;          // partials scratch [n_rhs][nblk_max]
+  double* part;          // partials of the stencil [n_rhs][3][nblk_hop]
+  double* part_e;        // partials of the residual update [n_rhs][nblk_e]
   double* part_ru;       // partials of the FP64 residual stencil [n_rhs][3][nblk_ru] (mixed precision)
   double* coef;          // [n_rhs][n_shift][2 + 2 cslots]: a, b, d[cslots], e[cslots]
   int32_t nslot;         // segment capacity guard of this view: FP64 ring slots, or (FP32 view)
-                         // the coefficient slots
-  int32_t cslots;        // coefficient slots: entries a segment can hold
+                         // the entries a segment can hold in all
+  int32_t cslots;        // coefficient slots: the latter in whole groups of eight
   // the residual rings: FP64 slots (nslot64 per rhs, rb64 bytes per rhs) and, with mixed
   // precision, FP32 slots (nslot32 per rhs, rb32 bytes per rhs) in a region of their own
   void* ring64;
@@ -173,41 +172,49 @@ struct CgDev {
 // (Base32 + i - K0) % nslot32 (K0: the entry held in FP32 slot Base32).  FP64 phases have
 // K64 = kAllFp64; at the switch to FP32 the segment goes on, K64 = M + 1 and the current FP64
 // residual is copied to FP32 slot Base32 as entry K0 = M; after an FP32-phase flush K64 = K0 = 0.
-constexpr int kMaxSlots = 33;
+// A segment holds up to 32 iterations where the caller sets its length; the default on small
+// lattices (fields of at most 32 MiB) goes up to 47.
+constexpr int kMaxBasis = 32;
+constexpr int kMaxSlots = 48;
+constexpr int32_t kLongSegmentSites = 1 << 17;
 constexpr int32_t kAllFp64 = 1 << 30;
 // scalar slots per rhs
+// RRc, MaxRc: RR and MaxR as the residual update of the current iteration found them
 enum : int { kScRR = 0, kScAlpha, kScAlphaPrev, kScBetaPrev, kScBnorm2, kScMaxR, kScTolAbs, kScIters,
-             kScRU, kScDelta, kScMaxIter, kScN };
+             kScRU, kScDelta, kScMaxIter, kScRRc, kScMaxRc, kScN };
 // per (rhs, shift) slots; Seg: the shift was updated in the current segment
 enum : int { kShZeta = 0, kShZetaPrev, kShZetaNext, kShCx, kShCr, kShCp, kShSeg, kShN };
 // int flags per rhs
-// Run: the rhs still iterates (read by the stencil of the next iteration);
-// Live: the current iteration is being carried out (set by the alpha kernel), so the
-// update kernels of the iteration in which a rhs converges still run once.
+// Run: the rhs still iterates (read by the stencil and the residual update of the next iteration);
+// Live: the current iteration is being carried out (set by the residual update), so the direction
+// update of the iteration in which a rhs converges still runs once; Mn: M + 1, set with Live.
 // Base, M: FP64 ring slot of the segment's first residual, index of the current residual in it;
 // K64, K0, Base32: the FP64 entries of the segment and the FP32 slot of entry K0 (above).
-enum : int { kFlRun = 0, kFlLive, kFlStatus, kFlNeedRU, kFlRUMask, kFlBase, kFlM, kFlK64, kFlK0, kFlBase32, kFlN };
+enum : int { kFlRun = 0, kFlLive, kFlStatus, kFlNeedRU, kFlMn, kFlBase, kFlM, kFlK64, kFlK0, kFlBase32, kFlN };
 enum : int { kStOk = 0, kStNoConv = 1, kStBreakdown = 2 };
 
 // fp32_start: the solve runs in FP32 from its first iteration (its segment has no FP64 entries)
 hipError_t launch_cg_init(const CgDev& cg, const double* bn2_partials, int32_t nblk, const double* tol_rel,
                           double delta, int32_t maxiter, int32_t fp32_start, hipStream_t s);
-hipError_t launch_cg_alpha(const CgDev& cg, hipStream_t s);
-hipError_t launch_cg_beta(const CgDev& cg, int32_t mixed, hipStream_t s);
+// blocks (and partials) per rhs of the residual and direction updates
+int cg_num_blocks(int64_t n_reals);
 // slot 0 of the ring region (ring, rhs_bytes per rhs) = (T) b, p = (T) b for every rhs
 template <typename T>
 hipError_t launch_cg_start(const double* b, void* ring, T* p, int32_t nr, int64_t rhs_bytes, int64_t n_reals,
                            hipStream_t s);
-// next residual r' = r - alpha Ap into the next segment entry (r taken from r64 when a reliable
-// update was consumed), partial <r', r'>; with x_hi non-null also x_hi[seed] += alpha p
+// alpha (from the stencil's partials) and the next residual r' = r - alpha Ap into the next segment entry (r
+// taken from r64 when a reliable update is consumed), partial <r', r'>; the shifts' zeta and x
+// coefficients; with x_hi non-null also x_hi[seed] += alpha p
 template <typename T>
 hipError_t launch_cg_r_update(const CgDev& cg, const T* Ap, const T* p, double* x_hi, const double* r64,
                               int64_t n_reals, hipStream_t s);
-// seed direction p = r' + beta p (while the rhs runs); with x_lo non-null also x_lo += alpha p
-// (the FP32 increment of the seed's solution, FP32 phase), and with x_hi non-null, for the rhs
-// with a pending reliable update, x_hi[seed] += x_lo, x_lo = 0 in the same pass
+// beta and the seed direction p = r' + beta p; the shifts' p coefficients, convergence, the decision for a
+// reliable update (mixed); with x_lo non-null also x_lo += alpha p (the FP32 increment of the seed's
+// solution, FP32 phase), and with x_hi non-null, for the rhs that need a reliable update,
+// x_hi[seed] += x_lo, x_lo = 0 in the same pass
 template <typename T>
-hipError_t launch_cg_p_update(const CgDev& cg, T* p, float* x_lo, double* x_hi, int64_t n_reals, hipStream_t s);
+hipError_t launch_cg_p_update(const CgDev& cg, T* p, float* x_lo, double* x_hi, int32_t mixed, int64_t n_reals,
+                              hipStream_t s);
 // x_hi[seed] += x_lo, x_lo = 0 for every rhs (all, the end of a mixed solve) or those with a
 // pending reliable update
 hipError_t launch_cg_xfold(const CgDev& cg, float* x_lo, double* x_hi, int32_t all, int64_t n_reals, hipStream_t s);

@@ -240,7 +240,7 @@ __global__ void k_cg_init(CgDev cg, const double* bn2_part, int32_t nblk, const 
     fl[kFlStatus] = (bn2 == bn2) ? kStOk : kStBreakdown;   // NaN source
     if (!(bn2 == bn2)) fl[kFlRun] = 0;
     fl[kFlNeedRU] = 0;
-    fl[kFlRUMask] = 0;
+    fl[kFlMn] = 0;
     fl[kFlLive] = 0;
     fl[kFlBase] = 0;
     fl[kFlM] = 0;
@@ -278,94 +278,80 @@ hipError_t launch_cg_init(const CgDev& cg, const double* bn2_partials, int32_t n
   return hipGetLastError();
 }
 
-// alpha_k = rr / <p, A0 p>;  zeta_{k+1}^j and the x-update coefficient of every active shift,
-// applied to the segment coefficients of the non-seed shifts: x_j += cx_j p_j
-__global__ void k_cg_alpha(CgDev cg) {
-  const int32_t v = blockIdx.x;
+// One iteration is three launches: the stencil (Ap and the partials of <p, Ap>), the residual update
+// with alpha, the direction update with beta.  Every block of an update sums the partials itself (the
+// same values in the same order, so every block gets the same bits) instead of waiting for a scalar
+// kernel of its own; the last block of each rhs carries out the scalar state and the shift
+// coefficients meanwhile.  A launch never writes what its other blocks read: the residual update's
+// last block writes Alpha, RRc, MaxRc, Mn and Live for the direction update, whose last block writes RR,
+// MaxR, M, Run and NeedRU for the next iteration.  (Run is cleared early on a breakdown, which every
+// block then finds by itself.)  With alpha and beta in kernels of their own an iteration took five
+// launches, the two of 4 to 5 us each: 12^4, one field, 36 us an iteration.
+
+// Fixed-order sum of p[0, n) by the whole block, in every thread.
+__device__ __forceinline__ double block_total(const double* p, int32_t n, double (*lds)[16], double* bc) {
+  const double t = block_sum_array(p, n, lds);
+  if (threadIdx.x == 0) *bc = t;
+  __syncthreads();
+  const double r = *bc;
+  __syncthreads();
+  return r;
+}
+
+struct CgAlpha {
+  double rr, alpha;   // the residual norm squared the iteration starts from, and its step
+  bool ok;
+};
+
+// alpha_k = rr / <p, A0 p>; with ru the residual is the FP64 one of a reliable update issued at the end of the
+// previous iteration (r64 = b - (Delta + sigma0) x_seed), which replaces the recursive residual from now on
+__device__ __forceinline__ CgAlpha cg_alpha(const CgDev& cg, int32_t v, bool ru, double rr_sc, double (*lds)[16],
+                                            double* bc) {
+  CgAlpha r;
+  r.rr = ru ? block_total(cg.part_ru + ((int64_t)v * 3 + 2) * cg.nblk_ru, cg.nblk_ru, lds, bc) : rr_sc;
+  const double pAp = block_total(cg.part + ((int64_t)v * 3 + 1) * cg.nblk_hop, cg.nblk_hop, lds, bc);
+  r.alpha = r.rr / pAp;
+  r.ok = pAp > 0.0 && r.alpha == r.alpha && r.alpha < 1e300;
+  return r;
+}
+
+// The scalar side of the residual update (one block per rhs): zeta_{k+1}^j and the x-update coefficient
+// of every active shift, applied to the segment coefficients of the non-seed shifts: x_j += cx_j p_j
+__device__ __forceinline__ void cg_alpha_state(const CgDev& cg, int32_t v, bool ru, const CgAlpha& al) {
   int32_t* fl = cg.flags + (int64_t)v * kFlN;
   double* sc = cg.sc + (int64_t)v * kScN;
   const int32_t ns = cg.n_shift;
   const int32_t nc = 2 + 2 * cg.cslots;
   const int32_t tid = threadIdx.x;
-  // Every load that does not need alpha is issued first (each address is valid whatever the
-  // flags hold), so the block waits on memory a few times instead of once per dependent step.
-  const int32_t run = fl[kFlRun];
   const int32_t m = fl[kFlM];
-  const int32_t ru = cg.part_ru ? fl[kFlNeedRU] : 0;
   const int32_t seed = cg.seed[v];
-  const double rr_sc = sc[kScRR], ap = sc[kScAlphaPrev], bp = sc[kScBetaPrev];
-  // this thread's shift (n_shift <= blockDim)
-  int32_t on = 0;
-  double z = 0.0, zp = 0.0, sig = 0.0;
-  if (tid < ns) {
-    const int64_t vj = (int64_t)v * ns + tid;
-    on = cg.act_next[vj];
-    z = cg.sh[vj * kShN + kShZeta];
-    zp = cg.sh[vj * kShN + kShZetaPrev];
-    sig = cg.sigma[vj];
-  }
-  const double s0 = cg.sigma[(int64_t)v * ns + seed];
-  // this thread's (shift, coefficient) pair when they all fit in the block: q = 0 the p_j0
-  // coefficient (x_j0 += cx p_j0), q = 1 + i the ring entry i <= m (d_ji += cx e_ji).  A shift is
-  // updated only while m < nslot <= cslots; past that (a single shift's segment index grows
-  // without flushes) the pairs stop at the last coefficient slot so every read stays in its row.
-  const int32_t per = min(m, cg.cslots - 1) + 2;
-  const bool one_pass = ns * per <= (int32_t)blockDim.x;
-  int32_t pj = 0, pq = 0;
-  double c_dst = 0.0, c_src = 0.0;
-  if (one_pass && tid < ns * per) {
-    pj = tid / per;
-    pq = tid - pj * per;
-    const double* cf = cg.coef + ((int64_t)v * ns + pj) * nc;
-    c_dst = pq == 0 ? cf[0] : cf[1 + pq];
-    c_src = pq == 0 ? cf[1] : cf[1 + pq + cg.cslots];
-  }
-  if (run == 0) {
-    if (tid == 0) fl[kFlLive] = 0;
-    return;
-  }
-  __shared__ double lds[1][16];
-  // a reliable update issued at the end of the previous iteration: its FP64 residual
-  // r64 = b - (Delta + sigma0) x_seed replaces the recursive residual from now on
-  double rr_true = 0.0;
-  if (ru) rr_true = block_sum_array(cg.part_ru + ((int64_t)v * 3 + 2) * cg.nblk_ru, cg.nblk_ru, lds);
-  const double pAp = block_sum_array(cg.part + ((int64_t)v * 3 + 1) * cg.nblk_hop, cg.nblk_hop, lds);
-  __shared__ double s_alpha;
-  __shared__ int s_ok;
+  const double ap = sc[kScAlphaPrev], bp = sc[kScBetaPrev];
+  const double alpha = al.alpha;
   if (tid == 0) {
-    if (ru) {
-      sc[kScRR] = rr_true;
-      sc[kScMaxR] = sqrt(rr_true);
-      sc[kScRU] += 1.0;
-      fl[kFlNeedRU] = 0;
-      fl[kFlRUMask] = 1;
-    }
-    const double rr = ru ? rr_true : rr_sc;
-    const double alpha = rr / pAp;
-    s_ok = (pAp > 0.0 && alpha == alpha && alpha < 1e300) ? 1 : 0;
-    s_alpha = alpha;
-    if (s_ok) {
-      sc[kScAlpha] = alpha;
-      fl[kFlLive] = 1;
-    } else {
+    sc[kScRRc] = al.rr;
+    sc[kScMaxRc] = ru ? sqrt(al.rr) : sc[kScMaxR];
+    if (ru) sc[kScRU] += 1.0;
+    sc[kScAlpha] = alpha;
+    fl[kFlMn] = m + 1;
+    fl[kFlLive] = al.ok ? 1 : 0;
+    if (!al.ok) {
       fl[kFlStatus] = kStBreakdown;
       fl[kFlRun] = 0;
-      fl[kFlLive] = 0;
     }
   }
-  __syncthreads();
-  if (!s_ok) return;
-  const double alpha = s_alpha;
+  if (!al.ok) return;
   __shared__ double s_cx[kMaxShifts];
   __shared__ int s_upd[kMaxShifts];
-  // per shift: zeta_{k+1} and the x coefficient
+  const double s0 = cg.sigma[(int64_t)v * ns + seed];
   if (tid < ns) {
     const int64_t vj = (int64_t)v * ns + tid;
-    cg.act[vj] = on;
+    const int32_t on = cg.act_next[vj];
     double* sh = cg.sh + vj * kShN;
+    cg.act[vj] = on;
     int upd = 0;
     if (on) {
-      const double ds = sig - s0;
+      const double z = sh[kShZeta], zp = sh[kShZetaPrev];
+      const double ds = cg.sigma[vj] - s0;
       const double zn = z * zp * ap / (ap * zp * (1.0 + alpha * ds) + alpha * bp * (zp - z));
       const double cx = alpha * zn / z;
       sh[kShZetaNext] = zn;
@@ -379,92 +365,35 @@ __global__ void k_cg_alpha(CgDev cg) {
     s_upd[tid] = upd;
   }
   __syncthreads();
-  // x_j += cx_j p_j on the segment coefficients, one (shift, coefficient) pair per thread
-  if (one_pass) {
-    if (tid < ns * per && s_upd[pj]) {
-      double* cf = cg.coef + ((int64_t)v * ns + pj) * nc;
-      cf[pq == 0 ? 0 : 1 + pq] = fma(s_cx[pj], c_src, c_dst);
-    }
-  } else {
-    for (int t = tid; t < ns * per; t += blockDim.x) {
-      const int32_t jj = t / per, q = t - jj * per;
-      if (!s_upd[jj]) continue;
-      double* cf = cg.coef + ((int64_t)v * ns + jj) * nc;
-      if (q == 0)
-        cf[0] = fma(s_cx[jj], cf[1], cf[0]);
-      else
-        cf[1 + q] = fma(s_cx[jj], cf[1 + q + cg.cslots], cf[1 + q]);
-    }
+  // one (shift, coefficient) pair per thread and round: q = 0 the p_j0 coefficient (x_j0 += cx p_j0),
+  // q = 1 + i the ring entry i <= m (d_ji += cx e_ji).  A shift is updated only while m < nslot <= cslots;
+  // past that (a single shift's segment index grows without flushes) the pairs stop at the last
+  // coefficient slot
+  const int32_t per = min(m, cg.cslots - 1) + 2;
+  for (int t = tid; t < ns * per; t += blockDim.x) {
+    const int32_t jj = t / per, q = t - jj * per;
+    if (!s_upd[jj]) continue;
+    double* cf = cg.coef + ((int64_t)v * ns + jj) * nc;
+    if (q == 0)
+      cf[0] = fma(s_cx[jj], cf[1], cf[0]);
+    else
+      cf[1 + q] = fma(s_cx[jj], cf[1 + q + cg.cslots], cf[1 + q]);
   }
 }
 
-hipError_t launch_cg_alpha(const CgDev& cg, hipStream_t s) {
-  if (cg.n_shift > kMaxShifts) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_cg_alpha, dim3(cg.n_rhs), dim3(kCgBlock), 0, s, cg);
-  return hipGetLastError();
-}
-
-// beta_k = rr_new / rr; shifted beta and p-update coefficients (applied to the segment
-// coefficients of the non-seed shifts: p_j = cr_j r' + cp_j p_j); convergence and freezing;
-// the new residual becomes the current ring entry
-__global__ void k_cg_beta(CgDev cg, int32_t mixed) {
-  const int32_t v = blockIdx.x;
+// The scalar side of the direction update (one block per rhs): beta_k = rr_new / rr, shifted beta and
+// p-update coefficients (applied to the segment coefficients of the non-seed shifts: p_j = cr_j r' +
+// cp_j p_j); convergence and freezing; the new residual becomes the current ring entry
+__device__ __forceinline__ void cg_beta_state(const CgDev& cg, int32_t v, int32_t mixed, double rrn, double beta,
+                                              bool need_ru) {
   int32_t* fl = cg.flags + (int64_t)v * kFlN;
   double* sc = cg.sc + (int64_t)v * kScN;
   const int32_t ns = cg.n_shift;
   const int32_t nc = 2 + 2 * cg.cslots;
   const int32_t tid = threadIdx.x;
-  // loads that do not need the new residual norm go out first (valid addresses whatever the
-  // flags hold)
-  const int32_t live = fl[kFlLive];
   const int32_t m = fl[kFlM];
   const int32_t seed = cg.seed[v];
-  const double rr_old = sc[kScRR], tolabs = sc[kScTolAbs];
-  // the scalars thread 0 updates after the shift pass, loaded now so that pass ends in no load
-  double alpha0 = 0.0, iters0 = 0.0, maxit0 = 0.0, maxr0 = 0.0, delta0 = 0.0;
-  if (tid == 0) {
-    alpha0 = sc[kScAlpha];
-    iters0 = sc[kScIters];
-    maxit0 = sc[kScMaxIter];
-    maxr0 = sc[kScMaxR];
-    delta0 = sc[kScDelta];
-  }
-  int32_t act = 0;
-  double z = 0.0, zn = 0.0;
-  if (tid < ns) {
-    const int64_t vj = (int64_t)v * ns + tid;
-    act = cg.act[vj];
-    z = cg.sh[vj * kShN + kShZeta];
-    zn = cg.sh[vj * kShN + kShZetaNext];
-  }
-  // this thread's (shift, coefficient) pair when they all fit in the block: q = 0 the p_j0
-  // coefficient, q = 1 + i the ring entry i <= m (both scaled by cp_j), q = m + 2 the new
-  // entry m + 1 (set to cr_j).  Updates need m + 1 < nslot <= cslots; the pairs stop at the
-  // last coefficient slot for larger m (reads in the row, nothing written).
-  const int32_t mc = min(m, cg.cslots - 2);
-  const int32_t per = mc + 3;
-  const bool one_pass = ns * per <= (int32_t)blockDim.x;
-  int32_t pj = 0, pq = 0;
-  double c_old = 0.0;
-  if (one_pass && tid < ns * per) {
-    pj = tid / per;
-    pq = tid - pj * per;
-    const double* cf = cg.coef + ((int64_t)v * ns + pj) * nc;
-    if (pq == 0)
-      c_old = cf[1];
-    else if (pq <= mc + 1)
-      c_old = cf[2 + cg.cslots + pq - 1];
-  }
-  if (live == 0) return;
-  __shared__ double lds[1][16];
-  __shared__ double s_rrn;
-  {
-    const double t = block_sum_array(cg.part + (int64_t)v * cg.nblk_e, cg.nblk_e, lds);
-    if (tid == 0) s_rrn = t;  // the block sum is valid in thread 0 only
-    __syncthreads();
-  }
-  const double rrn = s_rrn;
-  const double beta = rrn / rr_old;
+  const double tolabs = sc[kScTolAbs];
   const double rnorm = sqrt(rrn);
   __shared__ double s_cp[kMaxShifts], s_cr[kMaxShifts];
   __shared__ int s_upd[kMaxShifts];
@@ -474,8 +403,10 @@ __global__ void k_cg_beta(CgDev cg, int32_t mixed) {
   if (tid < ns) {
     const int64_t vj = (int64_t)v * ns + tid;
     double* sh = cg.sh + vj * kShN;
+    const int32_t act = cg.act[vj];
     int upd = 0;
     if (act) {
+      const double z = sh[kShZeta], zn = sh[kShZetaNext];
       const double ratio = zn / z;
       const double cr = zn, cp = beta * ratio * ratio;
       sh[kShCr] = cr;
@@ -507,60 +438,42 @@ __global__ void k_cg_beta(CgDev cg, int32_t mixed) {
     if (any_other) seed_next = 1;
     if (seed_next != s_seed_keep) cg.act_next[vs] = seed_next;
     const int32_t any = any_other | seed_next;
-    const double iters = iters0 + 1.0;
-    sc[kScAlphaPrev] = alpha0;
+    const double iters = sc[kScIters] + 1.0;
+    sc[kScAlphaPrev] = sc[kScAlpha];
     sc[kScBetaPrev] = beta;
     sc[kScRR] = rrn;
     sc[kScIters] = iters;
-    fl[kFlRUMask] = 0;  // the residual update of this iteration has consumed it
     fl[kFlM] = m + 1;
+    fl[kFlNeedRU] = need_ru ? 1 : 0;
     if (!(rrn == rrn)) {
       fl[kFlStatus] = kStBreakdown;
       fl[kFlRun] = 0;
     } else if (!any) {
       fl[kFlRun] = 0;
-    } else if (iters >= maxit0) {
+    } else if (iters >= sc[kScMaxIter]) {
       fl[kFlStatus] = kStNoConv;
       fl[kFlRun] = 0;
     }
-    if (mixed) {
-      const double maxr = rnorm > maxr0 ? rnorm : maxr0;
-      if (rnorm > maxr0) sc[kScMaxR] = rnorm;
-      if (rnorm < delta0 * maxr) fl[kFlNeedRU] = 1;
-    }
+    if (mixed) sc[kScMaxR] = rnorm > sc[kScMaxRc] ? rnorm : sc[kScMaxRc];
   }
   __syncthreads();
-  // p_j = cr_j r' + cp_j p_j on the segment coefficients, one (shift, coefficient) pair per thread
-  if (one_pass) {
-    if (tid < ns * per && s_upd[pj]) {
-      double* cf = cg.coef + ((int64_t)v * ns + pj) * nc;
-      if (pq == 0)
-        cf[1] = c_old * s_cp[pj];
-      else if (pq <= m + 1)
-        cf[2 + cg.cslots + pq - 1] = c_old * s_cp[pj];
-      else
-        cf[2 + cg.cslots + m + 1] = s_cr[pj];
-    }
-  } else {
-    for (int t = tid; t < ns * per; t += blockDim.x) {
-      const int32_t jj = t / per, q = t - jj * per;
-      if (!s_upd[jj]) continue;
-      double* cf = cg.coef + ((int64_t)v * ns + jj) * nc;
-      double* e = cf + 2 + cg.cslots;
-      if (q == 0)
-        cf[1] *= s_cp[jj];
-      else if (q <= m + 1)
-        e[q - 1] *= s_cp[jj];
-      else
-        e[m + 1] = s_cr[jj];
-    }
+  // p_j = cr_j r' + cp_j p_j on the segment coefficients: q = 0 the p_j0 coefficient, q = 1 + i the ring
+  // entry i <= m (both scaled by cp_j), q = m + 2 the new entry m + 1 (set to cr_j).  Updates need m + 1 <
+  // nslot <= cslots
+  const int32_t mc = min(m, cg.cslots - 2);
+  const int32_t per = mc + 3;
+  for (int t = tid; t < ns * per; t += blockDim.x) {
+    const int32_t jj = t / per, q = t - jj * per;
+    if (!s_upd[jj]) continue;
+    double* cf = cg.coef + ((int64_t)v * ns + jj) * nc;
+    double* e = cf + 2 + cg.cslots;
+    if (q == 0)
+      cf[1] *= s_cp[jj];
+    else if (q <= m + 1)
+      e[q - 1] *= s_cp[jj];
+    else
+      e[m + 1] = s_cr[jj];
   }
-}
-
-hipError_t launch_cg_beta(const CgDev& cg, int32_t mixed, hipStream_t s) {
-  if (cg.n_shift > kMaxShifts) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_cg_beta, dim3(cg.n_rhs), dim3(kCgBlock), 0, s, cg, mixed);
-  return hipGetLastError();
 }
 
 // ring slot i of rhs v in a ring region of rhs_bytes per rhs, viewed as T (slots of n_reals)
@@ -613,68 +526,103 @@ hipError_t launch_cg_start(const double* b, void* ring, T* p, int32_t nr, int64_
 template hipError_t launch_cg_start<double>(const double*, void*, double*, int32_t, int64_t, int64_t, hipStream_t);
 template hipError_t launch_cg_start<float>(const double*, void*, float*, int32_t, int64_t, int64_t, hipStream_t);
 
+// The element kernels of the iteration take their vectors in pieces of 16 bytes per lane, consecutive
+// lanes consecutive pieces; a block covers kCgChunk reals per step, all loads of a step in flight
+// together, and enough steps that about 1024 blocks and as many partials remain per rhs.
+constexpr int kCgChunk = 2048;
+static int cg_steps(int64_t n_reals) {
+  return (int)std::max<int64_t>(1, std::min<int64_t>(32, n_reals / ((int64_t)kCgChunk * 1024)));
+}
+int cg_num_blocks(int64_t n_reals) {
+  const int64_t c = (int64_t)kCgChunk * cg_steps(n_reals);
+  return (int)((n_reals + c - 1) / c);
+}
 template <typename T>
-__global__ void k_cg_r(CgDev cg, const T* __restrict__ Ap, const T* __restrict__ p, double* __restrict__ x_hi,
-                       const double* __restrict__ r64, int64_t n, int32_t steps) {
+using Piece = T __attribute__((ext_vector_type(16 / sizeof(T))));
+
+// r' = r - alpha Ap (and x_hi[seed] += alpha p), with alpha; the last block of each rhs keeps the state
+template <typename T>
+__global__ void __launch_bounds__(256) k_cg_r(CgDev cg, const T* __restrict__ Ap, const T* __restrict__ p,
+                                              double* __restrict__ x_hi, const double* __restrict__ r64, int64_t n,
+                                              int32_t steps) {
+  constexpr int N = 16 / sizeof(T), U = kCgChunk / (256 * N);
+  __shared__ double lds[1][16];
+  __shared__ double s_bc;
   const int32_t v = blockIdx.y;
-  const int32_t* fl = cg.flags + (int64_t)v * kFlN;
-  // the per-rhs state in one batch of independent loads, ahead of any branch on it
-  const int32_t live = fl[kFlLive], ru_mask = fl[kFlRUMask];
+  int32_t* fl = cg.flags + (int64_t)v * kFlN;
+  const bool state = blockIdx.x + 1 == gridDim.x;
+  const bool ru = cg.part_ru && fl[kFlNeedRU] != 0;
   const int32_t m = fl[kFlM];
   const int32_t st[3] = {fl[kFlBase], fl[kFlBase32], fl[kFlK0]};
-  const int32_t seed = cg.seed[v];
-  const double alpha_d = cg.sc[(int64_t)v * kScN + kScAlpha];
-  if (live == 0) return;
-  const int32_t from64 = r64 ? ru_mask : 0;
+  const double rr_sc = cg.sc[(int64_t)v * kScN + kScRR];
+  if (fl[kFlRun] == 0) {
+    if (state && threadIdx.x == 0) fl[kFlLive] = 0;
+    return;
+  }
+  if (state) {
+    const CgAlpha al = cg_alpha(cg, v, ru, rr_sc, lds, &s_bc);
+    cg_alpha_state(cg, v, ru, al);
+    return;
+  }
   const T* rc = entry<T>(cg, v, st, m, n);
   T* rn = entry<T>(cg, v, st, m + 1, n);
-  const T alpha = (T)alpha_d;
   const T* av = Ap + (int64_t)v * n;
   const T* pv = p + (int64_t)v * n;
-  double* xs = x_hi ? x_hi + ((int64_t)v * cg.n_shift + seed) * n : nullptr;
+  double* xs = x_hi ? x_hi + ((int64_t)v * cg.n_shift + cg.seed[v]) * n : nullptr;
   const double* r64v = r64 ? r64 + (int64_t)v * n : nullptr;
+  const bool from64 = r64 && ru;
+  Piece<T> r0[U], a4[U];
+  auto load = [&](int64_t i0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = i0 + (int64_t)u * 256 * N;
+      if (i >= n) break;
+      if (from64) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) r0[u][k] = (T)r64v[i + k];
+      } else {
+        r0[u] = *(const Piece<T>*)(rc + i);
+      }
+      a4[u] = *(const Piece<T>*)(av + i);
+    }
+  };
+  const int64_t b0 = (int64_t)blockIdx.x * steps * kCgChunk + threadIdx.x * N;
+  load(b0);   // in flight while the partials are summed
+  const CgAlpha al = cg_alpha(cg, v, ru, rr_sc, lds, &s_bc);
+  if (!al.ok) return;
+  const T alpha = (T)al.alpha;
   double d[1] = {0.0};
   for (int32_t t = 0; t < steps; ++t) {
-    const int64_t i0 = (((int64_t)blockIdx.x * steps + t) * blockDim.x + threadIdx.x) * 4;
-    if (i0 < n) {
-      // (the residual source is uniform per field: one branch around whole vector loads)
-      T r0[4], a4[4];
-      if (from64) {
-        double rd[4];
+    const int64_t i0 = b0 + (int64_t)t * kCgChunk;
+    if (t > 0) load(i0);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) rd[k] = r64v[i0 + k];
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = i0 + (int64_t)u * 256 * N;
+      if (i >= n) break;
+      Piece<T> r1;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) r0[k] = (T)rd[k];
-      } else {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) r0[k] = rc[i0 + k];
+      for (int k = 0; k < N; ++k) {
+        r1[k] = fmadd(-alpha, a4[u][k], r0[u][k]);
+        d[0] = fma((double)r1[k], (double)r1[k], d[0]);
       }
-#pragma unroll
-      for (int k = 0; k < 4; ++k) a4[k] = av[i0 + k];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const T r1 = fmadd(-alpha, a4[k], r0[k]);
-        rn[i0 + k] = r1;
-        d[0] = fma((double)r1, (double)r1, d[0]);
-      }
+      *(Piece<T>*)(rn + i) = r1;
       if (xs) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) xs[i0 + k] = fma(alpha_d, (double)pv[i0 + k], xs[i0 + k]);
+        for (int k = 0; k < N; ++k) xs[i + k] = fma(al.alpha, (double)pv[i + k], xs[i + k]);
       }
     }
   }
-  __shared__ double lds[1][16];
   block_sum<1>(d, lds);
-  if (threadIdx.x == 0) cg.part[(int64_t)v * cg.nblk_e + blockIdx.x] = d[0];
+  if (threadIdx.x == 0) cg.part_e[(int64_t)v * cg.nblk_e + blockIdx.x] = d[0];
 }
 
 template <typename T>
 hipError_t launch_cg_r_update(const CgDev& cg, const T* Ap, const T* p, double* x_hi, const double* r64,
                               int64_t n_reals, hipStream_t s) {
-  if (cg.nblk_e != red_num_blocks(n_reals)) return hipErrorInvalidValue;
+  if (cg.n_shift > kMaxShifts || cg.nblk_e != cg_num_blocks(n_reals)) return hipErrorInvalidValue;
   if (sizeof(T) == 4 && !cg.ring32) return hipErrorInvalidValue;
-  dim3 grid(cg.nblk_e, cg.n_rhs);
-  hipLaunchKernelGGL((k_cg_r<T>), grid, dim3(kBlock), 0, s, cg, Ap, p, x_hi, r64, n_reals, red_steps(n_reals));
+  dim3 grid(cg.nblk_e + 1, cg.n_rhs);
+  hipLaunchKernelGGL((k_cg_r<T>), grid, dim3(256), 0, s, cg, Ap, p, x_hi, r64, n_reals, cg_steps(n_reals));
   return hipGetLastError();
 }
 template hipError_t launch_cg_r_update<double>(const CgDev&, const double*, const double*, double*, const double*,
@@ -682,62 +630,89 @@ template hipError_t launch_cg_r_update<double>(const CgDev&, const double*, cons
 template hipError_t launch_cg_r_update<float>(const CgDev&, const float*, const float*, double*, const double*,
                                               int64_t, hipStream_t);
 
+// p = r' + beta p with beta, and in the FP32 phase x_lo += alpha p; the last block of each rhs keeps
+// the state.  (p is updated in the iteration its rhs converges in, too: nothing reads it then.)
 template <typename T>
-__global__ void k_cg_p(CgDev cg, T* __restrict__ p, float* __restrict__ x_lo, double* __restrict__ x_hi, int64_t n) {
+__global__ void __launch_bounds__(256) k_cg_p(CgDev cg, T* __restrict__ p, float* __restrict__ x_lo,
+                                              double* __restrict__ x_hi, int64_t n, int32_t steps, int32_t mixed) {
+  constexpr int N = 16 / sizeof(T), U = kCgChunk / (256 * N);
+  __shared__ double lds[1][16];
+  __shared__ double s_bc;
   const int32_t v = blockIdx.y;
   const int32_t* fl = cg.flags + (int64_t)v * kFlN;
   const double* scv = cg.sc + (int64_t)v * kScN;
-  // the per-rhs state in one batch of independent loads, ahead of any branch on it
-  const int32_t live = fl[kFlLive], upd_p = fl[kFlRun], need_ru = fl[kFlNeedRU];
-  const int32_t m = fl[kFlM];
+  const bool state = blockIdx.x + 1 == gridDim.x;
+  const int32_t mn = fl[kFlMn];
   const int32_t st[3] = {fl[kFlBase], fl[kFlBase32], fl[kFlK0]};
-  const int32_t seed = cg.seed[v];
-  const double beta_d = scv[kScBetaPrev], alpha_d = scv[kScAlpha];
-  if (live == 0) return;
-  if (!upd_p && !x_lo) return;
-  const int64_t i0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
-  if (i0 >= n) return;
-  const T* r = entry<T>(cg, v, st, m, n);
+  const double rr_old = scv[kScRRc], maxr = scv[kScMaxRc], delta = scv[kScDelta], alpha_d = scv[kScAlpha];
+  if (fl[kFlLive] == 0) return;
+  const T* r = entry<T>(cg, v, st, mn, n);
+  T* pv = p + (int64_t)v * n;
+  Piece<T> pold[U], rv[U];
+  auto load = [&](int64_t i0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = i0 + (int64_t)u * 256 * N;
+      if (i >= n) break;
+      pold[u] = *(const Piece<T>*)(pv + i);
+      rv[u] = *(const Piece<T>*)(r + i);
+    }
+  };
+  const int64_t b0 = (int64_t)blockIdx.x * steps * kCgChunk + threadIdx.x * N;
+  if (!state) load(b0);   // in flight while the partials are summed
+  const double rrn = block_total(cg.part_e + (int64_t)v * cg.nblk_e, cg.nblk_e, lds, &s_bc);
+  const double beta_d = rrn / rr_old;
+  // a reliable update once the residual norm fell below delta times its largest value since the last one
+  const double rnorm = sqrt(rrn);
+  const bool need_ru = mixed && rnorm < delta * (rnorm > maxr ? rnorm : maxr);
+  if (state) {
+    cg_beta_state(cg, v, mixed, rrn, beta_d, need_ru);
+    return;
+  }
   const T beta = (T)beta_d;
   const float alpha = (float)alpha_d;
-  T* pv = p + (int64_t)v * n;
-  T pold[4];
+  float* xl = x_lo ? x_lo + (int64_t)v * n : nullptr;
+  // with a reliable update due the seed's increment goes into its FP64 solution now (x_hi[seed] += x_lo,
+  // x_lo = 0), ahead of the update's FP64 residual stencil
+  double* xh = x_lo && x_hi && need_ru ? x_hi + ((int64_t)v * cg.n_shift + cg.seed[v]) * n : nullptr;
+  for (int32_t t = 0; t < steps; ++t) {
+    const int64_t i0 = b0 + (int64_t)t * kCgChunk;
+    if (t > 0) load(i0);
 #pragma unroll
-  for (int k = 0; k < 4; ++k) pold[k] = pv[i0 + k];
-  if (x_lo) {
-    // the seed's increment of this iteration, alpha p, in FP32 until the next reliable update;
-    // when this iteration's beta kernel asked for one, the increment goes into the FP64 seed
-    // solution now (x_hi[seed] += x_lo, x_lo = 0), ahead of the update's FP64 residual stencil
-    float* xv = x_lo + (int64_t)v * n + i0;
-    float xl[4];
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = i0 + (int64_t)u * 256 * N;
+      if (i >= n) break;
+      if (xl) {
+        // the seed's increment of this iteration, alpha p, in FP32 until the next reliable update
+        float inc[N];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) xl[k] = xv[k];
-    if (x_hi && need_ru) {
-      double* xh = x_hi + ((int64_t)v * cg.n_shift + seed) * n + i0;
-      double xo[4];
+        for (int k = 0; k < N; ++k) inc[k] = fmaf(alpha, (float)pold[u][k], xl[i + k]);
+        if (xh) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) xo[k] = xh[k];
+          for (int k = 0; k < N; ++k) {
+            xh[i + k] += (double)inc[k];
+            xl[i + k] = 0.0f;
+          }
+        } else {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        xh[k] = xo[k] + (double)fmaf(alpha, (float)pold[k], xl[k]);
-        xv[k] = 0.0f;
+          for (int k = 0; k < N; ++k) xl[i + k] = inc[k];
+        }
       }
-    } else {
+      Piece<T> pn;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) xv[k] = fmaf(alpha, (float)pold[k], xl[k]);
+      for (int k = 0; k < N; ++k) pn[k] = fmadd(beta, pold[u][k], rv[u][k]);
+      *(Piece<T>*)(pv + i) = pn;
     }
-  }
-  if (upd_p) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) pv[i0 + k] = fmadd(beta, pold[k], r[i0 + k]);
   }
 }
 
 template <typename T>
-hipError_t launch_cg_p_update(const CgDev& cg, T* p, float* x_lo, double* x_hi, int64_t n_reals, hipStream_t s) {
+hipError_t launch_cg_p_update(const CgDev& cg, T* p, float* x_lo, double* x_hi, int32_t mixed, int64_t n_reals,
+                              hipStream_t s) {
+  if (cg.nblk_e != cg_num_blocks(n_reals)) return hipErrorInvalidValue;
   if (sizeof(T) == 4 && !cg.ring32) return hipErrorInvalidValue;
-  dim3 grid(elem_num_blocks(n_reals), cg.n_rhs);
-  hipLaunchKernelGGL((k_cg_p<T>), grid, dim3(kBlock), 0, s, cg, p, x_lo, x_hi, n_reals);
+  dim3 grid(cg.nblk_e + 1, cg.n_rhs);
+  hipLaunchKernelGGL((k_cg_p<T>), grid, dim3(256), 0, s, cg, p, x_lo, x_hi, n_reals, cg_steps(n_reals), mixed);
   return hipGetLastError();
 }
 
@@ -762,16 +737,36 @@ hipError_t launch_cg_xfold(const CgDev& cg, float* x_lo, double* x_hi, int32_t a
   return hipGetLastError();
 }
 
-template hipError_t launch_cg_p_update<double>(const CgDev&, double*, float*, double*, int64_t, hipStream_t);
-template hipError_t launch_cg_p_update<float>(const CgDev&, float*, float*, double*, int64_t, hipStream_t);
+template hipError_t launch_cg_p_update<double>(const CgDev&, double*, float*, double*, int32_t, int64_t, hipStream_t);
+template hipError_t launch_cg_p_update<float>(const CgDev&, float*, float*, double*, int32_t, int64_t, hipStream_t);
+
+// s + sum of c_i r_i over i <= m, in groups of eight (entries past m carry zero coefficients)
+template <int NS>
+__device__ __forceinline__ double fold(const double* __restrict__ c, const double (&r)[NS], int32_t m, double s) {
+  double t[4] = {s, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int g = 0; g < NS; g += 8)
+    if (g <= m) {
+#pragma unroll
+      for (int i = g; i < g + 8 && i < NS; ++i) t[i & 3] = fma(c[i], r[i], t[i & 3]);
+    }
+  return (t[0] + t[1]) + (t[2] + t[3]);
+}
 
 // One element per thread: the segment's residuals at this element are loaded once and every
 // non-seed shift touched in the segment is folded from registers (seed_only: the seed alone,
 // its solution only).  F32: an FP32-phase segment, whose entries from K64 on are FP32 (those
-// below K64, in the segment that spans the switch of precision, are FP64).
-template <bool F32>
-__global__ void __launch_bounds__(256) k_cg_flush(CgDev cg, double* __restrict__ x_hi, double* __restrict__ pj,
-                                                  int32_t final_, int32_t first, int32_t seed_only, int64_t n) {
+// below K64, in the segment that spans the switch of precision, are FP64).  NS: the entries a thread
+// holds (33, or 48 for the long segments of small lattices).  They are loaded eight at a time, each
+// group without conditions so that its loads overlap: entries past the segment's end re-read an
+// existing one (a cache hit) against coefficients that are zero.  The coefficients are the same for a
+// whole block and come through the scalar cache into scalar registers (read from LDS, with a branch
+// per entry, the 36-entry fold of 12 shifts at 16^4 took 362 us).
+template <bool F32, int NS>
+__global__ void __launch_bounds__(256) k_cg_flush(CgDev cg, const double* __restrict__ coef,
+                                                  const double* __restrict__ sh, const int32_t* __restrict__ act_next,
+                                                  double* __restrict__ x_hi, double* __restrict__ pj, int32_t final_,
+                                                  int32_t first, int32_t seed_only, int64_t n) {
   const int32_t v = blockIdx.y;
   const int32_t* fl = cg.flags + (int64_t)v * kFlN;
   const int32_t m = min(fl[kFlM], cg.nslot - 1);   // the host flushes before m passes nslot - 1
@@ -779,66 +774,54 @@ __global__ void __launch_bounds__(256) k_cg_flush(CgDev cg, double* __restrict__
   const int32_t seed = cg.seed[v];
   const int32_t nc = 2 + 2 * cg.cslots;
   const int32_t ns = cg.n_shift;
-  // the segment coefficients of this rhs (and per shift: updated in the segment, still active)
-  extern __shared__ double s_cf[];
-  int32_t* s_fl = (int32_t*)(s_cf + (size_t)ns * nc);
-  for (int i = threadIdx.x; i < ns * nc; i += blockDim.x) s_cf[i] = cg.coef[(int64_t)v * ns * nc + i];
-  for (int j = threadIdx.x; j < ns; j += blockDim.x) {
-    const int64_t vj = (int64_t)v * ns + j;
-    s_fl[2 * j] = cg.sh[vj * kShN + kShSeg] != 0.0 ? 1 : 0;
-    s_fl[2 * j + 1] = cg.act_next[vj];
-  }
-  __syncthreads();
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= n) return;
-  double rv[kMaxSlots];
+  double rv[NS];
   if constexpr (!F32) {
 #pragma unroll
-    for (int i = 0; i < kMaxSlots; ++i) {
-      rv[i] = 0.0;
-      if (i <= m) rv[i] = entry64(cg, v, base, i, n)[e];
-    }
+    for (int g = 0; g < NS; g += 8)
+      if (g <= m) {
+#pragma unroll
+        for (int i = g; i < g + 8 && i < NS; ++i) rv[i] = entry64(cg, v, base, min(i, m), n)[e];
+      }
   } else {
-    // FP32 entries: every load is issued unconditionally so they overlap (the conditional form
-    // waits on each); indices outside [k0, m] re-read an end of that range (a cache hit) and are
-    // never used
-    float rt[kMaxSlots];
+    // below K64 the FP64 entries (only in the segment that spans the switch), from K0 on the FP32 ones
+    const int32_t m64 = min(k64, m + 1) - 1;
 #pragma unroll
-    for (int i = 0; i < kMaxSlots; ++i) rt[i] = entry32(cg, v, base32, k0, min(max(i, k0), m), n)[e];
+    for (int g = 0; g < NS; g += 8) {
+      if (g > m) continue;
+      float rt[8];
+      if (g + 7 > m64) {
 #pragma unroll
-    for (int i = 0; i < kMaxSlots; ++i) rv[i] = (double)rt[i];
-    if (k64 > 0) {   // uniform per rhs: only the segment that spans the switch
+        for (int i = 0; i < 8; ++i) rt[i] = entry32(cg, v, base32, k0, min(max(g + i, k0), m), n)[e];
 #pragma unroll
-      for (int i = 0; i < kMaxSlots; ++i)
-        if (i < k64) rv[i] = entry64(cg, v, base, i, n)[e];
+        for (int i = 0; i < 8; ++i)
+          if (g + i < NS) rv[g + i] = (double)rt[i];
+      }
+      if (g <= m64) {
+        double rd[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) rd[i] = entry64(cg, v, base, min(g + i, m64), n)[e];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          if (g + i < NS && g + i <= m64) rv[g + i] = rd[i];
+      }
     }
   }
   for (int j = 0; j < ns; ++j) {
     if (seed_only ? j != seed : (cg.seed_explicit && j == seed)) continue;   // kept current by the residual update
     const int64_t vj = (int64_t)v * ns + j;
-    const double* cf = s_cf + (size_t)j * nc;
-    const double* d = cf + 2;
-    const double* ec = cf + 2 + cg.cslots;
+    const double* cf = coef + vj * nc;
     double* xj = x_hi + vj * n + e;
     double* pp = pj + vj * n + e;
-    if (!s_fl[2 * j]) {
+    if (sh[vj * kShN + kShSeg] == 0.0) {
       if (first) *xj = 0.0;   // never updated (zero source)
       continue;
     }
     // p_j0 exists once a flush has written it; before that its coefficients are exactly zero
     const double p0 = (cf[0] != 0.0 || cf[1] != 0.0) ? *pp : 0.0;
-    double x = fma(cf[0], p0, first ? 0.0 : *xj);
-#pragma unroll
-    for (int i = 0; i < kMaxSlots; ++i)
-      if (i <= m) x = fma(d[i], rv[i], x);
-    *xj = x;
-    if (!final_ && !seed_only && s_fl[2 * j + 1]) {
-      double q = cf[1] * p0;
-#pragma unroll
-      for (int i = 0; i < kMaxSlots; ++i)
-        if (i <= m) q = fma(ec[i], rv[i], q);
-      *pp = q;
-    }
+    *xj = fold<NS>(cf + 2, rv, m, fma(cf[0], p0, first ? 0.0 : *xj));
+    if (!final_ && !seed_only && act_next[vj]) *pp = fold<NS>(cf + 2 + cg.cslots, rv, m, cf[1] * p0);
   }
 }
 
@@ -869,21 +852,15 @@ __global__ void k_cg_flush_reset(CgDev cg, int32_t fp32) {
   }
 }
 
-size_t flush_lds_bytes(const CgDev& cg) {
-  return (size_t)cg.n_shift * (2 + 2 * cg.cslots) * 8 + (size_t)cg.n_shift * 2 * 4;
-}
-
 hipError_t launch_cg_flush(const CgDev& cg, double* x_hi, double* pj, int32_t final_, int32_t first,
                            int32_t seed_only, int32_t fp32, int64_t n_reals, hipStream_t s) {
-  if (cg.nslot > kMaxSlots || cg.nslot > cg.cslots || cg.nslot64 > kMaxSlots) return hipErrorInvalidValue;
+  if (cg.nslot > kMaxSlots || cg.nslot > cg.cslots || cg.cslots % 8 || cg.nslot64 > kMaxSlots) return hipErrorInvalidValue;
   if (fp32 && (!cg.ring32 || cg.nslot32 < cg.nslot || seed_only)) return hipErrorInvalidValue;
   dim3 grid((unsigned)((n_reals + kBlock - 1) / kBlock), cg.n_rhs);
-  if (fp32)
-    hipLaunchKernelGGL((k_cg_flush<true>), grid, dim3(kBlock), flush_lds_bytes(cg), s, cg, x_hi, pj, final_, first,
-                       0, n_reals);
-  else
-    hipLaunchKernelGGL((k_cg_flush<false>), grid, dim3(kBlock), flush_lds_bytes(cg), s, cg, x_hi, pj, final_,
-                       first, seed_only, n_reals);
+  const auto kernel = cg.nslot <= kMaxBasis + 1 ? (fp32 ? k_cg_flush<true, kMaxBasis + 1> : k_cg_flush<false, kMaxBasis + 1>)
+                                                : (fp32 ? k_cg_flush<true, kMaxSlots> : k_cg_flush<false, kMaxSlots>);
+  hipLaunchKernelGGL(kernel, grid, dim3(kBlock), 0, s, cg, cg.coef, cg.sh, cg.act_next, x_hi, pj, final_, first,
+                     seed_only, n_reals);
   if (!seed_only) hipLaunchKernelGGL(k_cg_flush_reset, dim3(cg.n_rhs), dim3(kRedBlock), 0, s, cg, fp32);
   return hipGetLastError();
 }

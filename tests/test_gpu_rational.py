@@ -91,6 +91,32 @@ def test_rational_apply_segment_lengths(mode):
             assert np.abs(xp - xr).max() <= 1e-12 * np.abs(xr).max()
 
 
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("kappa,tol", [(0.9, 1e-8), (0.97, 1e-10), (0.97, 1e-11)])
+def test_rational_apply_long_segments(mode, kappa, tol):
+    """The default segments of a small lattice (up to 47 iterations, folded in groups of eight entries):
+    solves that end in the first segment and ones that open a second, against segments of 32
+    iterations and the oracle's residuals; one source is zero, so its blocks leave at once."""
+    L = (4, 4, 4, 6)
+    announce(f"rational_apply long segments mode={mode} kappa={kappa} tol={tol}")
+    U, P, Ud, Pd = setup(L, "eps", 0.3, 13, n=4)
+    scale = torch.tensor([1.0, 0.0, 1e-6, 7.0], dtype=torch.float64, device=Pd.device)
+    Pd = (Pd * scale[:, None, None, None]).contiguous()
+    rat = _rat_kappa(kappa, 12)
+    out = api.rational_apply(L, Ud, Pd, rat, api.Solver(tol=tol, mode=mode), want_poles=True)
+    ref = api.rational_apply(L, Ud, Pd, rat, api.Solver(tol=tol, mode=mode, basis=32), want_poles=True)
+    announce(f"  iterations {out['stats']['iters']}")
+    assert out["stats"]["true_relres_max"] <= tol
+    xp, xr = out["x_poles"].cpu().numpy(), ref["x_poles"].cpu().numpy()
+    Ph = Pd.cpu().numpy()
+    assert np.all(xp[1] == 0.0)
+    for i in (0, 2, 3):
+        bn = np.linalg.norm(Ph[i])
+        for j, sj in enumerate(rat.sigma):
+            assert np.linalg.norm(xp[i, j] - xr[i, j]) <= 2 * tol * bn / sj, (i, j)
+            assert np.linalg.norm(Ph[i] - olap.laplacian(U, xp[i, j], L, sj)) <= 1.01 * tol * bn, (i, j)
+
+
 @pytest.mark.parametrize("switch", [-1.0, 1e-2, 1e-4, 1e-7])
 @pytest.mark.parametrize("basis", [3, 16, 32])
 def test_mixed_switch_points(switch, basis):
