@@ -316,7 +316,8 @@ struct Engine {
   float* ring32 = nullptr; // [n_rhs][nslot32] seed residuals of the FP32 phase (mixed)
   double* pj = nullptr;    // [n_rhs][n_shift] shift directions at the segment start (n_shift > 1)
   double* coef = nullptr;  // [n_rhs][n_shift][2 + 2 coef_slots]
-  // scalar state, contiguous so one copy brings it to the host: sc then flags
+  // scalar state (sc then flags) in two copies of half the bytes each, contiguous so one copy brings it
+  // to the host
   double* sc = nullptr;
   int32_t* flags = nullptr;
   size_t state_bytes = 0;
@@ -333,7 +334,7 @@ struct Engine {
   double* tol_rhs = nullptr; // [n_rhs]
   int32_t* seed = nullptr;   // [n_rhs]
   double* part = nullptr;      // [n_rhs][max(3 nblk_hop, blocks of a dot product)]
-  double* part_e = nullptr;    // [n_rhs][nblk_e]
+  double* part_e = nullptr;    // [2][n_rhs][nblk_e]
   double* part_ru = nullptr;   // [n_rhs][3][nblk_hop]  (mixed precision)
   double* part_true = nullptr; // [n_rhs][n_shift][3][nblk_hop]
   double* sums_true = nullptr; // [n_rhs][n_shift][3]
@@ -386,10 +387,10 @@ void plan_engine(Carver& c, Engine& e, const Geom& g, int32_t n_rhs, int32_t n_s
   if (n_shift > 1) e.pj = c.take<double>(np * n);
   e.coef = c.take<double>(np * (2 + 2 * coef_slots(e)));
   const size_t scb = rup(nr * kScN * 8), flb = rup(nr * kFlN * 4);
-  char* st = c.take<char>(scb + flb);
+  e.state_bytes = 2 * (scb + flb);
+  char* st = c.take<char>(e.state_bytes);
   e.sc = (double*)st;
   e.flags = st ? (int32_t*)(st + scb) : nullptr;
-  e.state_bytes = scb + flb;
   e.sh = c.take<double>(np * kShN);
   e.act = c.take<int32_t>(np);
   e.act_next = c.take<int32_t>(np);
@@ -408,7 +409,7 @@ void plan_engine(Carver& c, Engine& e, const Geom& g, int32_t n_rhs, int32_t n_s
   e.nblk_hop = hop_max_blocks(g);
   e.nblk_e = cg_num_blocks(n);
   e.part = c.take<double>(nr * std::max<int64_t>(3 * e.nblk_hop, red_num_blocks(n)));
-  e.part_e = c.take<double>(nr * e.nblk_e);
+  e.part_e = c.take<double>(2 * nr * e.nblk_e);
   if (mode) e.part_ru = c.take<double>(nr * 3 * e.nblk_hop);
   e.part_true = c.take<double>(np * 3 * e.nblk_hop);
   e.sums_true = c.take<double>(np * 3);
@@ -426,7 +427,10 @@ CgDev cg_view(const Engine& e, int32_t nblk_hop, bool fp32) {
   d.sigma = e.sigma;
   d.seed = e.seed;
   d.part = e.part;
+  d.sc_next = (double*)((char*)e.sc + e.state_bytes / 2);
+  d.flags_next = (int32_t*)((char*)e.flags + e.state_bytes / 2);
   d.part_e = e.part_e;
+  d.part_e_next = e.part_e + (int64_t)e.n_rhs * e.nblk_e;
   d.part_ru = e.part_ru;
   d.coef = e.coef;
   d.cslots = coef_slots(e);
@@ -539,7 +543,8 @@ rmh_status engine_solve(Engine& e, const double* U64, const float* U32, const do
   HIP_TRY(launch_dot<double>(b, b, n, nr, e.part, s));
   HIP_TRY(launch_cg_init(cg64, e.part, red_num_blocks(n), e.tol_rhs, delta, maxiter, fp32_phase ? 1 : 0, s));
 
-  // FP64 stencil on the seed direction: Ap = (8 + sigma0) p - H p, partial <p, Ap>
+  // FP64 stencil on the seed direction: Ap = (8 + sigma0) p - H p, partial <p, Ap> and, where the
+  // kernel takes them, <r, Ap> and <Ap, Ap> for the update in one launch
   HopArgs<double> h64{};
   h64.g = g;
   h64.U = U64;
@@ -554,7 +559,13 @@ rmh_status engine_solve(Engine& e, const double* U64, const float* U32, const do
   h64.run_stride = kFlN;
   h64.store = 1;
   h64.partials = e.part;
-  h64.dot_mask = 2;
+  // one launch for the update where the stencil's kernel takes <r, Ap>; the walk over all directions would
+  // spill for it (16^4, eight FP32 fields: stencil 107 us and update 91, against 88 and two updates of 42
+  // and 59: on vectors past the caches the second pass costs little more than <r, Ap>'s)
+  const bool one64 = hop_ring_ok(g, c64), one32 = hop_ring_ok(g, c32);
+  h64.dot_mask = one64 ? 7 : 2;
+  h64.ring = one64 ? e.ring : nullptr;
+  h64.ring_slots = e.nslot;
   // FP32 stencil of the mixed phase
   HopArgs<float> h32{};
   h32.g = g;
@@ -570,7 +581,9 @@ rmh_status engine_solve(Engine& e, const double* U64, const float* U32, const do
   h32.run_stride = kFlN;
   h32.store = 1;
   h32.partials = e.part;
-  h32.dot_mask = 2;
+  h32.dot_mask = one32 ? 7 : 2;
+  h32.ring = one32 ? e.ring32 : nullptr;
+  h32.ring_slots = e.nslot32;
   // FP64 true residual of the seed for reliable updates: r64 = b - (Delta + sigma0) x_seed
   HopArgs<double> hr{};
   hr.g = g;
@@ -590,6 +603,16 @@ rmh_status engine_solve(Engine& e, const double* U64, const float* U32, const do
   hr.store = 1;
   hr.partials = e.part_ru;
   hr.dot_mask = 4;
+  // after an update: what it wrote is the state the next launches read
+  auto flip = [&]() {
+    for (CgDev* d : {&cg64, &cg32}) {
+      std::swap(d->sc, d->sc_next);
+      std::swap(d->flags, d->flags_next);
+      std::swap(d->part_e, d->part_e_next);
+    }
+    h64.run = h32.run = cg64.flags + kFlRun;
+    hr.run = cg64.flags + kFlNeedRU;
+  };
 
   // shift solutions through the residual ring (more than one shift): flush before a segment
   // would outgrow its ring; a single shift updates its solution each iteration.  The segment
@@ -618,8 +641,14 @@ rmh_status engine_solve(Engine& e, const double* U64, const float* U32, const do
   };
 
   std::vector<char> st(e.state_bytes);
-  const double* hsc = (const double*)st.data();
-  const int32_t* hfl = (const int32_t*)(st.data() + ((char*)e.flags - (char*)e.sc));
+  const double* hsc = nullptr;   // the current copy's scalars and flags on the host
+  const int32_t* hfl = nullptr;
+  auto fetch = [&]() -> rmh_status {
+    RMH_TRY(d2h(st.data(), e.sc, e.state_bytes, s));
+    hsc = (const double*)(st.data() + ((char*)cg64.sc - (char*)e.sc));
+    hfl = (const int32_t*)(st.data() + ((char*)cg64.flags - (char*)e.sc));
+    return RMH_OK;
+  };
   int32_t it = 0;
   info->fp64_iters = 0;
   // Iterations until the next host check.  From the second check on, the seed's convergence rate
@@ -638,31 +667,27 @@ rmh_status engine_solve(Engine& e, const double* U64, const float* U32, const do
     for (int i = 0; i < chunk; ++i) {
       if (!fp32_phase) {
         {
-          ProfScope ps(RMH_PROF_STENCIL, hop_bytes(g, nr, 8, false, true), s, nr);
+          ProfScope ps(RMH_PROF_STENCIL, hop_bytes(g, nr, 8, one64, true), s, nr);
           HIP_TRY(launch_hop<double>(h64, c64, s));
         }
         {
-          ProfScope ps(RMH_PROF_CG_RESIDUAL, (double)nr * n * (3 * 8.0 + (multi ? 0.0 : 24.0)), s, nr);
-          HIP_TRY(launch_cg_r_update<double>(cg64, e.Ap64, e.p64, multi ? nullptr : x_hi, nullptr, n, s));
+          ProfScope ps(RMH_PROF_CG_RESIDUAL, (double)nr * n * ((one64 ? 5 : 6) * 8.0 + (multi ? 0.0 : 16.0)), s, nr);
+          HIP_TRY((one64 ? launch_cg_step<double> : launch_cg_step2<double>)(cg64, e.Ap64, e.p64, nullptr,
+                                                                             multi ? nullptr : x_hi, nullptr, 0, n, s));
         }
-        {
-          ProfScope ps(RMH_PROF_CG_RESIDUAL, (double)nr * n * 3 * 8.0, s, nr);
-          HIP_TRY(launch_cg_p_update<double>(cg64, e.p64, nullptr, nullptr, 0, n, s));
-        }
+        flip();
       } else {
         {
-          ProfScope ps(RMH_PROF_STENCIL, hop_bytes(g, nr, 4, false, true), s, nr);
+          ProfScope ps(RMH_PROF_STENCIL, hop_bytes(g, nr, 4, one32, true), s, nr);
           HIP_TRY(launch_hop<float>(h32, c32, s));
         }
         {
-          ProfScope ps(RMH_PROF_CG_RESIDUAL, (double)nr * n * 3 * 4.0, s, nr);
-          HIP_TRY(launch_cg_r_update<float>(cg32, e.Ap32, e.p32, nullptr, e.r64, n, s));
+          ProfScope ps(RMH_PROF_CG_RESIDUAL, (double)nr * n * (one32 ? 7 : 8) * 4.0, s, nr);
+          HIP_TRY((one32 ? launch_cg_step<float> : launch_cg_step2<float>)(cg32, e.Ap32, e.p32, e.x_lo, x_hi, e.r64, 1,
+                                                                           n, s));
         }
-        {
-          ProfScope ps(RMH_PROF_CG_RESIDUAL, (double)nr * n * 5 * 4.0, s, nr);
-          HIP_TRY(launch_cg_p_update<float>(cg32, e.p32, e.x_lo, x_hi, 1, n, s));
-        }
-        // reliable update decided by this iteration's direction update (blocks of rhs without a
+        flip();
+        // reliable update decided by this iteration's update (blocks of rhs without a
         // pending update exit at once), which has folded the seed solution into FP64,
         // now its FP64 residual; the stencil's bytes are added once the update count is known
         {
@@ -674,7 +699,7 @@ rmh_status engine_solve(Engine& e, const double* U64, const float* U32, const do
     it += chunk;
     since += chunk;
     if (!fp32_phase) info->fp64_iters = it;
-    RMH_TRY(d2h(st.data(), e.sc, e.state_bytes, s));
+    RMH_TRY(fetch());
     bool running = false, below = true;
     double rel = 0.0;
     for (int v = 0; v < nr; ++v) {
@@ -708,7 +733,7 @@ rmh_status engine_solve(Engine& e, const double* U64, const float* U32, const do
   }
   RMH_TRY(flush(true));
   if (fp32_phase) HIP_TRY(launch_cg_xfold(cg32, e.x_lo, x_hi, 1, n, s));
-  RMH_TRY(d2h(st.data(), e.sc, e.state_bytes, s));
+  RMH_TRY(fetch());
   if (log_level() > 0) {
     for (int v = 0; v < nr; ++v)
       fprintf(stderr, "[rmh] engine mode=%d rhs %d/%d shifts=%d sigma0=%.4g iters=%g (fp64 %d) ru=%g status=%d |b|^2=%.4g rr=%.4g tol=%.3g\n",

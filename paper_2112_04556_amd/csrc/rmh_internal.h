@@ -75,6 +75,10 @@ struct HopArgs {
   int32_t store;            // write out
   double* partials;         // [n_rhs][3][nblk]: <x,x>, <out,x>, <out,out>
   int32_t dot_mask;         // bit q set -> compute dot q
+  // optional (z null, run = the CG's flags): dot 0 is <r, out>, r the current residual of field v in the
+  // CG's ring of T, ring_slots slots of 32 V reals per field
+  const T* ring;            // (hop_ring_ok)
+  int32_t ring_slots;
 };
 
 // Tile of the tiled walk: R1 x R2 rows of x0 per block, n1 x n2 tiles per plane, K planes per walk.
@@ -93,6 +97,8 @@ int hop_split_ok(const HopConfig& cfg);
 int hop_walk_ok(const Geom& g, const HopConfig& cfg);
 // whether the multi-field shape applies (ns > 1 divides n_rhs, nv = 4, no walk, orders 0 and 1)
 int hop_ns_ok(const HopConfig& cfg, int32_t n_rhs);
+// whether the kernel of a configuration takes HopArgs::ring
+bool hop_ring_ok(const Geom& g, const HopConfig& cfg);
 // upper bound of hop_num_blocks over every configuration: 16 sites per block at least (the
 // hop-split shape with one direction group per block), plus one partial block per x3 slice of
 // the walking shape; every per-block partial-sum buffer is sized with it
@@ -141,15 +147,19 @@ hipError_t launch_dot(const T* a, const T* b, int64_t n_reals, int32_t n, double
 // update it each iteration in FP64 phases.
 struct CgDev {
   int32_t n_rhs, n_shift;
+  // scalars and flags in two copies: the update reads one, writes the other, and the host exchanges them
   double* sc;            // [n_rhs][kScN]
-  double* sh;            // [n_rhs][n_shift][kShN]
   int32_t* flags;        // [n_rhs][kFlN]
+  double* sc_next;
+  int32_t* flags_next;
+  double* sh;            // [n_rhs][n_shift][kShN]
   int32_t* act;          // [n_rhs][n_shift]
   int32_t* act_next;     // [n_rhs][n_shift]
   const double* sigma;   // [n_rhs][n_shift]
   const int32_t* seed;   // [n_rhs]
   double* part;          // partials of the stencil [n_rhs][3][nblk_hop]
-  double* part_e;        // partials of the residual update [n_rhs][nblk_e]
+  double* part_e;        // partials of <r, r> of the current residual [n_rhs][nblk_e] and, written by the
+  double* part_e_next;   // update, of the next one (exchanged like the scalars)
   double* part_ru;       // partials of the FP64 residual stencil [n_rhs][3][nblk_ru] (mixed precision)
   double* coef;          // [n_rhs][n_shift][2 + 2 cslots]: a, b, d[cslots], e[cslots]
   int32_t nslot;         // segment capacity guard of this view: FP64 ring slots, or (FP32 view)
@@ -166,7 +176,7 @@ struct CgDev {
   int32_t ring_on;       // shift solutions through the ring (n_shift > 1); else the seed's
                          // solution is updated each iteration and nslot = 2
   int32_t seed_explicit; // the seed's solution is kept outside the ring (single shift, FP32 phase)
-  int32_t nblk_hop, nblk_e, nblk_ru;
+  int32_t nblk_hop, nblk_e, nblk_ru;   // nblk_e: row length of part_e
 };
 // Segment entries: entry i < K64 is FP64 slot (Base + i) % nslot64; entry i >= K64 is FP32 slot
 // (Base32 + i - K0) % nslot32 (K0: the entry held in FP32 slot Base32).  FP64 phases have
@@ -179,42 +189,40 @@ constexpr int kMaxSlots = 48;
 constexpr int32_t kLongSegmentSites = 1 << 17;
 constexpr int32_t kAllFp64 = 1 << 30;
 // scalar slots per rhs
-// RRc, MaxRc: RR and MaxR as the residual update of the current iteration found them
-enum : int { kScRR = 0, kScAlpha, kScAlphaPrev, kScBetaPrev, kScBnorm2, kScMaxR, kScTolAbs, kScIters,
-             kScRU, kScDelta, kScMaxIter, kScRRc, kScMaxRc, kScN };
+// RR: <r, r> as the update knew it (predicted or summed); ZMax: the largest |zeta| of the active shifts
+enum : int { kScRR = 0, kScAlphaPrev, kScBetaPrev, kScBnorm2, kScMaxR, kScTolAbs, kScIters,
+             kScRU, kScDelta, kScMaxIter, kScZMax, kScN };
 // per (rhs, shift) slots; Seg: the shift was updated in the current segment
-enum : int { kShZeta = 0, kShZetaPrev, kShZetaNext, kShCx, kShCr, kShCp, kShSeg, kShN };
+enum : int { kShZeta = 0, kShZetaPrev, kShSeg, kShN };
 // int flags per rhs
-// Run: the rhs still iterates (read by the stencil and the residual update of the next iteration);
-// Live: the current iteration is being carried out (set by the residual update), so the direction
-// update of the iteration in which a rhs converges still runs once; Mn: M + 1, set with Live.
+// Run: the rhs still iterates.  Sum: the number of partials in part_e of <r, r> of the current residual (0
+// before the first update).  Defer: convergence is decided on that sum, by the next update.
 // Base, M: FP64 ring slot of the segment's first residual, index of the current residual in it;
 // K64, K0, Base32: the FP64 entries of the segment and the FP32 slot of entry K0 (above).
-enum : int { kFlRun = 0, kFlLive, kFlStatus, kFlNeedRU, kFlMn, kFlBase, kFlM, kFlK64, kFlK0, kFlBase32, kFlN };
+enum : int { kFlRun = 0, kFlStatus, kFlNeedRU, kFlSum, kFlDefer, kFlBase, kFlM, kFlK64, kFlK0, kFlBase32, kFlN };
 enum : int { kStOk = 0, kStNoConv = 1, kStBreakdown = 2 };
 
 // fp32_start: the solve runs in FP32 from its first iteration (its segment has no FP64 entries)
 hipError_t launch_cg_init(const CgDev& cg, const double* bn2_partials, int32_t nblk, const double* tol_rel,
                           double delta, int32_t maxiter, int32_t fp32_start, hipStream_t s);
-// blocks (and partials) per rhs of the residual and direction updates
+// blocks (and partials) per rhs of the update
 int cg_num_blocks(int64_t n_reals);
 // slot 0 of the ring region (ring, rhs_bytes per rhs) = (T) b, p = (T) b for every rhs
 template <typename T>
 hipError_t launch_cg_start(const double* b, void* ring, T* p, int32_t nr, int64_t rhs_bytes, int64_t n_reals,
                            hipStream_t s);
-// alpha (from the stencil's partials) and the next residual r' = r - alpha Ap into the next segment entry (r
-// taken from r64 when a reliable update is consumed), partial <r', r'>; the shifts' zeta and x
-// coefficients; with x_hi non-null also x_hi[seed] += alpha p
+// One iteration after its stencil (dots <r, Ap>, <p, Ap>, <Ap, Ap>): alpha, r' = r - alpha Ap into the next
+// segment entry (r taken from r64 when a reliable update is consumed), beta, p = r' + beta p, partial
+// <r', r'>; the shifts' coefficients, convergence, the decision for a reliable update (mixed).  FP64: with
+// x_hi non-null x_hi[seed] += alpha p.  FP32: x_lo += alpha p (the increment of the seed's solution) and, for
+// the rhs that need a reliable update, x_hi[seed] += x_lo, x_lo = 0.
 template <typename T>
-hipError_t launch_cg_r_update(const CgDev& cg, const T* Ap, const T* p, double* x_hi, const double* r64,
-                              int64_t n_reals, hipStream_t s);
-// beta and the seed direction p = r' + beta p; the shifts' p coefficients, convergence, the decision for a
-// reliable update (mixed); with x_lo non-null also x_lo += alpha p (the FP32 increment of the seed's
-// solution, FP32 phase), and with x_hi non-null, for the rhs that need a reliable update,
-// x_hi[seed] += x_lo, x_lo = 0 in the same pass
+hipError_t launch_cg_step(const CgDev& cg, const T* Ap, T* p, float* x_lo, double* x_hi, const double* r64,
+                          int32_t mixed, int64_t n_reals, hipStream_t s);
+// the same in two launches, beta from the sum of r' (stencil dot <p, Ap> alone)
 template <typename T>
-hipError_t launch_cg_p_update(const CgDev& cg, T* p, float* x_lo, double* x_hi, int32_t mixed, int64_t n_reals,
-                              hipStream_t s);
+hipError_t launch_cg_step2(const CgDev& cg, const T* Ap, T* p, float* x_lo, double* x_hi, const double* r64,
+                           int32_t mixed, int64_t n_reals, hipStream_t s);
 // x_hi[seed] += x_lo, x_lo = 0 for every rhs (all, the end of a mixed solve) or those with a
 // pending reliable update
 hipError_t launch_cg_xfold(const CgDev& cg, float* x_lo, double* x_hi, int32_t all, int64_t n_reals, hipStream_t s);

@@ -227,7 +227,6 @@ __global__ void k_cg_init(CgDev cg, const double* bn2_part, int32_t nblk, const 
     int32_t* fl = cg.flags + (int64_t)v * kFlN;
     sc[kScRR] = bn2;
     sc[kScBnorm2] = bn2;
-    sc[kScAlpha] = 0.0;
     sc[kScAlphaPrev] = 1.0;
     sc[kScBetaPrev] = 0.0;
     sc[kScMaxR] = sqrt(bn2);
@@ -236,12 +235,13 @@ __global__ void k_cg_init(CgDev cg, const double* bn2_part, int32_t nblk, const 
     sc[kScRU] = 0.0;
     sc[kScDelta] = delta;
     sc[kScMaxIter] = (double)maxiter;
+    sc[kScZMax] = 1.0;
     fl[kFlRun] = (bn2 > 0.0) ? 1 : 0;
     fl[kFlStatus] = (bn2 == bn2) ? kStOk : kStBreakdown;   // NaN source
     if (!(bn2 == bn2)) fl[kFlRun] = 0;
     fl[kFlNeedRU] = 0;
-    fl[kFlMn] = 0;
-    fl[kFlLive] = 0;
+    fl[kFlSum] = 0;
+    fl[kFlDefer] = 0;
     fl[kFlBase] = 0;
     fl[kFlM] = 0;
     fl[kFlK64] = fp32_start ? 0 : kAllFp64;
@@ -256,10 +256,6 @@ __global__ void k_cg_init(CgDev cg, const double* bn2_part, int32_t nblk, const 
     double* sh = cg.sh + vj * kShN;
     sh[kShZeta] = 1.0;
     sh[kShZetaPrev] = 1.0;
-    sh[kShZetaNext] = 1.0;
-    sh[kShCx] = 0.0;
-    sh[kShCr] = 0.0;
-    sh[kShCp] = 0.0;
     sh[kShSeg] = 0.0;
     // x_j = 0, p_j = b = ring slot 0
     double* cf = cg.coef + vj * nc;
@@ -278,154 +274,163 @@ hipError_t launch_cg_init(const CgDev& cg, const double* bn2_partials, int32_t n
   return hipGetLastError();
 }
 
-// One iteration is three launches: the stencil (Ap and the partials of <p, Ap>), the residual update
-// with alpha, the direction update with beta.  Every block of an update sums the partials itself (the
-// same values in the same order, so every block gets the same bits) instead of waiting for a scalar
-// kernel of its own; the last block of each rhs carries out the scalar state and the shift
-// coefficients meanwhile.  A launch never writes what its other blocks read: the residual update's
-// last block writes Alpha, RRc, MaxRc, Mn and Live for the direction update, whose last block writes RR,
-// MaxR, M, Run and NeedRU for the next iteration.  (Run is cleared early on a breakdown, which every
-// block then finds by itself.)  With alpha and beta in kernels of their own an iteration took five
-// launches, the two of 4 to 5 us each: 12^4, one field, 36 us an iteration.
+// One iteration is two launches: the stencil (Ap and the partials of <r, Ap>, <p, Ap>, <Ap, Ap>) and the
+// update of r and p.  beta = <r', r'> / <r, r> needs the norm of a residual that the same launch computes;
+// it is taken from <r', r'> = <r, r> - 2 alpha <r, Ap> + alpha^2 <Ap, Ap>, which holds for the vectors at
+// hand whatever their conjugacy (a form without <r, Ap>, which the exact recurrences would allow, doubles
+// its error every iteration), and the residual that was computed gives alpha and the next prediction their
+// <r, r>, so a prediction's rounding, a few ulps of <r, r>, is not handed on.  Where <r', r'> comes out below
+// 1e-4 <r, r> more than four digits have cancelled: convergence is then decided by the next update from the
+// sum (Defer), and until then the norm counts as 1e-2 |r|.
+// Against residual and direction updates of their own, which read r' and p again (16^4, one field: 11.8 and
+// 11.0 us; 12^4: 6.9 and 7.8), one pass over five streams takes 17.5 and 10.6 us, and the stencil 1 us more.
+//
+// Every block sums the partials itself (the same values in the same order, so every block gets the same
+// bits) instead of waiting for a scalar kernel; the last block of each rhs carries out the scalar state and
+// the shift coefficients meanwhile, into the other copy of the state, so no launch writes what its other
+// blocks read.
 
-// Fixed-order sum of p[0, n) by the whole block, in every thread.
-__device__ __forceinline__ double block_total(const double* p, int32_t n, double (*lds)[16], double* bc) {
-  const double t = block_sum_array(p, n, lds);
-  if (threadIdx.x == 0) *bc = t;
-  __syncthreads();
-  const double r = *bc;
-  __syncthreads();
-  return r;
-}
-
-struct CgAlpha {
-  double rr, alpha;   // the residual norm squared the iteration starts from, and its step
-  bool ok;
+// One array of partials, p[0, n): this thread's first four, loaded without a wait or a branch, so that the
+// loads of all arrays, and the vectors' after them, are in flight together.
+struct CgPart {
+  const double* p;
+  int32_t n;
+  double t[4];
+  __device__ __forceinline__ CgPart(const double* p_, int32_t n_) : p(p_), n(n_) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) t[k] = p[min((int32_t)(threadIdx.x + k * blockDim.x), max(n - 1, 0))];
+  }
+  // this thread's part of the fixed-order sum
+  __device__ __forceinline__ double sum() const {
+    const int32_t B = blockDim.x;
+    double a = 0.0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) a += (int32_t)threadIdx.x + k * B < n ? t[k] : 0.0;
+    for (int32_t i = threadIdx.x + 4 * B; i < n; i += B) a += p[i];
+    return a;
+  }
 };
 
-// alpha_k = rr / <p, A0 p>; with ru the residual is the FP64 one of a reliable update issued at the end of the
+// The scalars of an iteration.
+struct CgStep {
+  double rr, alpha;    // <r, r> the iteration starts from, and its step
+  double rrn, beta;    // <r', r'> (predicted: at least 1e-4 rr) and the direction's coefficient
+  double maxr;         // largest residual norm since the last reliable update
+  bool done, ok;       // converged (or at its iteration limit) before this iteration; no breakdown
+  bool defer, need_ru;
+};
+
+// The partials an update reads.  kNext: <r', r'> is the sum of nnew partials in part_e_next, else predicted
+// (unused by the launch that writes them).  With ru the residual is the FP64 one of a reliable update issued at the end of the
 // previous iteration (r64 = b - (Delta + sigma0) x_seed), which replaces the recursive residual from now on
-__device__ __forceinline__ CgAlpha cg_alpha(const CgDev& cg, int32_t v, bool ru, double rr_sc, double (*lds)[16],
-                                            double* bc) {
-  CgAlpha r;
-  r.rr = ru ? block_total(cg.part_ru + ((int64_t)v * 3 + 2) * cg.nblk_ru, cg.nblk_ru, lds, bc) : rr_sc;
-  const double pAp = block_total(cg.part + ((int64_t)v * 3 + 1) * cg.nblk_hop, cg.nblk_hop, lds, bc);
+template <bool kNext>
+struct CgParts {
+  CgPart pAp, rr, a, b;   // a, b: <r', r'> and nothing, or <r, Ap> and <Ap, Ap>
+  __device__ __forceinline__ CgParts(const CgDev& cg, int32_t v, bool ru, int32_t sum, int32_t nnew)
+      : CgParts(cg, cg.part + (int64_t)v * 3 * cg.nblk_hop, v, ru, sum, nnew) {}
+
+ private:
+  __device__ __forceinline__ CgParts(const CgDev& cg, const double* part, int32_t v, bool ru, int32_t sum, int32_t nnew)
+      : pAp(part + cg.nblk_hop, cg.nblk_hop),
+        rr(ru ? cg.part_ru + ((int64_t)v * 3 + 2) * cg.nblk_ru : cg.part_e + (int64_t)v * cg.nblk_e,
+           ru ? cg.nblk_ru : sum),
+        a(kNext ? cg.part_e_next + (int64_t)v * cg.nblk_e : part, kNext ? nnew : cg.nblk_hop),
+        b(kNext ? part : part + 2 * (int64_t)cg.nblk_hop, kNext ? 0 : cg.nblk_hop) {}
+};
+
+template <bool kNext>
+__device__ __forceinline__ CgStep cg_scalars(const CgDev& cg, int32_t v, bool ru, int32_t mixed,
+                                             const CgParts<kNext>& pt, double (*lds)[16]) {
+  const int32_t* fl = cg.flags + (int64_t)v * kFlN;
+  const double* sc = cg.sc + (int64_t)v * kScN;
+  const int32_t sum = fl[kFlSum];
+  double q[4] = {pt.pAp.sum(), pt.rr.sum(), pt.a.sum(), pt.b.sum()};
+  block_sum_all<4>(q, lds);
+  const double pAp = q[0];
+  CgStep r;
+  r.rr = ru || sum ? q[1] : sc[kScRR];
+  r.done = fl[kFlDefer] != 0 &&
+           (sc[kScZMax] * sqrt(r.rr) <= sc[kScTolAbs] || sc[kScIters] >= sc[kScMaxIter]);
   r.alpha = r.rr / pAp;
   r.ok = pAp > 0.0 && r.alpha == r.alpha && r.alpha < 1e300;
+  const double rrn = kNext ? q[2] : fma(r.alpha, fma(r.alpha, q[3], -2.0 * q[2]), r.rr);
+  r.defer = !kNext && rrn < 1e-4 * r.rr;
+  r.beta = (rrn < 0.0 ? 0.0 : rrn) / r.rr;
+  r.rrn = r.defer ? 1e-4 * r.rr : rrn;
+  // a reliable update once the residual norm fell below delta times its largest value since the last one
+  r.maxr = ru ? sqrt(r.rr) : sc[kScMaxR];
+  const double rnorm = sqrt(r.rrn);
+  r.need_ru = mixed && rnorm < sc[kScDelta] * (rnorm > r.maxr ? rnorm : r.maxr);
   return r;
 }
 
-// The scalar side of the residual update (one block per rhs): zeta_{k+1}^j and the x-update coefficient
-// of every active shift, applied to the segment coefficients of the non-seed shifts: x_j += cx_j p_j
-__device__ __forceinline__ void cg_alpha_state(const CgDev& cg, int32_t v, bool ru, const CgAlpha& al) {
-  int32_t* fl = cg.flags + (int64_t)v * kFlN;
-  double* sc = cg.sc + (int64_t)v * kScN;
+// The scalar side of the update (one block per rhs).  zeta_{k+1}^j, the x-update coefficient and the
+// p-update coefficients of every active shift, applied to the segment coefficients of the non-seed shifts:
+// x_j += cx_j p_j, then p_j = cr_j r' + cp_j p_j; convergence and freezing; the new residual becomes the
+// current ring entry
+__device__ __forceinline__ void cg_state(const CgDev& cg, int32_t v, bool ru, int32_t mixed, int32_t nsum,
+                                         const CgStep& it) {
+  const int32_t* fl = cg.flags + (int64_t)v * kFlN;
+  const double* sc = cg.sc + (int64_t)v * kScN;
+  int32_t* fn = cg.flags_next + (int64_t)v * kFlN;
+  double* sn = cg.sc_next + (int64_t)v * kScN;
   const int32_t ns = cg.n_shift;
   const int32_t nc = 2 + 2 * cg.cslots;
   const int32_t tid = threadIdx.x;
   const int32_t m = fl[kFlM];
   const int32_t seed = cg.seed[v];
-  const double ap = sc[kScAlphaPrev], bp = sc[kScBetaPrev];
-  const double alpha = al.alpha;
-  if (tid == 0) {
-    sc[kScRRc] = al.rr;
-    sc[kScMaxRc] = ru ? sqrt(al.rr) : sc[kScMaxR];
-    if (ru) sc[kScRU] += 1.0;
-    sc[kScAlpha] = alpha;
-    fl[kFlMn] = m + 1;
-    fl[kFlLive] = al.ok ? 1 : 0;
-    if (!al.ok) {
-      fl[kFlStatus] = kStBreakdown;
-      fl[kFlRun] = 0;
+  if (it.done || !it.ok) {
+    if (tid == 0) {
+      fn[kFlRun] = 0;
+      fn[kFlNeedRU] = 0;
+      const bool conv = it.done && sc[kScZMax] * sqrt(it.rr) <= sc[kScTolAbs];
+      if (it.done && !conv) fn[kFlStatus] = kStNoConv;
+      if (!it.done) fn[kFlStatus] = kStBreakdown;
     }
+    return;
   }
-  if (!al.ok) return;
-  __shared__ double s_cx[kMaxShifts];
-  __shared__ int s_upd[kMaxShifts];
+  const double ap = sc[kScAlphaPrev], bp = sc[kScBetaPrev];
+  const double alpha = it.alpha, beta = it.beta;
+  const double tolabs = sc[kScTolAbs];
+  const double rnorm = sqrt(it.rrn);
+  __shared__ double s_cx[kMaxShifts], s_cp[kMaxShifts], s_cr[kMaxShifts], s_z[kMaxShifts];
+  __shared__ int s_ux[kMaxShifts], s_up[kMaxShifts];   // coefficients updated
+  __shared__ int s_seed_act, s_seed_keep;              // the seed's act and act_next, for thread 0
   const double s0 = cg.sigma[(int64_t)v * ns + seed];
+  int any_other = 0;
   if (tid < ns) {
     const int64_t vj = (int64_t)v * ns + tid;
     const int32_t on = cg.act_next[vj];
     double* sh = cg.sh + vj * kShN;
     cg.act[vj] = on;
-    int upd = 0;
+    int ux = 0, up = 0, keep = 0;
+    double zn = 0.0;
     if (on) {
       const double z = sh[kShZeta], zp = sh[kShZetaPrev];
       const double ds = cg.sigma[vj] - s0;
-      const double zn = z * zp * ap / (ap * zp * (1.0 + alpha * ds) + alpha * bp * (zp - z));
-      const double cx = alpha * zn / z;
-      sh[kShZetaNext] = zn;
-      sh[kShCx] = cx;
-      upd = (cg.ring_on && m < cg.nslot && !(cg.seed_explicit && tid == seed)) ? 1 : 0;
-      if (upd) sh[kShSeg] = 1.0;
-      s_cx[tid] = cx;
-    } else {
-      sh[kShCx] = 0.0;
-    }
-    s_upd[tid] = upd;
-  }
-  __syncthreads();
-  // one (shift, coefficient) pair per thread and round: q = 0 the p_j0 coefficient (x_j0 += cx p_j0),
-  // q = 1 + i the ring entry i <= m (d_ji += cx e_ji).  A shift is updated only while m < nslot <= cslots;
-  // past that (a single shift's segment index grows without flushes) the pairs stop at the last
-  // coefficient slot
-  const int32_t per = min(m, cg.cslots - 1) + 2;
-  for (int t = tid; t < ns * per; t += blockDim.x) {
-    const int32_t jj = t / per, q = t - jj * per;
-    if (!s_upd[jj]) continue;
-    double* cf = cg.coef + ((int64_t)v * ns + jj) * nc;
-    if (q == 0)
-      cf[0] = fma(s_cx[jj], cf[1], cf[0]);
-    else
-      cf[1 + q] = fma(s_cx[jj], cf[1 + q + cg.cslots], cf[1 + q]);
-  }
-}
-
-// The scalar side of the direction update (one block per rhs): beta_k = rr_new / rr, shifted beta and
-// p-update coefficients (applied to the segment coefficients of the non-seed shifts: p_j = cr_j r' +
-// cp_j p_j); convergence and freezing; the new residual becomes the current ring entry
-__device__ __forceinline__ void cg_beta_state(const CgDev& cg, int32_t v, int32_t mixed, double rrn, double beta,
-                                              bool need_ru) {
-  int32_t* fl = cg.flags + (int64_t)v * kFlN;
-  double* sc = cg.sc + (int64_t)v * kScN;
-  const int32_t ns = cg.n_shift;
-  const int32_t nc = 2 + 2 * cg.cslots;
-  const int32_t tid = threadIdx.x;
-  const int32_t m = fl[kFlM];
-  const int32_t seed = cg.seed[v];
-  const double tolabs = sc[kScTolAbs];
-  const double rnorm = sqrt(rrn);
-  __shared__ double s_cp[kMaxShifts], s_cr[kMaxShifts];
-  __shared__ int s_upd[kMaxShifts];
-  __shared__ int s_seed_act, s_seed_keep;   // the seed's act and act_next, for thread 0
-  int any_other = 0;
-  // per shift: beta_j, the p coefficients, convergence
-  if (tid < ns) {
-    const int64_t vj = (int64_t)v * ns + tid;
-    double* sh = cg.sh + vj * kShN;
-    const int32_t act = cg.act[vj];
-    int upd = 0;
-    if (act) {
-      const double z = sh[kShZeta], zn = sh[kShZetaNext];
+      zn = z * zp * ap / (ap * zp * (1.0 + alpha * ds) + alpha * bp * (zp - z));
       const double ratio = zn / z;
-      const double cr = zn, cp = beta * ratio * ratio;
-      sh[kShCr] = cr;
-      sh[kShCp] = cp;
-      s_cr[tid] = cr;
-      s_cp[tid] = cp;
-      const int32_t keep = (fabs(zn) * rnorm > tolabs) ? 1 : 0;
-      cg.act_next[vj] = keep;
+      const double cx = alpha * zn / z;
+      const bool in_ring = cg.ring_on && !(cg.seed_explicit && tid == seed);
+      ux = in_ring && m < cg.nslot ? 1 : 0;
+      if (ux) sh[kShSeg] = 1.0;
+      s_cx[tid] = cx;
+      s_cr[tid] = zn;
+      s_cp[tid] = beta * ratio * ratio;
+      keep = (fabs(zn) * rnorm > tolabs) ? 1 : 0;
       if (tid != seed) any_other |= keep;
-      if (tid == seed) s_seed_keep = keep;
-      upd = (!(cg.seed_explicit && tid == seed) && cg.ring_on && keep && m + 1 < cg.nslot) ? 1 : 0;
+      up = in_ring && keep && m + 1 < cg.nslot ? 1 : 0;
       sh[kShZetaPrev] = z;
       sh[kShZeta] = zn;
-    } else {
-      cg.act_next[vj] = 0;
-      if (tid == seed) s_seed_keep = 0;
     }
-    if (tid == seed) s_seed_act = act;
-    s_upd[tid] = upd;
+    cg.act_next[vj] = keep;
+    s_z[tid] = keep || tid == seed ? fabs(zn) : 0.0;
+    if (tid == seed) {
+      s_seed_act = on;
+      s_seed_keep = keep;
+    }
+    s_ux[tid] = ux;
+    s_up[tid] = up;
   }
   any_other = __syncthreads_or(any_other);
   if (tid == 0) {
@@ -433,46 +438,54 @@ __device__ __forceinline__ void cg_beta_state(const CgDev& cg, int32_t v, int32_
     int32_t seed_next = s_seed_keep;
     if (any_other && !seed_next && s_seed_act) {
       // the seed carries the Krylov space for the others: its direction keeps being updated
-      if (cg.ring_on && !cg.seed_explicit && m + 1 < cg.nslot) s_upd[seed] = 1;
+      if (cg.ring_on && !cg.seed_explicit && m + 1 < cg.nslot) s_up[seed] = 1;
     }
     if (any_other) seed_next = 1;
     if (seed_next != s_seed_keep) cg.act_next[vs] = seed_next;
     const int32_t any = any_other | seed_next;
     const double iters = sc[kScIters] + 1.0;
-    sc[kScAlphaPrev] = sc[kScAlpha];
-    sc[kScBetaPrev] = beta;
-    sc[kScRR] = rrn;
-    sc[kScIters] = iters;
-    fl[kFlM] = m + 1;
-    fl[kFlNeedRU] = need_ru ? 1 : 0;
-    if (!(rrn == rrn)) {
-      fl[kFlStatus] = kStBreakdown;
-      fl[kFlRun] = 0;
+    double zmax = 0.0;
+    for (int j = 0; j < ns; ++j) zmax = s_z[j] > zmax ? s_z[j] : zmax;
+    if (ru) sn[kScRU] = sc[kScRU] + 1.0;
+    sn[kScAlphaPrev] = alpha;
+    sn[kScBetaPrev] = beta;
+    sn[kScRR] = it.rrn;
+    sn[kScIters] = iters;
+    sn[kScZMax] = zmax;
+    if (mixed) sn[kScMaxR] = rnorm > it.maxr ? rnorm : it.maxr;
+    fn[kFlM] = m + 1;
+    fn[kFlSum] = nsum;
+    fn[kFlDefer] = it.defer && any ? 1 : 0;
+    fn[kFlNeedRU] = it.need_ru ? 1 : 0;
+    if (!(it.rrn == it.rrn)) {
+      fn[kFlStatus] = kStBreakdown;
+      fn[kFlRun] = 0;
     } else if (!any) {
-      fl[kFlRun] = 0;
-    } else if (iters >= sc[kScMaxIter]) {
-      fl[kFlStatus] = kStNoConv;
-      fl[kFlRun] = 0;
+      fn[kFlRun] = 0;
+    } else if (iters >= sc[kScMaxIter] && !it.defer) {
+      fn[kFlStatus] = kStNoConv;
+      fn[kFlRun] = 0;
     }
-    if (mixed) sc[kScMaxR] = rnorm > sc[kScMaxRc] ? rnorm : sc[kScMaxRc];
   }
   __syncthreads();
-  // p_j = cr_j r' + cp_j p_j on the segment coefficients: q = 0 the p_j0 coefficient, q = 1 + i the ring
-  // entry i <= m (both scaled by cp_j), q = m + 2 the new entry m + 1 (set to cr_j).  Updates need m + 1 <
-  // nslot <= cslots
-  const int32_t mc = min(m, cg.cslots - 2);
-  const int32_t per = mc + 3;
+  // One (shift, coefficient) pair per thread and round.  The pairs: q = 0 the p_j0 coefficient (x_j0 += cx p_j0,
+  // then scaled by cp), q = 1 + i the ring entry i <= m (d_ji += cx e_ji, e_ji scaled by cp), q = m + 2 the new
+  // entry m + 1 (e set to cr).  x is updated only while m < nslot <= cslots, p while m + 1 < nslot; past that
+  // (a single shift's segment index grows without flushes) the pairs stop at the last coefficient slot
+  const int32_t per = min(m, cg.cslots - 1) + 3;
   for (int t = tid; t < ns * per; t += blockDim.x) {
     const int32_t jj = t / per, q = t - jj * per;
-    if (!s_upd[jj]) continue;
     double* cf = cg.coef + ((int64_t)v * ns + jj) * nc;
     double* e = cf + 2 + cg.cslots;
-    if (q == 0)
-      cf[1] *= s_cp[jj];
-    else if (q <= m + 1)
-      e[q - 1] *= s_cp[jj];
-    else
-      e[m + 1] = s_cr[jj];
+    if (q == m + 2) {
+      if (s_up[jj]) e[m + 1] = s_cr[jj];
+      continue;
+    }
+    double* pc = q == 0 ? cf + 1 : e + (q - 1);
+    double* xc = q == 0 ? cf : cf + 1 + q;
+    if (q - 1 >= cg.cslots) continue;
+    if (s_ux[jj]) *xc = fma(s_cx[jj], *pc, *xc);
+    if (s_up[jj]) *pc *= s_cp[jj];
   }
 }
 
@@ -526,13 +539,13 @@ hipError_t launch_cg_start(const double* b, void* ring, T* p, int32_t nr, int64_
 template hipError_t launch_cg_start<double>(const double*, void*, double*, int32_t, int64_t, int64_t, hipStream_t);
 template hipError_t launch_cg_start<float>(const double*, void*, float*, int32_t, int64_t, int64_t, hipStream_t);
 
-// The element kernels of the iteration take their vectors in pieces of 16 bytes per lane, consecutive
-// lanes consecutive pieces; a block covers kCgChunk reals per step, all loads of a step in flight
-// together, and enough steps that about 1024 blocks and as many partials remain per rhs.
+// The update takes its vectors in pieces of 16 bytes per lane, consecutive lanes consecutive pieces: a block
+// covers kCgChunk reals per step, all loads of a step in flight together, in enough steps that at most 1024
+// blocks and as many partials remain per rhs.  Blocks of 1024 threads on as few partials are slower (21.1 us
+// against 18.2 at 16^4, 16.9 against 11.8 at 12^4, before the block sums were rewritten): they start and
+// stop together.
 constexpr int kCgChunk = 2048;
-static int cg_steps(int64_t n_reals) {
-  return (int)std::max<int64_t>(1, std::min<int64_t>(32, n_reals / ((int64_t)kCgChunk * 1024)));
-}
+static int cg_steps(int64_t n_reals) { return (int)std::max<int64_t>(1, n_reals / ((int64_t)kCgChunk * 1024)); }
 int cg_num_blocks(int64_t n_reals) {
   const int64_t c = (int64_t)kCgChunk * cg_steps(n_reals);
   return (int)((n_reals + c - 1) / c);
@@ -540,57 +553,74 @@ int cg_num_blocks(int64_t n_reals) {
 template <typename T>
 using Piece = T __attribute__((ext_vector_type(16 / sizeof(T))));
 
-// r' = r - alpha Ap (and x_hi[seed] += alpha p), with alpha; the last block of each rhs keeps the state
-template <typename T>
-__global__ void __launch_bounds__(256) k_cg_r(CgDev cg, const T* __restrict__ Ap, const T* __restrict__ p,
-                                              double* __restrict__ x_hi, const double* __restrict__ r64, int64_t n,
-                                              int32_t steps) {
+// the last block of a rhs: a copy of the state, to be changed by cg_state after a barrier
+__device__ __forceinline__ void cg_state_copy(const CgDev& cg, int32_t v) {
+  if (threadIdx.x < kScN) cg.sc_next[(int64_t)v * kScN + threadIdx.x] = cg.sc[(int64_t)v * kScN + threadIdx.x];
+  if (threadIdx.x >= 64 && threadIdx.x < 64 + kFlN) {
+    const int32_t i = threadIdx.x - 64;
+    cg.flags_next[(int64_t)v * kFlN + i] = i == kFlNeedRU ? 0 : cg.flags[(int64_t)v * kFlN + i];
+  }
+}
+
+// One launch of the update; PART 0: all of it, 1: alpha and r' alone, 2: beta, p, the seed's solution and the
+// state (launch_cg_step2).
+template <typename T, int PART>
+__global__ void __launch_bounds__(256) k_cg_step(CgDev cg, const T* __restrict__ Ap, T* __restrict__ p,
+                                                      float* __restrict__ x_lo, double* __restrict__ x_hi,
+                                                      const double* __restrict__ r64, int64_t n, int32_t steps,
+                                                      int32_t mixed, int32_t nsum) {
   constexpr int N = 16 / sizeof(T), U = kCgChunk / (256 * N);
-  __shared__ double lds[1][16];
-  __shared__ double s_bc;
+  constexpr bool R = PART != 2, P = PART != 1;   // the residual, the direction
+  __shared__ double lds[4][16], lds_r[1][16];
   const int32_t v = blockIdx.y;
-  int32_t* fl = cg.flags + (int64_t)v * kFlN;
-  const bool state = blockIdx.x + 1 == gridDim.x;
+  const int32_t* fl = cg.flags + (int64_t)v * kFlN;
+  const bool run = fl[kFlRun] != 0;
   const bool ru = cg.part_ru && fl[kFlNeedRU] != 0;
-  const int32_t m = fl[kFlM];
+  const int32_t m = fl[kFlM], sum = fl[kFlSum];
   const int32_t st[3] = {fl[kFlBase], fl[kFlBase32], fl[kFlK0]};
-  const double rr_sc = cg.sc[(int64_t)v * kScN + kScRR];
-  if (fl[kFlRun] == 0) {
-    if (state && threadIdx.x == 0) fl[kFlLive] = 0;
+  if (P && blockIdx.x + 1 == gridDim.x) {
+    cg_state_copy(cg, v);
+    if (!run) return;
+    const CgParts<PART == 2> pt(cg, v, ru, sum, nsum);
+    const CgStep it = cg_scalars<PART == 2>(cg, v, ru, mixed, pt, lds);
+    cg_state(cg, v, ru, mixed, nsum, it);
     return;
   }
-  if (state) {
-    const CgAlpha al = cg_alpha(cg, v, ru, rr_sc, lds, &s_bc);
-    cg_alpha_state(cg, v, ru, al);
-    return;
-  }
-  const T* rc = entry<T>(cg, v, st, m, n);
+  if (!run) return;
+  const T* rc = R ? entry<T>(cg, v, st, m, n) : nullptr;
   T* rn = entry<T>(cg, v, st, m + 1, n);
   const T* av = Ap + (int64_t)v * n;
-  const T* pv = p + (int64_t)v * n;
-  double* xs = x_hi ? x_hi + ((int64_t)v * cg.n_shift + cg.seed[v]) * n : nullptr;
+  T* pv = p + (int64_t)v * n;
   const double* r64v = r64 ? r64 + (int64_t)v * n : nullptr;
   const bool from64 = r64 && ru;
-  Piece<T> r0[U], a4[U];
+  Piece<T> r4[U], a4[U], p4[U];
   auto load = [&](int64_t i0) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t i = i0 + (int64_t)u * 256 * N;
       if (i >= n) break;
-      if (from64) {
+      if (!R) {
+        r4[u] = *(const Piece<T>*)(rn + i);
+      } else if (from64) {
 #pragma unroll
-        for (int k = 0; k < N; ++k) r0[u][k] = (T)r64v[i + k];
+        for (int k = 0; k < N; ++k) r4[u][k] = (T)r64v[i + k];
       } else {
-        r0[u] = *(const Piece<T>*)(rc + i);
+        r4[u] = *(const Piece<T>*)(rc + i);
       }
-      a4[u] = *(const Piece<T>*)(av + i);
+      if (R) a4[u] = *(const Piece<T>*)(av + i);
+      if (P) p4[u] = *(const Piece<T>*)(pv + i);
     }
   };
   const int64_t b0 = (int64_t)blockIdx.x * steps * kCgChunk + threadIdx.x * N;
+  const CgParts<PART == 2> pt(cg, v, ru, sum, nsum);
   load(b0);   // in flight while the partials are summed
-  const CgAlpha al = cg_alpha(cg, v, ru, rr_sc, lds, &s_bc);
-  if (!al.ok) return;
-  const T alpha = (T)al.alpha;
+  const CgStep it = cg_scalars<PART == 2>(cg, v, ru, mixed, pt, lds);
+  if (it.done || !it.ok) return;
+  const T alpha = (T)it.alpha, beta = (T)it.beta;
+  float* xl = x_lo ? x_lo + (int64_t)v * n : nullptr;
+  // with a reliable update due the seed's increment goes into its FP64 solution now (x_hi[seed] += x_lo,
+  // x_lo = 0), ahead of the update's FP64 residual stencil
+  double* xh = x_hi && (!x_lo || it.need_ru) ? x_hi + ((int64_t)v * cg.n_shift + cg.seed[v]) * n : nullptr;
   double d[1] = {0.0};
   for (int32_t t = 0; t < steps; ++t) {
     const int64_t i0 = b0 + (int64_t)t * kCgChunk;
@@ -599,122 +629,77 @@ __global__ void __launch_bounds__(256) k_cg_r(CgDev cg, const T* __restrict__ Ap
     for (int u = 0; u < U; ++u) {
       const int64_t i = i0 + (int64_t)u * 256 * N;
       if (i >= n) break;
-      Piece<T> r1;
+      Piece<T> r1 = r4[u];
+      if (R) {
 #pragma unroll
-      for (int k = 0; k < N; ++k) {
-        r1[k] = fmadd(-alpha, a4[u][k], r0[u][k]);
-        d[0] = fma((double)r1[k], (double)r1[k], d[0]);
+        for (int k = 0; k < N; ++k) {
+          r1[k] = fmadd(-alpha, a4[u][k], r4[u][k]);
+          d[0] = fma((double)r1[k], (double)r1[k], d[0]);
+        }
+        *(Piece<T>*)(rn + i) = r1;
       }
-      *(Piece<T>*)(rn + i) = r1;
-      if (xs) {
+      if (!P) continue;
+      Piece<T> p1;
 #pragma unroll
-        for (int k = 0; k < N; ++k) xs[i + k] = fma(al.alpha, (double)pv[i + k], xs[i + k]);
-      }
-    }
-  }
-  block_sum<1>(d, lds);
-  if (threadIdx.x == 0) cg.part_e[(int64_t)v * cg.nblk_e + blockIdx.x] = d[0];
-}
-
-template <typename T>
-hipError_t launch_cg_r_update(const CgDev& cg, const T* Ap, const T* p, double* x_hi, const double* r64,
-                              int64_t n_reals, hipStream_t s) {
-  if (cg.n_shift > kMaxShifts || cg.nblk_e != cg_num_blocks(n_reals)) return hipErrorInvalidValue;
-  if (sizeof(T) == 4 && !cg.ring32) return hipErrorInvalidValue;
-  dim3 grid(cg.nblk_e + 1, cg.n_rhs);
-  hipLaunchKernelGGL((k_cg_r<T>), grid, dim3(256), 0, s, cg, Ap, p, x_hi, r64, n_reals, cg_steps(n_reals));
-  return hipGetLastError();
-}
-template hipError_t launch_cg_r_update<double>(const CgDev&, const double*, const double*, double*, const double*,
-                                               int64_t, hipStream_t);
-template hipError_t launch_cg_r_update<float>(const CgDev&, const float*, const float*, double*, const double*,
-                                              int64_t, hipStream_t);
-
-// p = r' + beta p with beta, and in the FP32 phase x_lo += alpha p; the last block of each rhs keeps
-// the state.  (p is updated in the iteration its rhs converges in, too: nothing reads it then.)
-template <typename T>
-__global__ void __launch_bounds__(256) k_cg_p(CgDev cg, T* __restrict__ p, float* __restrict__ x_lo,
-                                              double* __restrict__ x_hi, int64_t n, int32_t steps, int32_t mixed) {
-  constexpr int N = 16 / sizeof(T), U = kCgChunk / (256 * N);
-  __shared__ double lds[1][16];
-  __shared__ double s_bc;
-  const int32_t v = blockIdx.y;
-  const int32_t* fl = cg.flags + (int64_t)v * kFlN;
-  const double* scv = cg.sc + (int64_t)v * kScN;
-  const bool state = blockIdx.x + 1 == gridDim.x;
-  const int32_t mn = fl[kFlMn];
-  const int32_t st[3] = {fl[kFlBase], fl[kFlBase32], fl[kFlK0]};
-  const double rr_old = scv[kScRRc], maxr = scv[kScMaxRc], delta = scv[kScDelta], alpha_d = scv[kScAlpha];
-  if (fl[kFlLive] == 0) return;
-  const T* r = entry<T>(cg, v, st, mn, n);
-  T* pv = p + (int64_t)v * n;
-  Piece<T> pold[U], rv[U];
-  auto load = [&](int64_t i0) {
+      for (int k = 0; k < N; ++k) p1[k] = fmadd(beta, p4[u][k], r1[k]);
+      *(Piece<T>*)(pv + i) = p1;
+      if (sizeof(T) == 8) {
+        if (xh) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t i = i0 + (int64_t)u * 256 * N;
-      if (i >= n) break;
-      pold[u] = *(const Piece<T>*)(pv + i);
-      rv[u] = *(const Piece<T>*)(r + i);
-    }
-  };
-  const int64_t b0 = (int64_t)blockIdx.x * steps * kCgChunk + threadIdx.x * N;
-  if (!state) load(b0);   // in flight while the partials are summed
-  const double rrn = block_total(cg.part_e + (int64_t)v * cg.nblk_e, cg.nblk_e, lds, &s_bc);
-  const double beta_d = rrn / rr_old;
-  // a reliable update once the residual norm fell below delta times its largest value since the last one
-  const double rnorm = sqrt(rrn);
-  const bool need_ru = mixed && rnorm < delta * (rnorm > maxr ? rnorm : maxr);
-  if (state) {
-    cg_beta_state(cg, v, mixed, rrn, beta_d, need_ru);
-    return;
-  }
-  const T beta = (T)beta_d;
-  const float alpha = (float)alpha_d;
-  float* xl = x_lo ? x_lo + (int64_t)v * n : nullptr;
-  // with a reliable update due the seed's increment goes into its FP64 solution now (x_hi[seed] += x_lo,
-  // x_lo = 0), ahead of the update's FP64 residual stencil
-  double* xh = x_lo && x_hi && need_ru ? x_hi + ((int64_t)v * cg.n_shift + cg.seed[v]) * n : nullptr;
-  for (int32_t t = 0; t < steps; ++t) {
-    const int64_t i0 = b0 + (int64_t)t * kCgChunk;
-    if (t > 0) load(i0);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t i = i0 + (int64_t)u * 256 * N;
-      if (i >= n) break;
-      if (xl) {
+          for (int k = 0; k < N; ++k) xh[i + k] = fma(it.alpha, (double)p4[u][k], xh[i + k]);
+        }
+      } else {
         // the seed's increment of this iteration, alpha p, in FP32 until the next reliable update
-        float inc[N];
+        Piece<float> inc = *(const Piece<float>*)(xl + i);
 #pragma unroll
-        for (int k = 0; k < N; ++k) inc[k] = fmaf(alpha, (float)pold[u][k], xl[i + k]);
+        for (int k = 0; k < N; ++k) inc[k & 3] = fmaf((float)alpha, (float)p4[u][k], inc[k & 3]);
         if (xh) {
 #pragma unroll
           for (int k = 0; k < N; ++k) {
-            xh[i + k] += (double)inc[k];
-            xl[i + k] = 0.0f;
+            xh[i + k] += (double)inc[k & 3];
+            inc[k & 3] = 0.0f;
           }
-        } else {
-#pragma unroll
-          for (int k = 0; k < N; ++k) xl[i + k] = inc[k];
         }
+        *(Piece<float>*)(xl + i) = inc;
       }
-      Piece<T> pn;
-#pragma unroll
-      for (int k = 0; k < N; ++k) pn[k] = fmadd(beta, pold[u][k], rv[u][k]);
-      *(Piece<T>*)(pv + i) = pn;
     }
+  }
+  if (R) {
+    block_sum<1>(d, lds_r);
+    if (threadIdx.x == 0) cg.part_e_next[(int64_t)v * cg.nblk_e + blockIdx.x] = d[0];
   }
 }
 
-template <typename T>
-hipError_t launch_cg_p_update(const CgDev& cg, T* p, float* x_lo, double* x_hi, int32_t mixed, int64_t n_reals,
-                              hipStream_t s) {
-  if (cg.nblk_e != cg_num_blocks(n_reals)) return hipErrorInvalidValue;
-  if (sizeof(T) == 4 && !cg.ring32) return hipErrorInvalidValue;
-  dim3 grid(cg.nblk_e + 1, cg.n_rhs);
-  hipLaunchKernelGGL((k_cg_p<T>), grid, dim3(256), 0, s, cg, p, x_lo, x_hi, n_reals, cg_steps(n_reals), mixed);
+template <typename T, int PART>
+static hipError_t launch_cg_part(const CgDev& cg, const T* Ap, T* p, float* x_lo, double* x_hi, const double* r64,
+                                 int32_t mixed, int64_t n_reals, hipStream_t s) {
+  const int32_t nblk = cg_num_blocks(n_reals);
+  if (cg.n_shift > kMaxShifts || cg.nblk_e < nblk) return hipErrorInvalidValue;
+  if (sizeof(T) == 4 && (!cg.ring32 || !x_lo)) return hipErrorInvalidValue;
+  dim3 grid(nblk + (PART == 1 ? 0 : 1), cg.n_rhs);
+  hipLaunchKernelGGL((k_cg_step<T, PART>), grid, dim3(256), 0, s, cg, Ap, p, x_lo, x_hi, r64, n_reals,
+                     cg_steps(n_reals), mixed, nblk);
   return hipGetLastError();
 }
+template <typename T>
+hipError_t launch_cg_step(const CgDev& cg, const T* Ap, T* p, float* x_lo, double* x_hi, const double* r64,
+                          int32_t mixed, int64_t n_reals, hipStream_t s) {
+  return launch_cg_part<T, 0>(cg, Ap, p, x_lo, x_hi, r64, mixed, n_reals, s);
+}
+template <typename T>
+hipError_t launch_cg_step2(const CgDev& cg, const T* Ap, T* p, float* x_lo, double* x_hi, const double* r64,
+                           int32_t mixed, int64_t n_reals, hipStream_t s) {
+  const hipError_t e = launch_cg_part<T, 1>(cg, Ap, p, x_lo, x_hi, r64, mixed, n_reals, s);
+  return e != hipSuccess ? e : launch_cg_part<T, 2>(cg, Ap, p, x_lo, x_hi, r64, mixed, n_reals, s);
+}
+#define RMH_CG(T)                                                                                                   \
+  template hipError_t launch_cg_step<T>(const CgDev&, const T*, T*, float*, double*, const double*, int32_t, int64_t, \
+                                        hipStream_t);                                                              \
+  template hipError_t launch_cg_step2<T>(const CgDev&, const T*, T*, float*, double*, const double*, int32_t, int64_t, \
+                                         hipStream_t);
+RMH_CG(double)
+RMH_CG(float)
+#undef RMH_CG
 
 // x_hi[seed] += x_lo, x_lo = 0: for the rhs with a pending reliable update, or for all
 __global__ void k_cg_xfold(CgDev cg, float* __restrict__ x_lo, double* __restrict__ x_hi, int32_t all, int64_t n) {
@@ -736,9 +721,6 @@ hipError_t launch_cg_xfold(const CgDev& cg, float* x_lo, double* x_hi, int32_t a
   hipLaunchKernelGGL(k_cg_xfold, grid, dim3(kBlock), 0, s, cg, x_lo, x_hi, all, n_reals);
   return hipGetLastError();
 }
-
-template hipError_t launch_cg_p_update<double>(const CgDev&, double*, float*, double*, int32_t, int64_t, hipStream_t);
-template hipError_t launch_cg_p_update<float>(const CgDev&, float*, float*, double*, int32_t, int64_t, hipStream_t);
 
 // s + sum of c_i r_i over i <= m, in groups of eight (entries past m carry zero coefficients)
 template <int NS>

@@ -15,10 +15,53 @@ namespace rmh {
 // ------------------------------------------------------------------------------------------
 // reductions
 
+// v plus its value in another lane, by data-parallel-primitive moves (CTRL) within rows of 16 lanes
+template <int CTRL>
+__device__ __forceinline__ double add_dpp(double v) {
+  const uint64_t w = __builtin_bit_cast(uint64_t, v);
+  const uint32_t l = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)w, CTRL, 0xf, 0xf, false);
+  const uint32_t h = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(w >> 32), CTRL, 0xf, 0xf, false);
+  return v + __builtin_bit_cast(double, (uint64_t)l | ((uint64_t)h << 32));
+}
+
+// Butterfly over lane distances 32, 16, 8, 4, 2, 1, the result in every lane.  Distances 32 and 16 are swaps of
+// lane halves and rows; for 8 and 4 a rotation of the row by as much finds the same values (the lanes 8 apart
+// are equal by then); 2 and 1 are quad permutations.  Moves through registers: shuffles go through the LDS
+// unit, some 90 cycles for each of the six dependent steps.
 __device__ __forceinline__ double wave_sum(double v) {
+  const auto swap_add = [](double x, auto swap) {
+    const uint64_t w = __builtin_bit_cast(uint64_t, x);
+    const auto l = swap((uint32_t)w), h = swap((uint32_t)(w >> 32));
+    return __builtin_bit_cast(double, (uint64_t)(uint32_t)l[0] | ((uint64_t)(uint32_t)h[0] << 32)) +
+           __builtin_bit_cast(double, (uint64_t)(uint32_t)l[1] | ((uint64_t)(uint32_t)h[1] << 32));
+  };
+  v = swap_add(v, [](uint32_t x) { return __builtin_amdgcn_permlane32_swap(x, x, false, false); });
+  v = swap_add(v, [](uint32_t x) { return __builtin_amdgcn_permlane16_swap(x, x, false, false); });
+  v = add_dpp<0x128>(v);   // row_ror:8
+  v = add_dpp<0x124>(v);   // row_ror:4
+  v = add_dpp<0x4e>(v);    // quad_perm [2, 3, 0, 1]
+  return add_dpp<0xb1>(v); // quad_perm [1, 0, 3, 2]
+}
+
+// Sum of the waves' values in order; all reads in flight together (one after the other they cost an LDS
+// latency per wave).
+__device__ __forceinline__ double waves_sum(const double* w) {
+  const int nw = (blockDim.x + 63) >> 6;
+  double s = 0.0;
+  if (nw <= 4) {
 #pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-  return v;
+    for (int i = 0; i < 4; ++i) {
+      const double t = w[i];
+      s = i < nw ? s + t : s;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const double t = w[i];
+      s = i < nw ? s + t : s;
+    }
+  }
+  return s;
 }
 
 // Sum over the block (any multiple of 64 threads up to 1024); result valid in thread 0.
@@ -32,15 +75,24 @@ __device__ __forceinline__ void block_sum(double (&v)[NQ], double (*lds)[16]) {
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    const int nw = (blockDim.x + 63) >> 6;
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      double s = 0.0;
-      for (int i = 0; i < nw; ++i) s += lds[q][i];
-      v[q] = s;
-    }
+    for (int q = 0; q < NQ; ++q) v[q] = waves_sum(lds[q]);
   }
   __syncthreads();  // lds may be reused by the caller right away
+}
+
+// The same with the result in every thread; the caller does not reuse lds before a barrier.
+template <int NQ>
+__device__ __forceinline__ void block_sum_all(double (&v)[NQ], double (*lds)[16]) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    double w = wave_sum(v[q]);
+    if (lane == 0) lds[q][wid] = w;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) v[q] = waves_sum(lds[q]);
 }
 
 // Strided fixed-order sum of n values by a whole block; result in thread 0.

@@ -148,11 +148,21 @@ __device__ __forceinline__ void load_field(const T* __restrict__ xf, int32_t s, 
     for (int b = 0; b < 8; ++b) f[i][b] = r.get();
 }
 
+// The current residual of field v in the CG's ring (HopArgs::ring), of which dot 0 is taken.
+template <typename T>
+__device__ __forceinline__ const T* hop_ring_field(const HopArgs<T>& A, int32_t v) {
+  if (!A.ring) return nullptr;
+  const int32_t* fl = A.run - kFlRun + (int64_t)v * A.run_stride;
+  const int32_t i = sizeof(T) == 8 ? fl[kFlBase] + fl[kFlM] : fl[kFlBase32] + fl[kFlM] - fl[kFlK0];
+  return A.ring + ((int64_t)v * A.ring_slots + i % A.ring_slots) * 32 * (int64_t)A.g.V;
+}
+
 // The epilogue at one site: out = a h + b x + c z for NV directions from nu0 on, and the partial dot
-// products.  kLoadX: x is read back from the field, else it is handed over in xc.  Per direction the
+// products.  kLoadX: x is read back from the field, else it is handed over in xc.  kRing: the kernel takes
+// HopArgs::ring (the walk has no registers left for it).  Per direction the
 // loads of x and z come before the stores (z may be the output itself, each element read and
 // written by this thread only), so they overlap.
-template <typename T, int NV, bool DOTS, bool kLoadX>
+template <typename T, int NV, bool DOTS, bool kLoadX, bool kRing>
 __device__ __forceinline__ void hop_store(const HopArgs<T>& A, int32_t v, const T* __restrict__ xf, const T (*xc)[8],
                                           int nu0, int32_t s, bool store, const T (*acc)[8], double* dsum) {
   const int64_t V = A.g.V;
@@ -162,6 +172,7 @@ __device__ __forceinline__ void hop_store(const HopArgs<T>& A, int32_t v, const 
   const T cc = T(A.c);
   const T* zf = A.z ? A.z + (int64_t)(v / A.z_div) * FV : nullptr;  // may alias out
   T* outf = A.out + (int64_t)v * FV;
+  const T* rf = DOTS && kRing ? hop_ring_field(A, v) : nullptr;   // z is null with it
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
     T xs[8], zv[8];
@@ -199,7 +210,7 @@ __device__ __forceinline__ void hop_store(const HopArgs<T>& A, int32_t v, const 
 #pragma unroll
       for (int a = 0; a < 8; ++a) {
         const double xd = (double)xs[a], od = (double)w[a];
-        dsum[0] = fma(xd, xd, dsum[0]);
+        if (!kRing || !rf) dsum[0] = fma(xd, xd, dsum[0]);
         dsum[1] = fma(od, xd, dsum[1]);
         dsum[2] = fma(od, od, dsum[2]);
       }
@@ -211,6 +222,14 @@ __device__ __forceinline__ void hop_store(const HopArgs<T>& A, int32_t v, const 
         __builtin_nontemporal_store(w[a], outr.ptr());
         outr.next();
       }
+    }
+    if (DOTS && kRing && rf) {   // last, where the fewest registers are in use
+      Rows<T> rr(rf + r0, V, byte_off<T>(s));
+      T rv[8];
+#pragma unroll
+      for (int a = 0; a < 8; ++a) rv[a] = rr.get();
+#pragma unroll
+      for (int a = 0; a < 8; ++a) dsum[0] = fma((double)w[a], (double)rv[a], dsum[0]);
     }
   }
 }
@@ -283,7 +302,7 @@ __global__ void __launch_bounds__(256) k_hop(const HopArgs<T> A, int32_t xcd, in
       hop_term_fwd<T, FORM, NV>(U + (int64_t)mu * 18 * V, s, site_shift(A.g, s, xc, mu, +1), xf, nu0, V, acc);
     }
     hop_finish<T, FORM, NV>(acc);
-    hop_store<T, NV, DOTS, true>(A, v, xf, nullptr, nu0, s, A.store != 0, acc, dsum);
+    hop_store<T, NV, DOTS, true, true>(A, v, xf, nullptr, nu0, s, A.store != 0, acc, dsum);
   }
   if (DOTS) {
     __shared__ double lds[3][16];
@@ -365,6 +384,7 @@ __global__ void __launch_bounds__(256) k_hop_split(const HopArgs<T> A, int32_t x
     const T cc = T(A.c);
     const T* zf = A.z ? A.z + (int64_t)(v / A.z_div) * FV : nullptr;  // may alias out
     T* outf = A.out + (int64_t)v * FV;
+    const T* rf = DOTS ? hop_ring_field(A, v) : nullptr;   // z is null with it
     using Bits = typename std::conditional<sizeof(T) == 8, uint64_t, uint32_t>::type;
     const Bits m0 = mu == 0 ? ~Bits(0) : Bits(0), m1 = mu == 1 ? ~Bits(0) : Bits(0);
     const Bits m2 = mu == 2 ? ~Bits(0) : Bits(0), m3 = mu == 3 ? ~Bits(0) : Bits(0);
@@ -377,7 +397,7 @@ __global__ void __launch_bounds__(256) k_hop_split(const HopArgs<T> A, int32_t x
       hs[q] = __builtin_bit_cast(T, hb_);
       const int64_t e = (int64_t)(nu0 * 8 + 4 * q + mu) * V + s;
       xs[q] = xf[e];
-      zv[q] = !zf ? T(0) : A.z_div == 1 ? __builtin_nontemporal_load(&zf[e]) : zf[e];
+      zv[q] = rf ? rf[e] : !zf ? T(0) : A.z_div == 1 ? __builtin_nontemporal_load(&zf[e]) : zf[e];
     }
 #pragma unroll
     for (int q = 0; q < 2 * NV; ++q) {
@@ -389,7 +409,7 @@ __global__ void __launch_bounds__(256) k_hop_split(const HopArgs<T> A, int32_t x
       if (A.store) __builtin_nontemporal_store(o, &outf[e]);
       if (DOTS) {
         const double xd = (double)xv, od = (double)o;
-        dsum[0] = fma(xd, xd, dsum[0]);
+        dsum[0] = rf ? fma(od, (double)zv[q], dsum[0]) : fma(xd, xd, dsum[0]);
         dsum[1] = fma(od, xd, dsum[1]);
         dsum[2] = fma(od, od, dsum[2]);
       }
@@ -540,7 +560,7 @@ k_hop_walk(const HopArgs<T> A, int32_t xcd, int32_t K, int32_t tile2, int32_t la
         hop_apply<T, FORM, NV, false>(u, fwd, acc);
       }
       hop_finish<T, FORM, NV>(acc);
-      hop_store<T, NV, DOTS, false>(A, v, xf, cen, nu0, s, A.store != 0, acc, dsum);
+      hop_store<T, NV, DOTS, false, false>(A, v, xf, cen, nu0, s, A.store != 0, acc, dsum);
 #pragma unroll
       for (int i = 0; i < NV; ++i)
 #pragma unroll
@@ -653,7 +673,7 @@ __global__ void __launch_bounds__(256) k_hop_ns(const HopArgs<T> A, int32_t xcd,
     }
 #pragma unroll
     for (int f = 0; f < NS; ++f)
-      hop_store<T, 4, DOTS, true>(A, v0 + f, xf[f], nullptr, 0, s, A.store && runs[f], acc + f * 4, dsum + f * 3);
+      hop_store<T, 4, DOTS, true, true>(A, v0 + f, xf[f], nullptr, 0, s, A.store && runs[f], acc + f * 4, dsum + f * 3);
   }
   if (DOTS) {
     __shared__ double lds[NS * 3][16];
@@ -849,6 +869,7 @@ k_hop_tile(const HopArgs<T> A, const HopTile S, int32_t xcd) {
   const T ca = T(A.a), cb = T(A.b_rhs ? A.b_rhs[v] : A.b), cc = T(A.c);
   const T* zf = Z ? A.z + (int64_t)(v / A.z_div) * FV : nullptr;   // may alias out
   T* outf = A.out + (int64_t)v * FV;
+  const T* rf = DOTS && !Z ? hop_ring_field(A, v) : nullptr;
   const uint32_t buf = (uint32_t)(S.R1 * S.R2 * L0) * PB;          // one plane of the tile in LDS
   double dsum[3] = {0.0, 0.0, 0.0};
   uint32_t pl = (uint32_t)x3_0 * plane;
@@ -918,6 +939,7 @@ k_hop_tile(const HopArgs<T> A, const HopTile S, int32_t xcd) {
         zr.next();
       }
     }
+    if (DOTS && !Z && rf) get_half(rf, V, hf + gc + pl, q);
     whole_link(la, u);
     hop_pair<T, false>(u, p, acc);    // x3 forward; phi(x+3) is the next plane
     if (live) lds_put<T>(nxt + lc, p);
@@ -936,7 +958,7 @@ k_hop_tile(const HopArgs<T> A, const HopTile S, int32_t xcd) {
       w[i >> 3][i & 7] = o;
       if (DOTS && live) {
         const double xd = (double)r[i >> 3][i & 7], od = (double)o;
-        dsum[0] = fma(xd, xd, dsum[0]);
+        dsum[0] = !Z && rf ? fma(od, (double)q[i >> 3][i & 7], dsum[0]) : fma(xd, xd, dsum[0]);
         dsum[1] = fma(od, xd, dsum[1]);
         dsum[2] = fma(od, od, dsum[2]);
       }
@@ -1033,6 +1055,11 @@ int hop_split_ok(const HopConfig& cfg) {
   return ((cfg.order == 2 || cfg.order == 3) && (cfg.block / 64) % (4 / cfg.nv) == 0) ? 1 : 0;
 }
 static int hop_split_spb(const HopConfig& cfg) { return (cfg.block / 64) / (4 / cfg.nv) * 16; }
+
+bool hop_ring_ok(const Geom& g, const HopConfig& cfg) {
+  HopTile tile;
+  return hop_tile_of(g, cfg, &tile) || hop_split_ok(cfg) || !hop_walk_ok(g, cfg);
+}
 
 int hop_num_blocks(const Geom& g, const HopConfig& cfg) {
   HopTile tile;
@@ -1136,6 +1163,7 @@ static hipError_t launch_hop_nv(const HopArgs<T>& A, const HopConfig& cfg, hipSt
 template <typename T>
 hipError_t launch_hop(const HopArgs<T>& A, const HopConfig& cfg, hipStream_t s) {
   if (A.n_rhs == 0 || A.g.V == 0) return hipSuccess;
+  if (A.ring && (A.z || !A.run || A.ring_slots < 1 || !hop_ring_ok(A.g, cfg))) return hipErrorInvalidValue;
   if (cfg.form == kFormMatrix) return launch_hop_nv<T, kFormMatrix>(A, cfg, s);
   if (cfg.form == kFormAdjoint) return launch_hop_nv<T, kFormAdjoint>(A, cfg, s);
   return launch_hop_nv<T, kFormStream>(A, cfg, s);

@@ -117,6 +117,51 @@ def test_rational_apply_long_segments(mode, kappa, tol):
             assert np.linalg.norm(Ph[i] - olap.laplacian(U, xp[i, j], L, sj)) <= 1.01 * tol * bn, (i, j)
 
 
+# form, block, nv, order, walk, tile2: the hop-split, one-launch-per-site and tiled-walk stencils, whose
+# iterations take one update, and the walk, whose iterations take two
+CG_SHAPES = [(1, 256, 2, 2, 0, 1), (1, 128, 2, 0, 0, 1), (1, 128, 2, 1, 2, 2), (1, 64, 4, 1, 2, 1)]
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("shape", CG_SHAPES, ids=["split", "site", "tile", "walk"])
+def test_rational_apply_update_forms(mode, shape):
+    """Each form of the CG update on the free field, where the eigenvectors are plane waves: a source of one
+    eigenvector converges in one iteration and one of two in two, far past the digits of the predicted
+    residual norm, beside a Gaussian source and alone; x_j = sum of parts / (lambda + sigma_j)."""
+    L = (4, 6, 4, 4)
+    tol = 1e-10
+    announce(f"rational_apply update forms mode={mode} shape={shape}")
+    U, P, Ud, Pd = setup(L, "unit", 0.0, 5, n=3)
+    x0 = torch.arange(Pd.shape[-1], device=Pd.device) % L[0]
+    e1 = torch.cos(2 * torch.pi * x0.double() / L[0])     # lambda = 2
+    e2 = torch.cos(torch.pi * x0.double())                # lambda = 4
+    Pd[0] = e1
+    Pd[1] = e1 + 0.25 * e2
+    rat = _rat_kappa(0.9, 6)
+    form, block, nv, order, walk, tile2 = shape
+    try:
+        for n in (1, 3):
+            for dt in (torch.float64, torch.float32):
+                api.tune_set(L, dt, n, form, block, 1, nv, order, walk, 1, "cg", tile2)
+        both = api.rational_apply(L, Ud, Pd, rat, api.Solver(tol=tol, mode=mode), want_poles=True)
+        alone = [api.rational_apply(L, Ud, Pd[i:i + 1].contiguous(), rat, api.Solver(tol=tol, mode=mode), want_poles=True)
+                 for i in (0, 1)]
+    finally:
+        api.tune_clear()
+    assert both["stats"]["true_relres_max"] <= tol
+    if mode == 0:
+        assert [a["stats"]["iters"] for a in alone] == [1, 2]
+    for i, part in ((0, 0.0), (1, 0.25)):
+        bn = float(torch.linalg.norm(Pd[i]))
+        for j, sj in enumerate(rat.sigma):
+            want = (e1 / (2 + sj) + part * e2 / (4 + sj)).expand_as(Pd[i])
+            for x in (both["x_poles"][i, j], alone[i]["x_poles"][0, j]):
+                assert float(torch.linalg.norm(x - want)) <= tol * bn / sj, (i, j)
+    for j, sj in enumerate(rat.sigma):
+        r = Pd[2].cpu().numpy() - olap.laplacian(U, both["x_poles"][2, j].cpu().numpy(), L, sj)
+        assert np.linalg.norm(r) <= 1.01 * tol * float(torch.linalg.norm(Pd[2])), j
+
+
 @pytest.mark.parametrize("switch", [-1.0, 1e-2, 1e-4, 1e-7])
 @pytest.mark.parametrize("basis", [3, 16, 32])
 def test_mixed_switch_points(switch, basis):
