@@ -1157,23 +1157,29 @@ rmh_status cheb_filter_t(const Geom& g, const T* U, const T* x, int32_t n_rhs, i
 //   dL/d omega = (1/8) <tb_1, dDelta t_0> + (1/4) sum_{k=2..D} <tb_k, dDelta t_{k-1}>,
 //   dL/dx      = tb_0 = G_0 + A tb_1 - tb_2  (through the recursion only).
 // t_D, t_{D-1} come from a forward sweep; the reverse sweep then runs the recursion backwards,
-// t_{k-2} = 2A t_{k-1} - t_k, so only two t and two tb vectors are held.  2A = -H/4.
-// tb_j lives in B[(j-1) % 2] and t_j (j >= 1) in T[(j-1) % 2], and B[i] is followed by T[i] in
-// memory: the two recursion steps of a reverse step (tb_k from tb_{k+1}, tb_{k+2} and t_{k-2} from
-// t_{k-1}, t_k) then read one 2 n_rhs-field batch and write another, and go out as one launch.
+// t_{k-2} = 2A t_{k-1} - t_k, so only a few t and tb vectors are held.  2A = -H/4.
+// Reverse step j = D - k writes slot j % R, {tb_k, t_{k-2}} one after the other in memory, from the two slots
+// before it, {tb_{k+1}, t_{k-1}} and {tb_{k+2}, t_k}: one launch over 2 n_rhs fields, the source G_k added to the
+// first n_rhs of them.  The link term of step k pairs tb_k with t_{k-1} of the slot before; `batch` steps go into
+// one launch, since its 8 x 8 products with R(U) and the update of the gradient cost as much as two pairs
+// (16^4: 26 us and 12 per pair; 64 steps one by one 2.42 ms, by four @F@): R = batch + 1 slots, or with batch = 1 two,
+// the slot of step j - 2 overwritten in place.
+constexpr int kBwdBatch = 4;
+// Batches while the slots stay small (10 fields of 256 MiB); past that memory goes first.
+constexpr int64_t kBwdBatchSites = 1 << 20;
+
 struct ChebBwdPlan {
-  double* T[2];
-  double* B[2];
+  int32_t batch, R;
+  double* slot[kBwdBatch + 1];   // tb, then t
   double* coef;   // [n_rhs][n_y][D+1], then [n_rhs][n_y] scaled k = 0 coefficients
 };
 
 ChebBwdPlan plan_cheb_bwd(Carver& c, const Geom& g, int32_t n_rhs, int32_t n_y, int32_t D) {
   ChebBwdPlan p{};
   const size_t fr = (size_t)n_rhs * 32 * g.V;
-  for (int i = 0; i < 2; ++i) {
-    p.B[i] = c.take<double>(2 * fr);
-    p.T[i] = p.B[i] + fr;
-  }
+  p.batch = (int64_t)n_rhs * g.V <= kBwdBatchSites ? kBwdBatch : 1;
+  p.R = p.batch + 1;
+  for (int i = 0; i < p.R; ++i) p.slot[i] = c.take<double>(2 * fr);
   p.coef = c.take<double>((size_t)n_rhs * n_y * (D + 2));
   return p;
 }
@@ -1192,8 +1198,10 @@ rmh_status cheb_bwd(const Geom& g, const double* U, const double* x, int32_t n_r
   const double* coef_x = p.coef + (size_t)n_rhs * n_y * nk;
   const HopConfig cfg = hop_config(g, RMH_F64, n_rhs, RMH_PURPOSE_CHEB_BWD);
   const HopConfig cfg2 = hop_config(g, RMH_F64, 2 * n_rhs, RMH_PURPOSE_CHEB_BWD);
-  // nf fields (n_rhs, or 2 n_rhs for a B[i]-T[i] pair)
-  auto hopn = [&](const double* in, const double* z, double* out, double a, double c, int32_t nf) -> rmh_status {
+  // nf fields (n_rhs, or 2 n_rhs for a whole slot); k >= 0: plus the source G_k
+  auto hopn = [&](const double* in, const double* z, double* out, double a, double c, int32_t nf,
+                  int32_t k) -> rmh_status {
+    const HopConfig& hc = nf == n_rhs ? cfg : cfg2;
     HopArgs<double> h{};
     h.g = g;
     h.U = U;
@@ -1206,69 +1214,74 @@ rmh_status cheb_bwd(const Geom& g, const double* U, const double* x, int32_t n_r
     h.c = c;
     h.n_rhs = nf;
     h.store = 1;
-    ProfScope ps(RMH_PROF_STENCIL, hop_bytes(g, nf, 8, z != nullptr, true), s, nf);
-    HIP_TRY(launch_hop<double>(h, nf == n_rhs ? cfg : cfg2, s));
+    const bool fused = k >= 0 && z && hop_ring_ok(g, hc);
+    if (fused) {
+      h.src = Y;
+      h.src_coef = p.coef + k;
+      h.src_n = n_y;
+      h.src_rhs = n_rhs;
+      h.src_stride = nk;
+    }
+    {
+      ProfScope ps(RMH_PROF_STENCIL, hop_bytes(g, nf, 8, z != nullptr, true) + (fused ? 8.0 * n * n_rhs * n_y : 0.0), s,
+                   nf);
+      HIP_TRY(launch_hop<double>(h, hc, s));
+    }
+    if (k >= 0 && !fused) HIP_TRY(launch_cheb_source(out, Y, p.coef, n_rhs, n_y, nk, k, n, s));
     return RMH_OK;
   };
   auto hop = [&](const double* in, const double* z, double* out, double a, double c) -> rmh_status {
-    return hopn(in, z, out, a, c, n_rhs);
+    return hopn(in, z, out, a, c, n_rhs, -1);
   };
   const int64_t fr = n * n_rhs;
-  // forward: prv = t_{D-1}, cur = t_D
-  const double* prv = x;
-  double* cur = p.T[0];
-  RMH_TRY(hop(x, nullptr, cur, -0.125, 0.0));
+  const int32_t R = p.R;
+  auto slot = [&](int32_t j) { return p.slot[(j + 2 * R) % R]; };   // of step j >= -2
+  // forward: t_D into slot(-2), t_{D-1} into slot(-1) (t_0 = x itself is never written)
+  double* even = slot(D % 2 ? -1 : -2) + fr;   // of t_k, k even
+  double* odd = slot(D % 2 ? -2 : -1) + fr;
+  RMH_TRY(hop(x, nullptr, odd, -0.125, 0.0));
   for (int32_t k = 2; k <= D; ++k) {
-    double* out = (k == 2) ? p.T[1] : (double*)prv;   // t_{k-2}'s buffer (x itself is never written)
-    RMH_TRY(hop(cur, prv, out, -0.25, -1.0));
-    prv = cur;
-    cur = out;
+    double* out = k % 2 ? odd : even;
+    RMH_TRY(hop(k % 2 ? even : odd, k == 2 ? x : out, out, -0.25, -1.0));
   }
   // reverse
-  double* nb = p.B[D % 2];         // tb_{k+1}
-  double* nb2 = p.B[(D - 1) % 2];  // tb_{k+2}
-  HIP_TRY(launch_zero(nb, (size_t)n * n_rhs * 8, s));
-  HIP_TRY(launch_zero(nb2, (size_t)n * n_rhs * 8, s));
+  HIP_TRY(launch_zero(slot(-1), (size_t)fr * 8, s));
+  HIP_TRY(launch_zero(slot(0), (size_t)fr * 8, s));
+  ForceArgs fa{};
+  fa.g = g;
+  fa.U = U;
+  fa.rhs_stride = n;
+  fa.n_rhs = n_rhs;
+  fa.grad = grad_omega;
+  fa.per_rhs = per_rhs ? 1 : 0;
   for (int32_t k = D; k >= 1; --k) {
-    // tb_k into tb_{k+2}'s buffer (for k < D), t_{k-2} = 2A t_{k-1} - t_k into t_k's buffer (for
-    // k >= 3; t_{k-1} stays for the link term below): one launch over the pairs B[i]-T[i] when both
-    // run (tb_{D+1} is the zeroed buffer, so its z term adds nothing)
+    // tb_k for k < D (its source alone at k = D; tb_{D+1} is the zeroed half of slot(-1)), t_{k-2} for k >= 3
+    const int32_t j = D - k;
+    double *out = slot(j), *in = slot(j - 1), *z = slot(j - 2);
     const bool tb_hop = k < D, t_hop = k >= 3;
     if (tb_hop && t_hop) {
-      if (prv != nb + fr || cur != nb2 + fr) return fail(RMH_E_HOST, "Chebyshev backward: buffer pairing broken");
-      RMH_TRY(hopn(nb, nb2, nb2, -0.25, -1.0, 2 * n_rhs));
+      RMH_TRY(hopn(in, z, out, -0.25, -1.0, 2 * n_rhs, k));
     } else if (tb_hop) {
-      RMH_TRY(hop(nb, k + 1 < D ? nb2 : nullptr, nb2, -0.25, k + 1 < D ? -1.0 : 0.0));
-    } else if (t_hop) {
-      RMH_TRY(hop(prv, cur, cur, -0.25, -1.0));
+      RMH_TRY(hopn(in, k + 1 < D ? z : nullptr, out, -0.25, k + 1 < D ? -1.0 : 0.0, n_rhs, k));
+    } else {
+      if (t_hop) RMH_TRY(hop(in + fr, z + fr, out + fr, -0.25, -1.0));
+      HIP_TRY(launch_cheb_source(out, Y, p.coef, n_rhs, n_y, nk, k, n, s));
     }
-    HIP_TRY(launch_cheb_source(nb2, Y, p.coef, n_rhs, n_y, nk, k, n, s));
-    std::swap(nb, nb2);   // nb = tb_k, nb2 = tb_{k+1}
     if (grad_omega) {
-      ForceArgs fa{};
-      fa.g = g;
-      fa.U = U;
-      fa.A = nb;
-      fa.B = prv;     // t_{k-1}
-      fa.n_rhs = n_rhs;
-      fa.n_pair = 1;
-      fa.w[0] = (k == 1) ? 0.125 : 0.25;
-      fa.grad = grad_omega;
-      fa.per_rhs = per_rhs ? 1 : 0;
-      fa.accumulate = (k == D) ? 0 : 1;
-      const double fbytes = (double)g.V * 8.0 * (48.0 + 64.0 * n_rhs + 32.0 * (per_rhs ? n_rhs : 1) * (k == D ? 1.0 : 2.0));
-      ProfScope ps(RMH_PROF_FORCE, fbytes, s, n_rhs);
-      HIP_TRY(launch_force(fa, s));
-    }
-    if (k >= 3) {
-      const double* t_km2 = cur;
-      cur = (double*)prv;
-      prv = t_km2;
-    } else if (k == 2) {
-      cur = (double*)prv;   // t_0 is x itself
-      prv = x;
+      fa.A[fa.n_pair] = out;
+      fa.B[fa.n_pair] = k == 1 ? x : in + fr;     // t_{k-1}
+      fa.w[fa.n_pair] = (k == 1) ? 0.125 : 0.25;
+      if (++fa.n_pair == p.batch || k == 1) {
+        const double fbytes = (double)g.V * 8.0 * (48.0 + 64.0 * n_rhs * fa.n_pair +
+                                                   32.0 * (per_rhs ? n_rhs : 1) * (fa.accumulate ? 2.0 : 1.0));
+        ProfScope ps(RMH_PROF_FORCE, fbytes, s, n_rhs);
+        HIP_TRY(launch_force(fa, s));
+        fa.accumulate = 1;
+        fa.n_pair = 0;
+      }
     }
   }
+  const double *nb = slot(D - 1), *nb2 = slot(D - 2);   // tb_1, tb_2
   if (grad_x) {
     // tb_0 = G_0 + A tb_1 - tb_2, scaled by xscale (nb = tb_1, nb2 = tb_2, zero when D = 1)
     RMH_TRY(hop(nb, D >= 2 ? nb2 : nullptr, grad_x, -0.125 * xscale, D >= 2 ? -xscale : 0.0));
@@ -1613,8 +1626,9 @@ rmh_status rmh_laplacian_apply_bwd(const int32_t L[4], const void* U, int32_t dt
     ForceArgs fa{};
     fa.g = g;
     fa.U = (const double*)U;
-    fa.A = (const double*)g_;
-    fa.B = (const double*)x;
+    fa.A[0] = (const double*)g_;
+    fa.B[0] = (const double*)x;
+    fa.rhs_stride = field_reals(g);
     fa.n_rhs = n_rhs;
     fa.n_pair = 1;
     fa.w[0] = 1.0;
@@ -2006,11 +2020,14 @@ static rmh_status force_from_solves(RationalPlan& rp, const Geom& g, const doubl
   RMH_TRY(solve_all(rp.sp, U, gsrc, rp.Z, sig, *sv, s, res2));
   if (grad_x) HIP_TRY(launch_rational_combine(gsrc, rp.Z, n_rhs, np, rp.coef, grad_x, n, nullptr, s));
   ForceArgs fa{};
-  for (int j = 0; j < np; ++j) fa.w[j] = -rat->r[j];
+  for (int j = 0; j < np; ++j) {
+    fa.A[j] = rp.Z + j * n;
+    fa.B[j] = X + j * n;
+    fa.w[j] = -rat->r[j];
+  }
   fa.g = g;
   fa.U = U;
-  fa.A = rp.Z;
-  fa.B = X;
+  fa.rhs_stride = np * n;
   fa.n_rhs = n_rhs;
   fa.n_pair = np;
   fa.grad = grad_omega;
@@ -2147,11 +2164,14 @@ static rmh_status lf_velocity(LeapfrogPlan& lp, const Geom& g, const double* U, 
 static rmh_status lf_force_from_held(LeapfrogPlan& lp, const Geom& g, const double* U, const rmh_rational* rat,
                                      hipStream_t s) {
   ForceArgs fa{};
-  for (int j = 0; j < rat->n_poles; ++j) fa.w[j] = -rat->r[j];
+  for (int j = 0; j < rat->n_poles; ++j) {
+    fa.A[j] = lp.rp.Z + j * field_reals(g);
+    fa.B[j] = lp.rp.X + j * field_reals(g);
+    fa.w[j] = -rat->r[j];
+  }
   fa.g = g;
   fa.U = U;
-  fa.A = lp.rp.Z;
-  fa.B = lp.rp.X;
+  fa.rhs_stride = rat->n_poles * field_reals(g);
   fa.n_rhs = 1;
   fa.n_pair = rat->n_poles;
   fa.grad = lp.dK;

@@ -79,6 +79,11 @@ struct HopArgs {
   // CG's ring of T, ring_slots slots of 32 V reals per field
   const T* ring;            // (hop_ring_ok)
   int32_t ring_slots;
+  // optional, FP64 without dots (hop_ring_ok): out += sum_{y < src_n} src_coef[(v src_n + y) src_stride] src[y][v]
+  // for the fields v < src_rhs, src [src_n][src_rhs][4][8][V]
+  const T* src;
+  const double* src_coef;
+  int32_t src_n, src_rhs, src_stride;
 };
 
 // Tile of the tiled walk: R1 x R2 rows of x0 per block, n1 x n2 tiles per plane, K planes per walk.
@@ -97,7 +102,7 @@ int hop_split_ok(const HopConfig& cfg);
 int hop_walk_ok(const Geom& g, const HopConfig& cfg);
 // whether the multi-field shape applies (ns > 1 divides n_rhs, nv = 4, no walk, orders 0 and 1)
 int hop_ns_ok(const HopConfig& cfg, int32_t n_rhs);
-// whether the kernel of a configuration takes HopArgs::ring
+// whether the kernel of a configuration takes HopArgs::ring and HopArgs::src
 bool hop_ring_ok(const Geom& g, const HopConfig& cfg);
 // upper bound of hop_num_blocks over every configuration: 16 sites per block at least (the
 // hop-split shape with one direction group per block), plus one partial block per x3 slice of
@@ -258,10 +263,12 @@ hipError_t launch_add(double* x, const double* e, int64_t n, hipStream_t s);
 struct ForceArgs {
   Geom g;
   const double* U;
-  const double* A;   // [n_rhs][n_pair][4][8][V]
-  const double* B;   // same layout
+  // pair k of rhs r: A[k] + r rhs_stride, B[k] + r rhs_stride, each [4][8][V], with weight w[k]
+  const double* A[64];
+  const double* B[64];
+  double w[64];
+  int64_t rhs_stride;
   int32_t n_rhs, n_pair;
-  double w[64];      // weight of each pair
   double* grad;      // [n_out][4][8][V]
   int32_t per_rhs;
   int32_t accumulate;  // grad += (else grad =)

@@ -1002,56 +1002,103 @@ __device__ __forceinline__ void force_cross_cols(const double* u, const double* 
   for (int t = 0; t < 9; ++t) {
     const int a = kF[t].a, b = kF[t].b, c = kF[t].c;
     const double f = kF[t].f;
-    // (p x q)_c += f (p_a q_b - p_b q_a), cyclically in (a, b, c)
-    G[c] += f * ((c1[a] * C[b1 * 8 + b] - c1[b] * C[b1 * 8 + a]) + (c2[a] * C[b2 * 8 + b] - c2[b] * C[b2 * 8 + a]));
-    G[a] += f * ((c1[b] * C[b1 * 8 + c] - c1[c] * C[b1 * 8 + b]) + (c2[b] * C[b2 * 8 + c] - c2[c] * C[b2 * 8 + b]));
-    G[b] += f * ((c1[c] * C[b1 * 8 + a] - c1[a] * C[b1 * 8 + c]) + (c2[c] * C[b2 * 8 + a] - c2[a] * C[b2 * 8 + c]));
+    // (p x q)_c += f (p_a q_b - p_b q_a), cyclically in (a, b, c), both columns in one chain
+    const auto cross = [&](int i, int j) {
+      return fma(-c2[j], C[b2 * 8 + i],
+                 fma(c2[i], C[b2 * 8 + j], fma(-c1[j], C[b1 * 8 + i], c1[i] * C[b1 * 8 + j])));
+    };
+    G[c] = fma(f, cross(a, b), G[c]);
+    G[a] = fma(f, cross(b, c), G[a]);
+    G[b] = fma(f, cross(c, a), G[b]);
   }
 }
 
-// One thread per (site, mu): a block of 256 threads is four waves, wave w taking direction mu = w
-// for 64 consecutive sites, so every link and field base address is wave-uniform.
-__global__ void __launch_bounds__(256) k_force(const ForceArgs F, int32_t xcd) {
+// One thread per (site, mu): a block of 256 threads is four waves, wave w taking direction mu = w for the
+// block's 64 consecutive sites.  With every lane loading A and B at x and x+mu, 512 reals per site and pair,
+// the path from the caches to the registers (32 bytes per clock and CU) bounds it: 12 us a pair at 16^4 and 26
+// for the rest of the launch.  So the four waves load A and B at x once, a quarter each, into LDS, where a
+// neighbour inside the block is read too: at 16^4 208 reals per site and pair.  One step is one nu of one
+// pair; the loads of the next step are in flight during the 128 multiply-adds of this one (two steps ahead
+// they spill: four pairs in 133 us).  12 pairs 168 -> 111 us, four pairs of a reverse Chebyshev sweep 123 -> 71 us;
+// 12 pairs at 12^4 111 -> 82 us.  What is left is the latency of a step, two waves per SIMD.
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+k_force(const ForceArgs F, int32_t xcd) {
+  __shared__ double own[2][16][64];   // A and B at the block's sites, by turns
   const int32_t o = blockIdx.y;
   const int32_t V = F.g.V;
   const int32_t blk = remap_block(blockIdx.x, gridDim.x, xcd);
   const int32_t mu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int32_t s = blk * 64 + (threadIdx.x & 63);
-  if (s >= V) return;
-  const int64_t FV = 32 * (int64_t)V;
+  const int32_t lane = threadIdx.x & 63;
+  const bool live = blk * 64 + lane < V;
+  const int32_t s = live ? blk * 64 + lane : blk * 64;   // lanes past the end go along with the first site
   int32_t xc[4];
   site_coords(F.g, s, xc);
   const int32_t r0 = F.per_rhs ? o : 0;
-  const int32_t r1 = F.per_rhs ? o + 1 : F.n_rhs;
+  const int32_t nr = F.per_rhs ? 1 : F.n_rhs;
   {
     const int32_t sf = site_shift(F.g, s, xc, mu, +1);
+    const int32_t d = sf - blk * 64;
+    const bool near = d >= 0 && d < 64;
+    const uint32_t os = byte_off<double>(s), of = byte_off<double>(sf);
     double C[64];
 #pragma unroll
     for (int i = 0; i < 64; ++i) C[i] = 0.0;
-#pragma unroll 1
-    for (int32_t rh = r0; rh < r1; ++rh)
-#pragma unroll 1
-      for (int32_t k = 0; k < F.n_pair; ++k) {
-        const double w = F.w[k];
-        const double* Ak = F.A + ((int64_t)rh * F.n_pair + k) * FV;
-        const double* Bk = F.B + ((int64_t)rh * F.n_pair + k) * FV;
-#pragma unroll 1
-        for (int nu = 0; nu < 4; ++nu) {
-          double ax[8], bx[8], af[8], bf[8];
+    const int32_t steps = nr * F.n_pair * 4;
+    // the step whose loads go out next
+    int32_t rh = r0, k = 0, nu = 0;
+    double q[4], fa[8], fb[8];
+    auto load = [&]() {
+      const int64_t off = rh * F.rhs_stride + (int64_t)nu * 8 * V;
+      const double* Ak = F.A[k] + off;
+      const double* Bk = F.B[k] + off;
+      Rows<double> qr((mu < 2 ? Ak : Bk) + (int64_t)((mu & 1) * 4) * V, V, os);
 #pragma unroll
-          for (int a = 0; a < 8; ++a) {
-            const int64_t e = (int64_t)(nu * 8 + a) * V;
-            ax[a] = w * Ak[e + s];
-            bx[a] = w * Bk[e + s];
-            af[a] = Ak[e + sf];
-            bf[a] = Bk[e + sf];
-          }
+      for (int a = 0; a < 4; ++a) q[a] = qr.get();
+      if (!near) {
+        Rows<double> ar(Ak, V, of), br(Bk, V, of);
 #pragma unroll
-          for (int b = 0; b < 8; ++b)
+        for (int a = 0; a < 8; ++a) fa[a] = ar.get();
 #pragma unroll
-            for (int e = 0; e < 8; ++e) C[b * 8 + e] = fma(af[b], bx[e], fma(bf[b], ax[e], C[b * 8 + e]));
+        for (int a = 0; a < 8; ++a) fb[a] = br.get();
+      }
+      if (++nu == 4) {
+        nu = 0;
+        if (++k == F.n_pair) {
+          k = 0;
+          ++rh;
         }
       }
+    };
+    if (steps > 0) load();
+#pragma unroll 1
+    for (int32_t t = 0; t < steps; ++t) {
+      double(*buf)[64] = own[t & 1];
+      const double w = F.w[(t >> 2) % F.n_pair];
+#pragma unroll
+      for (int a = 0; a < 4; ++a) buf[mu * 4 + a][lane] = q[a];
+      double af[8], bf[8];
+#pragma unroll
+      for (int a = 0; a < 8; ++a) {
+        af[a] = fa[a];
+        bf[a] = fb[a];
+      }
+      __syncthreads();
+      if (t + 1 < steps) load();
+      if (near) {
+#pragma unroll
+        for (int a = 0; a < 8; ++a) {
+          af[a] = buf[a][d];
+          bf[a] = buf[8 + a][d];
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const double ax = w * buf[e][lane], bx = w * buf[8 + e][lane];
+#pragma unroll
+        for (int b = 0; b < 8; ++b) C[b * 8 + e] = fma(af[b], bx, fma(bf[b], ax, C[b * 8 + e]));
+      }
+    }
+    if (!live) return;
     // rows 0 and 1 of U_mu(x) (12 reals), row 2 rebuilt (SU(3))
     double u[18];
     const double* Um = F.U + (int64_t)mu * 18 * V;

@@ -75,39 +75,6 @@ __device__ __forceinline__ void hop_finish(T (*acc)[8]) {
   }
 }
 
-// The rows (components) of an array at one site per lane: row r at base + r * V, with the base address
-// the same for the whole wave, in scalar registers, and an unsigned 32-bit byte offset per lane (at
-// most 2^28 sites of 8 bytes) that the load instruction adds by itself.  The empty asm keeps the base
-// scalar and stepped from row to row: left alone, the compiler computes every row's address as a
-// 64-bit vector add, a quarter of the vector instructions of a hop.  With the 3x3 form's shorter
-// arithmetic (mat_hop) this took FP64 at 32^3x64 from 644 to 569 us per application, FP32 at 24^4 (4 fields)
-// from 211 to 195 us; the streamed form alone, at equal arithmetic, gains 1-7 %.
-template <typename T>
-using Global = __attribute__((address_space(1))) T;
-template <typename T>
-__device__ __forceinline__ uint32_t byte_off(int32_t s) {
-  return (uint32_t)s * (uint32_t)sizeof(T);
-}
-template <typename T>
-struct Rows {
-  uint64_t b, stride;
-  uint32_t o;
-  __device__ __forceinline__ Rows(const T* base, int64_t V, uint32_t byte_offset)
-      : b((uint64_t)base), stride((uint64_t)V * sizeof(T)), o(byte_offset) {
-    asm volatile("" : "+s"(b), "+v"(o));
-  }
-  __device__ __forceinline__ Global<T>* ptr() const { return (Global<T>*)((Global<char>*)b + o); }
-  __device__ __forceinline__ T get() {
-    const T x = *ptr();
-    next();
-    return x;
-  }
-  __device__ __forceinline__ void next() {
-    b += stride;
-    asm("" : "+s"(b));
-  }
-};
-
 // Row 2 from rows 0 and 1 in the rounding the form uses (su3_row2).
 template <typename T, int FORM>
 __device__ __forceinline__ void link_row2(T* u) {
@@ -159,7 +126,7 @@ __device__ __forceinline__ const T* hop_ring_field(const HopArgs<T>& A, int32_t 
 
 // The epilogue at one site: out = a h + b x + c z for NV directions from nu0 on, and the partial dot
 // products.  kLoadX: x is read back from the field, else it is handed over in xc.  kRing: the kernel takes
-// HopArgs::ring (the walk has no registers left for it).  Per direction the
+// HopArgs::ring and HopArgs::src (the walk has no registers left for them).  Per direction the
 // loads of x and z come before the stores (z may be the output itself, each element read and
 // written by this thread only), so they overlap.
 template <typename T, int NV, bool DOTS, bool kLoadX, bool kRing>
@@ -205,6 +172,19 @@ __device__ __forceinline__ void hop_store(const HopArgs<T>& A, int32_t v, const 
     if (zf) {
 #pragma unroll
       for (int a = 0; a < 8; ++a) w[a] = fmadd(cc, zv[a], w[a]);
+    }
+    if constexpr (!DOTS && kRing && sizeof(T) == 8) {
+      if (A.src && v < A.src_rhs) {
+        for (int32_t y = 0; y < A.src_n; ++y) {
+          const double c = A.src_coef[((int64_t)v * A.src_n + y) * A.src_stride];
+          Rows<T> yr(A.src + ((int64_t)y * A.src_rhs + v) * FV + r0, V, byte_off<T>(s));
+          T yv[8];
+#pragma unroll
+          for (int a = 0; a < 8; ++a) yv[a] = yr.get();
+#pragma unroll
+          for (int a = 0; a < 8; ++a) w[a] = fma(c, yv[a], w[a]);
+        }
+      }
     }
     if (DOTS) {
 #pragma unroll
@@ -406,6 +386,12 @@ __global__ void __launch_bounds__(256) k_hop_split(const HopArgs<T> A, int32_t x
       const T xv = xs[q];
       T o = fmadd(ca, h, cb * xv);
       if (zf) o = fmadd(cc, zv[q], o);
+      if constexpr (!DOTS && sizeof(T) == 8) {
+        if (A.src && v < A.src_rhs)
+          for (int32_t y = 0; y < A.src_n; ++y)
+            o = fma(A.src_coef[((int64_t)v * A.src_n + y) * A.src_stride],
+                    A.src[((int64_t)y * A.src_rhs + v) * FV + e], o);
+      }
       if (A.store) __builtin_nontemporal_store(o, &outf[e]);
       if (DOTS) {
         const double xd = (double)xv, od = (double)o;
@@ -963,6 +949,17 @@ k_hop_tile(const HopArgs<T> A, const HopTile S, int32_t xcd) {
         dsum[2] = fma(od, od, dsum[2]);
       }
     }
+    if constexpr (!DOTS && Z && sizeof(T) == 8) {
+      if (A.src && v < A.src_rhs) {
+        for (int32_t y = 0; y < A.src_n; ++y) {
+          const double c = A.src_coef[((int64_t)v * A.src_n + y) * A.src_stride];
+          T yv[2][8];
+          get_half(A.src + ((int64_t)y * A.src_rhs + v) * FV, V, hf + gc + pl, yv);
+#pragma unroll
+          for (int i = 0; i < 16; ++i) w[i >> 3][i & 7] = fma(c, yv[i >> 3][i & 7], w[i >> 3][i & 7]);
+        }
+      }
+    }
     if (A.store && live) {
       Rows<T> outr(outf, V, hf + gc + pl);
 #pragma unroll
@@ -1164,6 +1161,7 @@ template <typename T>
 hipError_t launch_hop(const HopArgs<T>& A, const HopConfig& cfg, hipStream_t s) {
   if (A.n_rhs == 0 || A.g.V == 0) return hipSuccess;
   if (A.ring && (A.z || !A.run || A.ring_slots < 1 || !hop_ring_ok(A.g, cfg))) return hipErrorInvalidValue;
+  if (A.src && (sizeof(T) != 8 || A.dot_mask || !A.z || !hop_ring_ok(A.g, cfg))) return hipErrorInvalidValue;
   if (cfg.form == kFormMatrix) return launch_hop_nv<T, kFormMatrix>(A, cfg, s);
   if (cfg.form == kFormAdjoint) return launch_hop_nv<T, kFormAdjoint>(A, cfg, s);
   return launch_hop_nv<T, kFormStream>(A, cfg, s);

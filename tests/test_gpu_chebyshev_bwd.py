@@ -2,6 +2,8 @@
 bandpass filters) against the oracle's dense spectral derivative, and properties that hold at any
 size: the filter's adjoint identity, grad_F = 2 sum_w gamma_w B_w F, and central finite
 differences of the GPU's own forward calls."""
+import functools
+
 import numpy as np
 import pytest
 import torch
@@ -178,3 +180,57 @@ def test_gradcheck_power_spectrum_displaced_links():
     Fg = Fd.clone().requires_grad_(True)
     assert torch.autograd.gradcheck(lambda w, f: torch.sum(autograd.power_spectrum(w, f, Ud, L, 8, 3) * gamma),
                                     (omega, Fg), eps=1e-6, atol=1e-7, rtol=1e-6)
+
+
+# form, block, nv, order, walk, ns, tile2: the hop-split, one-launch-per-site, two-field and tiled-walk stencils, which
+# add the source G_k themselves, and the walk, which leaves it to a launch of its own
+SHAPES = [(1, 256, 2, 2, 0, 1, 1), (1, 128, 2, 0, 0, 1, 1), (2, 64, 4, 0, 0, 2, 1), (1, 128, 2, 1, 2, 1, 2),
+          (1, 64, 4, 1, 2, 1, 1)]
+
+
+@functools.lru_cache
+def _filter_case(L, D, nw):
+    """Inputs and oracle derivatives, once for all shapes (the oracle is dense)."""
+    U, F, Ud, Fd = setup(L, "eps", 0.6, 60 + D, n=2)
+    gy = np.random.default_rng(60 + D).normal(size=(nw,) + F.shape)
+    return Ud, Fd, torch.from_numpy(gy).to(dev()), ocg.cheb_filter_vjp(U, F, gy, L, D, och.equal_windows(nw),
+                                                                       per_rhs=True)
+
+
+@pytest.mark.parametrize("D", [6, 9])
+@pytest.mark.parametrize("shape", SHAPES, ids=["split", "site", "fields", "tile", "walk"])
+def test_bwd_shapes(shape, D):
+    """Link terms in batches of four that the degree fills (with the last pair of its own) and does not, under
+    each stencil: filter derivatives for two fields and three windows against the oracle."""
+    L, nw = (4, 3, 2, 4), 3
+    announce(f"chebyshev bwd shape {shape} degree {D}")
+    Ud, Fd, gy, (rgx, rgo) = _filter_case(L, D, nw)
+    edges = och.equal_windows(nw)
+    form, block, nv, order, walk, ns, tile2 = shape
+    try:
+        for n in (2, 4):
+            api.tune_set(L, torch.float64, n, form, block, 1, nv, order, walk, ns, "any", tile2)
+        gx, go = api.cheb_filter_bwd(L, Ud, Fd, gy, D, nw, edges, per_rhs=True)
+        _, gs = api.cheb_filter_bwd(L, Ud, Fd, gy, D, nw, edges, grad_x=False)
+    finally:
+        api.tune_clear()
+    assert rel_max(gx.cpu().numpy(), rgx) <= 1e-12
+    assert rel_max(go.cpu().numpy(), rgo) <= 1e-12
+    assert rel_max(gs[0].cpu().numpy(), rgo.sum(axis=0)) <= 1e-12
+
+
+def test_bwd_many_fields():
+    """More fields than the batched link terms are used for (n V > 2^20): the gradients of the first and the
+    last field against calls with those fields alone."""
+    L = (8, 8, 8, 8)
+    n, D, nw = 260, 6, 2
+    announce("chebyshev bwd many fields")
+    _, _, Ud, F1 = setup(L, "eps", 0.5, 71, n=2)
+    Fd = F1[:1].repeat(n, 1, 1, 1)
+    Fd[-1] = F1[1]
+    gamma = np.random.default_rng(71).normal(size=(n, nw))
+    gF, go = api.power_spectrum_bwd(L, Ud, Fd, gamma, D, nw, per_rhs=True)
+    for i in (0, n - 1):
+        hF, ho = api.power_spectrum_bwd(L, Ud, Fd[i:i + 1].contiguous(), gamma[i:i + 1], D, nw, per_rhs=True)
+        assert rel_max(gF[i].cpu().numpy(), hF[0].cpu().numpy()) <= 1e-12
+        assert rel_max(go[i].cpu().numpy(), ho[0].cpu().numpy()) <= 1e-12
