@@ -1157,29 +1157,22 @@ rmh_status cheb_filter_t(const Geom& g, const T* U, const T* x, int32_t n_rhs, i
 //   dL/d omega = (1/8) <tb_1, dDelta t_0> + (1/4) sum_{k=2..D} <tb_k, dDelta t_{k-1}>,
 //   dL/dx      = tb_0 = G_0 + A tb_1 - tb_2  (through the recursion only).
 // t_D, t_{D-1} come from a forward sweep; the reverse sweep then runs the recursion backwards,
-// t_{k-2} = 2A t_{k-1} - t_k, so only a few t and tb vectors are held.  2A = -H/4.
-// Reverse step j = D - k writes slot j % R, {tb_k, t_{k-2}} one after the other in memory, from the two slots
-// before it, {tb_{k+1}, t_{k-1}} and {tb_{k+2}, t_k}: one launch over 2 n_rhs fields, the source G_k added to the
-// first n_rhs of them.  The link term of step k pairs tb_k with t_{k-1} of the slot before; `batch` steps go into
-// one launch, since its 8 x 8 products with R(U) and the update of the gradient cost as much as two pairs
-// (16^4: 26 us and 12 per pair; 64 steps one by one 2.42 ms, by four @F@): R = batch + 1 slots, or with batch = 1 two,
-// the slot of step j - 2 overwritten in place.
-constexpr int kBwdBatch = 4;
-// Batches while the slots stay small (10 fields of 256 MiB); past that memory goes first.
-constexpr int64_t kBwdBatchSites = 1 << 20;
-
+// t_{k-1} = 2A t_k - t_{k+1}, so only two t and two tb vectors are held.  2A = -H/4.
+// tb_k and t_{k-1} lie one after the other in slot (D - k) % 2: a reverse step writes them over {tb_{k+2}, t_{k+1}}
+// from {tb_{k+1}, t_k} in one launch over 2 n_rhs fields, the source G_k added to the first n_rhs of them.  The link
+// term of step k pairs the two halves of its slot, so the two slots together hold two steps' terms, and these
+// go out in one launch: the products with R(U), the update of the gradient and the start of the launch cost
+// more than a pair (16^4, degree 64: steps one by one 2.42 ms before that kernel was
+// rewritten, two by two 1.37 ms; four by four on five slots 1.14 ms, for two and a half times the workspace).
 struct ChebBwdPlan {
-  int32_t batch, R;
-  double* slot[kBwdBatch + 1];   // tb, then t
+  double* slot[2];   // tb, then t
   double* coef;   // [n_rhs][n_y][D+1], then [n_rhs][n_y] scaled k = 0 coefficients
 };
 
 ChebBwdPlan plan_cheb_bwd(Carver& c, const Geom& g, int32_t n_rhs, int32_t n_y, int32_t D) {
   ChebBwdPlan p{};
   const size_t fr = (size_t)n_rhs * 32 * g.V;
-  p.batch = (int64_t)n_rhs * g.V <= kBwdBatchSites ? kBwdBatch : 1;
-  p.R = p.batch + 1;
-  for (int i = 0; i < p.R; ++i) p.slot[i] = c.take<double>(2 * fr);
+  for (int i = 0; i < 2; ++i) p.slot[i] = c.take<double>(2 * fr);
   p.coef = c.take<double>((size_t)n_rhs * n_y * (D + 2));
   return p;
 }
@@ -1234,19 +1227,14 @@ rmh_status cheb_bwd(const Geom& g, const double* U, const double* x, int32_t n_r
     return hopn(in, z, out, a, c, n_rhs, -1);
   };
   const int64_t fr = n * n_rhs;
-  const int32_t R = p.R;
-  auto slot = [&](int32_t j) { return p.slot[(j + 2 * R) % R]; };   // of step j >= -2
-  // forward: t_D into slot(-2), t_{D-1} into slot(-1) (t_0 = x itself is never written)
-  double* even = slot(D % 2 ? -1 : -2) + fr;   // of t_k, k even
-  double* odd = slot(D % 2 ? -2 : -1) + fr;
-  RMH_TRY(hop(x, nullptr, odd, -0.125, 0.0));
-  for (int32_t k = 2; k <= D; ++k) {
-    double* out = k % 2 ? odd : even;
-    RMH_TRY(hop(k % 2 ? even : odd, k == 2 ? x : out, out, -0.25, -1.0));
-  }
+  auto slot = [&](int32_t k) { return p.slot[(D - k) & 1]; };   // of {tb_k, t_{k-1}}
+  // forward: t_k where the reverse sweep has it for k = D, D - 1 (t_0 = x itself is never written)
+  RMH_TRY(hop(x, nullptr, slot(2) + fr, -0.125, 0.0));
+  for (int32_t k = 2; k <= D; ++k)
+    RMH_TRY(hop(slot(k) + fr, k == 2 ? x : slot(k + 1) + fr, slot(k + 1) + fr, -0.25, -1.0));
   // reverse
-  HIP_TRY(launch_zero(slot(-1), (size_t)fr * 8, s));
-  HIP_TRY(launch_zero(slot(0), (size_t)fr * 8, s));
+  HIP_TRY(launch_zero(slot(D + 1), (size_t)fr * 8, s));
+  HIP_TRY(launch_zero(slot(D), (size_t)fr * 8, s));
   ForceArgs fa{};
   fa.g = g;
   fa.U = U;
@@ -1255,23 +1243,17 @@ rmh_status cheb_bwd(const Geom& g, const double* U, const double* x, int32_t n_r
   fa.grad = grad_omega;
   fa.per_rhs = per_rhs ? 1 : 0;
   for (int32_t k = D; k >= 1; --k) {
-    // tb_k for k < D (its source alone at k = D; tb_{D+1} is the zeroed half of slot(-1)), t_{k-2} for k >= 3
-    const int32_t j = D - k;
-    double *out = slot(j), *in = slot(j - 1), *z = slot(j - 2);
-    const bool tb_hop = k < D, t_hop = k >= 3;
-    if (tb_hop && t_hop) {
-      RMH_TRY(hopn(in, z, out, -0.25, -1.0, 2 * n_rhs, k));
-    } else if (tb_hop) {
-      RMH_TRY(hopn(in, k + 1 < D ? z : nullptr, out, -0.25, k + 1 < D ? -1.0 : 0.0, n_rhs, k));
-    } else {
-      if (t_hop) RMH_TRY(hop(in + fr, z + fr, out + fr, -0.25, -1.0));
+    // tb_k = G_k at k = D (tb_{D+1} = 0 in its slot); t_{k-1} is there at k = D and x at k = 1
+    double *out = slot(k), *in = slot(k + 1);
+    if (k == D)
       HIP_TRY(launch_cheb_source(out, Y, p.coef, n_rhs, n_y, nk, k, n, s));
-    }
+    else
+      RMH_TRY(hopn(in, out, out, -0.25, -1.0, k >= 2 ? 2 * n_rhs : n_rhs, k));
     if (grad_omega) {
       fa.A[fa.n_pair] = out;
-      fa.B[fa.n_pair] = k == 1 ? x : in + fr;     // t_{k-1}
+      fa.B[fa.n_pair] = k == 1 ? x : out + fr;
       fa.w[fa.n_pair] = (k == 1) ? 0.125 : 0.25;
-      if (++fa.n_pair == p.batch || k == 1) {
+      if (++fa.n_pair == 2 || k == 1) {
         const double fbytes = (double)g.V * 8.0 * (48.0 + 64.0 * n_rhs * fa.n_pair +
                                                    32.0 * (per_rhs ? n_rhs : 1) * (fa.accumulate ? 2.0 : 1.0));
         ProfScope ps(RMH_PROF_FORCE, fbytes, s, n_rhs);
@@ -1281,7 +1263,7 @@ rmh_status cheb_bwd(const Geom& g, const double* U, const double* x, int32_t n_r
       }
     }
   }
-  const double *nb = slot(D - 1), *nb2 = slot(D - 2);   // tb_1, tb_2
+  const double *nb = slot(1), *nb2 = slot(2);   // tb_1, tb_2
   if (grad_x) {
     // tb_0 = G_0 + A tb_1 - tb_2, scaled by xscale (nb = tb_1, nb2 = tb_2, zero when D = 1)
     RMH_TRY(hop(nb, D >= 2 ? nb2 : nullptr, grad_x, -0.125 * xscale, D >= 2 ? -xscale : 0.0));

@@ -200,8 +200,7 @@ def _filter_case(L, D, nw):
 @pytest.mark.parametrize("D", [6, 9])
 @pytest.mark.parametrize("shape", SHAPES, ids=["split", "site", "fields", "tile", "walk"])
 def test_bwd_shapes(shape, D):
-    """Link terms in batches of four that the degree fills (with the last pair of its own) and does not, under
-    each stencil: filter derivatives for two fields and three windows against the oracle."""
+    """Link terms two by two, with the last one alone in odd degrees, under each stencil: filter derivatives for two fields and three windows against the oracle."""
     L, nw = (4, 3, 2, 4), 3
     announce(f"chebyshev bwd shape {shape} degree {D}")
     Ud, Fd, gy, (rgx, rgo) = _filter_case(L, D, nw)
@@ -217,20 +216,3 @@ def test_bwd_shapes(shape, D):
     assert rel_max(gx.cpu().numpy(), rgx) <= 1e-12
     assert rel_max(go.cpu().numpy(), rgo) <= 1e-12
     assert rel_max(gs[0].cpu().numpy(), rgo.sum(axis=0)) <= 1e-12
-
-
-def test_bwd_many_fields():
-    """More fields than the batched link terms are used for (n V > 2^20): the gradients of the first and the
-    last field against calls with those fields alone."""
-    L = (8, 8, 8, 8)
-    n, D, nw = 260, 6, 2
-    announce("chebyshev bwd many fields")
-    _, _, Ud, F1 = setup(L, "eps", 0.5, 71, n=2)
-    Fd = F1[:1].repeat(n, 1, 1, 1)
-    Fd[-1] = F1[1]
-    gamma = np.random.default_rng(71).normal(size=(n, nw))
-    gF, go = api.power_spectrum_bwd(L, Ud, Fd, gamma, D, nw, per_rhs=True)
-    for i in (0, n - 1):
-        hF, ho = api.power_spectrum_bwd(L, Ud, Fd[i:i + 1].contiguous(), gamma[i:i + 1], D, nw, per_rhs=True)
-        assert rel_max(gF[i].cpu().numpy(), hF[0].cpu().numpy()) <= 1e-12
-        assert rel_max(go[i].cpu().numpy(), ho[0].cpu().numpy()) <= 1e-12
