@@ -562,7 +562,7 @@ rmh_status engine_solve(Engine& e, const double* U64, const float* U32, const do
   // one launch for the update where the stencil's kernel takes <r, Ap>; the walk over all directions would
   // spill for it (16^4, eight FP32 fields: stencil 107 us and update 91, against 88 and two updates of 42
   // and 59: on vectors past the caches the second pass costs little more than <r, Ap>'s)
-  const bool one64 = hop_ring_ok(g, c64), one32 = hop_ring_ok(g, c32);
+  const bool one64 = hop_ring_ok(g, c64, 8), one32 = hop_ring_ok(g, c32, 4);
   h64.dot_mask = one64 ? 7 : 2;
   h64.ring = one64 ? e.ring : nullptr;
   h64.ring_slots = e.nslot;
@@ -1207,7 +1207,7 @@ rmh_status cheb_bwd(const Geom& g, const double* U, const double* x, int32_t n_r
     h.c = c;
     h.n_rhs = nf;
     h.store = 1;
-    const bool fused = k >= 0 && z && hop_ring_ok(g, hc);
+    const bool fused = k >= 0 && z && hop_ring_ok(g, hc, 8);
     if (fused) {
       h.src = Y;
       h.src_coef = p.coef + k;

@@ -103,7 +103,7 @@ int hop_walk_ok(const Geom& g, const HopConfig& cfg);
 // whether the multi-field shape applies (ns > 1 divides n_rhs, nv = 4, no walk, orders 0 and 1)
 int hop_ns_ok(const HopConfig& cfg, int32_t n_rhs);
 // whether the kernel of a configuration takes HopArgs::ring and HopArgs::src
-bool hop_ring_ok(const Geom& g, const HopConfig& cfg);
+bool hop_ring_ok(const Geom& g, const HopConfig& cfg, int bytes);
 // upper bound of hop_num_blocks over every configuration: 16 sites per block at least (the
 // hop-split shape with one direction group per block), plus one partial block per x3 slice of
 // the walking shape; every per-block partial-sum buffer is sized with it

@@ -43,8 +43,8 @@ __device__ __forceinline__ double wave_sum(double v) {
   return add_dpp<0xb1>(v); // quad_perm [1, 0, 3, 2]
 }
 
-// Sum of the waves' values in order; all reads in flight together (one after the other they cost an LDS
-// latency per wave).
+// Sum of the waves' values in order; up to four with their reads in flight together (one after the other they
+// cost an LDS latency per wave).
 __device__ __forceinline__ double waves_sum(const double* w) {
   const int nw = (blockDim.x + 63) >> 6;
   double s = 0.0;
@@ -55,11 +55,7 @@ __device__ __forceinline__ double waves_sum(const double* w) {
       s = i < nw ? s + t : s;
     }
   } else {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const double t = w[i];
-      s = i < nw ? s + t : s;
-    }
+    for (int i = 0; i < nw; ++i) s += w[i];
   }
   return s;
 }

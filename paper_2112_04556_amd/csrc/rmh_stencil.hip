@@ -105,14 +105,22 @@ __device__ __forceinline__ void load_rows(const T* __restrict__ Um, int32_t s, i
   for (int c = 0; c < 12; ++c) u[c] = r.get();
 }
 
-// Directions nu0 .. nu0 + NV - 1 of the field at site s.
-template <typename T, int NV>
+// Directions nu0 .. nu0 + NV - 1 of the field at site s.  kScalar false: addressed per lane (the streamed form
+// of the hop split: scalar rows made it 1 % slower, FP32 moments at 13x16x10x11, four fields).
+template <typename T, int NV, bool kScalar = true>
 __device__ __forceinline__ void load_field(const T* __restrict__ xf, int32_t s, int nu0, int32_t V, T (*f)[8]) {
-  Rows<T> r(xf + (size_t)(nu0 * 8) * V, V, byte_off<T>(s));
+  if (kScalar) {
+    Rows<T> r(xf + (size_t)(nu0 * 8) * V, V, byte_off<T>(s));
 #pragma unroll
-  for (int i = 0; i < NV; ++i)
+    for (int i = 0; i < NV; ++i)
 #pragma unroll
-    for (int b = 0; b < 8; ++b) f[i][b] = r.get();
+      for (int b = 0; b < 8; ++b) f[i][b] = r.get();
+  } else {
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+#pragma unroll
+      for (int b = 0; b < 8; ++b) f[i][b] = (xf + (size_t)((nu0 + i) * 8 + b) * V)[s];
+  }
 }
 
 // The current residual of field v in the CG's ring (HopArgs::ring), of which dot 0 is taken.
@@ -222,7 +230,7 @@ __device__ __forceinline__ void hop_term(const T* __restrict__ Um, int32_t sb, c
                                          int nu0, int32_t V, T (&acc)[NV][8]) {
   T u[18], phi[NV][8];
   load_link<T, FORM, kUni>(Um, sb, V, u);
-  load_field<T, NV>(xf, sb, nu0, V, phi);
+  load_field<T, NV, kUni || FORM == kFormMatrix>(xf, sb, nu0, V, phi);
   hop_apply<T, FORM, NV, kT>(u, phi, acc);
 }
 
@@ -233,7 +241,7 @@ __device__ __forceinline__ void hop_term_fwd(const T* __restrict__ Um, int32_t s
                                              T (&acc)[NV][8]) {
   T u[18], phi[NV][8];
   load_link<T, FORM, kUni>(Um, s, V, u);
-  load_field<T, NV>(xf, sf, nu0, V, phi);
+  load_field<T, NV, kUni || FORM == kFormMatrix>(xf, sf, nu0, V, phi);
   hop_apply<T, FORM, NV, false>(u, phi, acc);
 }
 
@@ -364,7 +372,8 @@ __global__ void __launch_bounds__(256) k_hop_split(const HopArgs<T> A, int32_t x
     const T cc = T(A.c);
     const T* zf = A.z ? A.z + (int64_t)(v / A.z_div) * FV : nullptr;  // may alias out
     T* outf = A.out + (int64_t)v * FV;
-    const T* rf = DOTS ? hop_ring_field(A, v) : nullptr;   // z is null with it
+    constexpr bool kRing = sizeof(T) == 8 || FORM == kFormMatrix;   // the FP32 moments' form does without
+    const T* rf = DOTS && kRing ? hop_ring_field(A, v) : nullptr;   // z is null with it
     using Bits = typename std::conditional<sizeof(T) == 8, uint64_t, uint32_t>::type;
     const Bits m0 = mu == 0 ? ~Bits(0) : Bits(0), m1 = mu == 1 ? ~Bits(0) : Bits(0);
     const Bits m2 = mu == 2 ? ~Bits(0) : Bits(0), m3 = mu == 3 ? ~Bits(0) : Bits(0);
@@ -377,7 +386,11 @@ __global__ void __launch_bounds__(256) k_hop_split(const HopArgs<T> A, int32_t x
       hs[q] = __builtin_bit_cast(T, hb_);
       const int64_t e = (int64_t)(nu0 * 8 + 4 * q + mu) * V + s;
       xs[q] = xf[e];
-      zv[q] = rf ? rf[e] : !zf ? T(0) : A.z_div == 1 ? __builtin_nontemporal_load(&zf[e]) : zf[e];
+      zv[q] = !zf ? T(0) : A.z_div == 1 ? __builtin_nontemporal_load(&zf[e]) : zf[e];
+    }
+    if (kRing && rf) {
+#pragma unroll
+      for (int q = 0; q < 2 * NV; ++q) zv[q] = rf[(int64_t)(nu0 * 8 + 4 * q + mu) * V + s];
     }
 #pragma unroll
     for (int q = 0; q < 2 * NV; ++q) {
@@ -395,7 +408,8 @@ __global__ void __launch_bounds__(256) k_hop_split(const HopArgs<T> A, int32_t x
       if (A.store) __builtin_nontemporal_store(o, &outf[e]);
       if (DOTS) {
         const double xd = (double)xv, od = (double)o;
-        dsum[0] = rf ? fma(od, (double)zv[q], dsum[0]) : fma(xd, xd, dsum[0]);
+        const double rd = kRing && rf ? (double)zv[q] : xd;
+        dsum[0] = fma(kRing && rf ? od : xd, rd, dsum[0]);
         dsum[1] = fma(od, xd, dsum[1]);
         dsum[2] = fma(od, od, dsum[2]);
       }
@@ -1053,9 +1067,11 @@ int hop_split_ok(const HopConfig& cfg) {
 }
 static int hop_split_spb(const HopConfig& cfg) { return (cfg.block / 64) / (4 / cfg.nv) * 16; }
 
-bool hop_ring_ok(const Geom& g, const HopConfig& cfg) {
+bool hop_ring_ok(const Geom& g, const HopConfig& cfg, int bytes) {
   HopTile tile;
-  return hop_tile_of(g, cfg, &tile) || hop_split_ok(cfg) || !hop_walk_ok(g, cfg);
+  if (hop_tile_of(g, cfg, &tile)) return true;
+  if (hop_split_ok(cfg)) return bytes == 8 || cfg.form == kFormMatrix;
+  return !hop_walk_ok(g, cfg);
 }
 
 int hop_num_blocks(const Geom& g, const HopConfig& cfg) {
@@ -1160,8 +1176,8 @@ static hipError_t launch_hop_nv(const HopArgs<T>& A, const HopConfig& cfg, hipSt
 template <typename T>
 hipError_t launch_hop(const HopArgs<T>& A, const HopConfig& cfg, hipStream_t s) {
   if (A.n_rhs == 0 || A.g.V == 0) return hipSuccess;
-  if (A.ring && (A.z || !A.run || A.ring_slots < 1 || !hop_ring_ok(A.g, cfg))) return hipErrorInvalidValue;
-  if (A.src && (sizeof(T) != 8 || A.dot_mask || !A.z || !hop_ring_ok(A.g, cfg))) return hipErrorInvalidValue;
+  if (A.ring && (A.z || !A.run || A.ring_slots < 1 || !hop_ring_ok(A.g, cfg, sizeof(T)))) return hipErrorInvalidValue;
+  if (A.src && (sizeof(T) != 8 || A.dot_mask || !A.z || !hop_ring_ok(A.g, cfg, sizeof(T)))) return hipErrorInvalidValue;
   if (cfg.form == kFormMatrix) return launch_hop_nv<T, kFormMatrix>(A, cfg, s);
   if (cfg.form == kFormAdjoint) return launch_hop_nv<T, kFormAdjoint>(A, cfg, s);
   return launch_hop_nv<T, kFormStream>(A, cfg, s);
