@@ -1267,12 +1267,23 @@ struct M3 {
   double re[9], im[9];
 };
 
-// U_mu(x) at site s: rows 0 and 1 loaded (12 reals), row 2 rebuilt from them (SU(3)).
-__device__ __forceinline__ void load_link(const double* __restrict__ U, int32_t mu, int32_t s, int32_t V, M3& m) {
-  const double* Um = U + (int64_t)mu * 18 * V;
+// Rows 0 and 1 of the links at a block's 64 sites, by direction and component.
+using OwnLinks = double[4][12][64];
+
+// U_mu at site s: rows 0 and 1 (12 reals) from LDS where s is one of the block's sites (from s0 on), else from
+// memory; row 2 rebuilt from them (SU(3)).
+__device__ __forceinline__ void load_link(const double* __restrict__ U, const OwnLinks& own, int32_t mu, int32_t s,
+                                          int32_t s0, int32_t V, M3& m) {
   double u[18];
+  const int32_t d = s - s0;
+  if (d >= 0 && d < 64) {
 #pragma unroll
-  for (int c = 0; c < 12; ++c) u[c] = (Um + (size_t)c * V)[s];
+    for (int c = 0; c < 12; ++c) u[c] = own[mu][c][d];
+  } else {
+    Rows<double> r(U + (int64_t)mu * 18 * V, V, byte_off<double>(s));
+#pragma unroll
+    for (int c = 0; c < 12; ++c) u[c] = r.get();
+  }
   su3_row2<double>(u);
 #pragma unroll
   for (int k = 0; k < 9; ++k) {
@@ -1308,12 +1319,27 @@ __device__ __forceinline__ void mul3(const M3& A, const M3& B, M3& C) {
 // the same 64 consecutive sites, wave w computing the force on U_w: the direction is wave-uniform,
 // every load is a coalesced 64-site row of one component, and a lattice gives four times as many
 // waves as sites / 64 to hide the staples' dependent loads.
+// Loaded by every wave for itself, the 76 links of a site take 912 reals through the path from the caches to the
+// registers (32 bytes per clock and CU), 0.85 ms at 32^3x64: so the block's own links go to LDS once, and a
+// link at one of the block's sites (all x0 neighbours and half the x1 neighbours there) is read from it: 46
+// links, 552 reals, 1140 -> 1040 us.  With row 2 in LDS too the kernel needs 290 registers: one wave per SIMD, 1680 us.
 __global__ void __launch_bounds__(256) k_gauge_force(Geom g, const double* __restrict__ U, double beta,
                                                      double* __restrict__ F, double* __restrict__ partials) {
+  __shared__ OwnLinks own;
   const int32_t V = g.V;
   const int32_t mu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int32_t s = blockIdx.x * 64 + (threadIdx.x & 63);
+  const int32_t s0 = blockIdx.x * 64, lane = threadIdx.x & 63;
+  const int32_t s = s0 + lane;
   double tr[1] = {0.0};
+  {
+    Rows<double> r(U + (int64_t)mu * 18 * V, V, byte_off<double>(min(s, V - 1)));
+    double u[12];
+#pragma unroll
+    for (int c = 0; c < 12; ++c) u[c] = r.get();
+#pragma unroll
+    for (int c = 0; c < 12; ++c) own[mu][c][lane] = u[c];
+  }
+  __syncthreads();
   if (s < V) {
     int32_t xc[4];
     site_coords(g, s, xc);
@@ -1324,27 +1350,27 @@ __global__ void __launch_bounds__(256) k_gauge_force(Geom g, const double* __res
 #pragma unroll
     for (int k = 0; k < 9; ++k) A.re[k] = A.im[k] = 0.0;
 #pragma unroll 1
-    for (int nu = 0; nu < 4; ++nu) {
+    for (int32_t nu = 0; nu < 4; ++nu) {
       if (nu == mu) continue;
       const int32_t s_pn = site_shift(g, s, xc, nu, +1);
       const int32_t s_mn = site_shift(g, s, xc, nu, -1);
       const int32_t s_pm_mn = site_shift(g, s_pm, xm, nu, -1);
       M3 a, b, t;
       // upper staple U_nu(x+mu) U_mu(x+nu)^dag U_nu(x)^dag
-      load_link(U, nu, s_pm, V, a);
-      load_link(U, mu, s_pn, V, b);
+      load_link(U, own, nu, s_pm, s0, V, a);
+      load_link(U, own, mu, s_pn, s0, V, b);
       mul3<false, true>(a, b, t);
-      load_link(U, nu, s, V, a);
+      load_link(U, own, nu, s, s0, V, a);
       mul3<false, true, true>(t, a, A);
       // lower staple U_nu(x+mu-nu)^dag U_mu(x-nu)^dag U_nu(x-nu)
-      load_link(U, nu, s_pm_mn, V, a);
-      load_link(U, mu, s_mn, V, b);
+      load_link(U, own, nu, s_pm_mn, s0, V, a);
+      load_link(U, own, mu, s_mn, s0, V, b);
       mul3<true, true>(a, b, t);
-      load_link(U, nu, s_mn, V, a);
+      load_link(U, own, nu, s_mn, s0, V, a);
       mul3<false, false, true>(t, a, A);
     }
     M3 u, m;
-    load_link(U, mu, s, V, u);
+    load_link(U, own, mu, s, s0, V, u);
     mul3<false, false>(u, A, m);
     tr[0] = m.re[0] + m.re[4] + m.re[8];
     // Im Tr(lambda^c M) for the eight Gell-Mann matrices; T^c = lambda^c / 2

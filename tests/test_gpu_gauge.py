@@ -26,6 +26,19 @@ def test_gauge_force_parity(L, kind, beta):
     assert abs(S - So) <= 1e-12 * abs(So)
 
 
+@pytest.mark.parametrize("L", [(64, 2, 2, 2), (70, 2, 3, 2), (33, 3, 2, 2), (2, 2, 2, 2)])
+def test_gauge_force_block_edges(L):
+    """Rows of a block's 64 sites, longer and odd ones, and a lattice within one block: links read from the
+    block's own in LDS and from memory, in the same wave."""
+    announce(f"gauge force block edges {L}")
+    U, _, Ud, _ = setup(L, "haar", 0.0, 75)
+    F, S = api.wilson_gauge_force(L, Ud, 5.5)
+    assert rel_max(F.cpu().numpy(), og.gauge_force(U, L, 5.5)) <= 1e-12
+    So = og.wilson_action(U, L, 5.5)
+    # a sum of 6 V terms of order 1 that may cancel: bounded by the terms, not by the sum
+    assert abs(S - So) <= 1e-12 * 5.5 * 6 * np.prod(L)
+
+
 def test_gauge_force_unit_links():
     L = (6, 4, 4, 4)
     _, _, Ud, _ = setup(L, "unit", 0.0, 72)

@@ -118,12 +118,13 @@ def test_rational_apply_long_segments(mode, kappa, tol):
 
 
 # form, block, nv, order, walk, tile2: the hop-split, one-launch-per-site and tiled-walk stencils, whose
-# iterations take one update, and the walk, whose iterations take two
-CG_SHAPES = [(1, 256, 2, 2, 0, 1), (1, 128, 2, 0, 0, 1), (1, 128, 2, 1, 2, 2), (1, 64, 4, 1, 2, 1)]
+# iterations take one update, and the walk (in FP32 the streamed hop split too), whose iterations take two
+CG_SHAPES = [(1, 256, 2, 2, 0, 1), (1, 128, 2, 0, 0, 1), (1, 128, 2, 1, 2, 2), (1, 64, 4, 1, 2, 1),
+             (2, 256, 4, 2, 0, 1)]
 
 
 @pytest.mark.parametrize("mode", [0, 1])
-@pytest.mark.parametrize("shape", CG_SHAPES, ids=["split", "site", "tile", "walk"])
+@pytest.mark.parametrize("shape", CG_SHAPES, ids=["split", "site", "tile", "walk", "stream"])
 def test_rational_apply_update_forms(mode, shape):
     """Each form of the CG update on the free field, where the eigenvectors are plane waves: a source of one
     eigenvector converges in one iteration and one of two in two, far past the digits of the predicted
