@@ -410,7 +410,8 @@ rmh_status rmh_leapfrog_step(const int32_t L[4], const double* U0, const double*
  * columns, so part of its x2 neighbours are its own (used when the tile divides the plane).  Order 1
  * with walk = K > 0, form 1 and nv = 2 is the tiled walk: a block walks up to K x3 sites with an
  * L0 x R1 x R2 tile of at most `block` columns (R2 <= tile2) whose plane of the field sits in LDS (used
- * up to 2^24 sites and where a row of x0 fits `block`; K need not divide L3 nor the tile the plane).
+ * up to 2^24 sites, where a row of x0 fits `block` and where the tiles number at most V / 16 + L3, else the
+ * walk or one thread per site; K need not divide L3 nor the tile the plane).
  * Every configuration computes the same operator; a form fixes the per-site arithmetic, so results
  * are bitwise identical across block sizes, remaps, nv, ns, orders 0 and 1 and walks of one form
  * (orders 2 and 3 and the tiled walk sum the eight hops in another order: equal to rounding). */

@@ -90,7 +90,8 @@ struct HopArgs {
 struct HopTile {
   int32_t R1, R2, n1, n2, K;
 };
-// the tile of a configuration, false if it is not the tiled walk or the lattice does not fit it
+// the tile of a configuration, false if it is not the tiled walk, the lattice does not fit it or it would
+// take more blocks than hop_max_blocks
 bool hop_tile_of(const Geom& g, const HopConfig& cfg, HopTile* t);
 
 int hop_num_blocks(const Geom& g, const HopConfig& cfg);
@@ -106,7 +107,8 @@ int hop_ns_ok(const HopConfig& cfg, int32_t n_rhs);
 bool hop_ring_ok(const Geom& g, const HopConfig& cfg, int bytes);
 // upper bound of hop_num_blocks over every configuration: 16 sites per block at least (the
 // hop-split shape with one direction group per block), plus one partial block per x3 slice of
-// the walking shape; every per-block partial-sum buffer is sized with it
+// the walking shape, which the tiled walk keeps to as well (hop_tile_of); every per-block partial-sum buffer
+// is sized with it
 inline int hop_max_blocks(const Geom& g) { return (g.V + 15) / 16 + g.L3; }
 
 template <typename T>

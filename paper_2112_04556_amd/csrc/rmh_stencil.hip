@@ -1004,6 +1004,8 @@ k_hop_tile(const HopArgs<T> A, const HopTile S, int32_t xcd) {
   }
 }
 
+static int hop_tile_blocks(const Geom& g, const HopTile& t) { return t.n1 * t.n2 * ((g.L3 + t.K - 1) / t.K); }
+
 // The tile of a configuration: cfg.tile2 rows of x2 and as many rows of x1 as cfg.block columns
 // allow, evened out over the lattice; segments of cfg.walk planes, the last one shorter where
 // walk does not divide L3.
@@ -1019,9 +1021,10 @@ bool hop_tile_of(const Geom& g, const HopConfig& cfg, HopTile* t) {
   t->n2 = (g.L2 + t->R2 - 1) / t->R2;
   t->R2 = (g.L2 + t->n2 - 1) / t->n2;
   t->K = std::min(cfg.walk, g.L3);
-  return true;
+  // small extents can leave a tile a handful of columns (4x3x6x7 in single rows and planes: 42 blocks of 12
+  // sites), and the buffers of the partial sums hold hop_max_blocks: such a launch runs as if there were no tile
+  return hop_tile_blocks(g, *t) <= hop_max_blocks(g);
 }
-static int hop_tile_blocks(const Geom& g, const HopTile& t) { return t.n1 * t.n2 * ((g.L3 + t.K - 1) / t.K); }
 
 template <typename T>
 static hipError_t launch_hop_tile(const HopArgs<T>& A, const HopTile& t, int32_t xcd, dim3 grid, hipStream_t s) {

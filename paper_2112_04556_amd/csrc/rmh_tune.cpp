@@ -69,10 +69,11 @@ bool tile_shape(const Geom& g, int32_t dtype, int32_t n_rhs, HopConfig* out) {
         const int64_t per_cu = ((int64_t)t.n1 * t.n2 * nseg * n_rhs + 255) / 256;
         const double waves = (double)w * std::min<int64_t>(fit, per_cu);
         const double cost = (double)per_cu * w * (K + 1.5) * (1.0 + halo) * (1.0 + 0.5 * max_waves / waves);
-        if (best == 0.0 || cost < best) {
+        HopConfig ck = c;
+        ck.walk = K;
+        if ((best == 0.0 || cost < best) && hop_tile_of(g, ck, &t)) {
           best = cost;
-          *out = c;
-          out->walk = K;
+          *out = ck;
         }
         if (K == 1) break;
       }

@@ -373,3 +373,35 @@ def test_laplacian_default_shapes(L, n):
     y32 = api.laplacian_apply(L, Ud.float(), Pd.float()).double().cpu().numpy()
     ref = olap.laplacian(U, P, L)
     assert np.abs(y32 - ref).max() <= 1e-5 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("L", [(2, 4, 8, 8), (4, 3, 6, 7), (4, 2, 4, 4)])
+def test_tiled_walk_of_few_columns(L):
+    """Tiles of one row and one plane on small extents, more blocks than the partial sums have room for: the
+    launch is the plain walk's, bit for bit, in spectra and solves too, and the autotuner goes on past them."""
+    n = 2
+    announce(f"tiled walk of few columns {L}")
+    U, P, Ud, Pd = setup(L, "eps", 0.5, 14, n=n)
+    rat = api.rational_kappa(0.8, 3)
+    tile, walk = (1, 128, 1, 2, 1, 1), (1, 128, 1, 2, 0, 1)
+    res = {}
+    try:
+        for cfg in (tile, walk):
+            api.tune_clear()
+            for k in (1, n, 3 * n):
+                api.tune_set(L, torch.float64, k, *cfg)
+            y = api.laplacian_apply(L, Ud, Pd)
+            mom, _ = api.power_spectrum(L, Ud, Pd, 9, 3)
+            out = api.rational_apply(L, Ud, Pd, rat, api.Solver(tol=1e-11))
+            assert out["stats"]["true_relres_max"] <= 1e-11
+            res[cfg] = (y.cpu().numpy(), mom, out["y"].cpu().numpy())
+        for a, b in zip(res[tile], res[walk]):
+            assert np.array_equal(a, b)
+        assert rel_max(res[tile][0], olap.laplacian(U, P, L)) <= 1e-12
+        for dtype in (torch.float64, torch.float32):
+            for purpose in ("moments", "cg", "cg64"):
+                api.tune_clear()
+                _, ms = api.autotune_laplacian(L, Ud.to(dtype), Pd.to(dtype), reps=1, purpose=purpose)
+                assert ms > 0
+    finally:
+        api.tune_clear()
