@@ -405,3 +405,26 @@ def test_tiled_walk_of_few_columns(L):
                 assert ms > 0
     finally:
         api.tune_clear()
+
+
+@pytest.mark.parametrize("L3", range(2, 10))
+def test_xcd_map_of_any_grid(L3):
+    """The block-to-XCD map over grids of every remainder modulo 8: bitwise the unmapped launch, moments
+    (partial sums per block) included."""
+    L, n = (8, 8, 3, L3), 3
+    announce(f"xcd map {L}")
+    _, _, Ud, Pd = setup(L, "haar", 0.0, 15, n=n)
+    try:
+        for cfg in ((2, 64, 4, 0, 0), (1, 128, 2, 0, 0), (1, 64, 4, 0, 1), (1, 128, 2, 2, 0), (1, 128, 2, 1, 2)):
+            form, block, nv, order, walk = cfg
+            out = []
+            for xcd in (0, 1):
+                api.tune_clear()
+                for k in (1, n):
+                    api.tune_set(L, torch.float64, k, form, block, xcd, nv, order, walk)
+                out.append((api.laplacian_apply(L, Ud, Pd).cpu().numpy(), api.power_spectrum(L, Ud, Pd, 5, 2)[0],
+                            api.laplacian_apply(L, Ud, Pd[1:2].contiguous()).cpu().numpy()))
+            for a, b in zip(*out):
+                assert np.array_equal(a, b), cfg
+    finally:
+        api.tune_clear()
