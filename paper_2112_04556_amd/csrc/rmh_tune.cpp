@@ -33,7 +33,7 @@ Key key_of(const Geom& g, int32_t dtype, int32_t n_rhs, int32_t purpose) {
   return Key(g.L0, g.L1, g.L2, g.L3, dtype, n_rhs, purpose);
 }
 
-// The longest of the given x3 walks that divides L3 (0: none does).
+// The first of the given x3 walks that divides L3 (0: none does).
 int32_t walk_of(const Geom& g, std::initializer_list<int> ks) {
   for (int k : ks)
     if (g.L3 % k == 0) return k;
@@ -81,24 +81,48 @@ bool tile_shape(const Geom& g, int32_t dtype, int32_t n_rhs, HopConfig* out) {
   return best > 0.0;
 }
 
-// Untuned defaults, from the sweeps of the autotuner on MI355X.  All but the FP32 moments use the 3x3
-// form, which needs the fewest operations per hop.
-//  - FP64 from 2^16 site-fields on: the tiled walk (32^3x64 0.494 ms against 0.568 for the walk with four
-//    directions per thread; 24^4 84 us against 99 for the hop split, its recursion step 93 against 124;
-//    20x18^3 39 against 51; 16^4 x 2 35 against 41; 16^4 20.0-24.4 against 20.2-24.7).  Below, the tiles
-//    of a launch are few and the hop split wins or loses by how they fall on the 256 CUs (14x12x11x14
-//    17.4 against 14.2 tiled, 16x16x12x12 15.5 against 17.7, 17x15x13x19 27 against 32).
-//  - FP32 from 2^20 sites on: the tiled walk (32^3x64 0.263 ms against 0.292).  In smaller FP32 lattices its
-//    vector work, the link rebuilt by both lane halves, is the bound: a batch of at least 2^19 site-fields
-//    walks with four directions per thread (24^4 x 8 sweep 0.415 ms against 0.417), smaller launches
-//    take one thread per site and direction pair (16^4 13.4 us against 14.9 tiled, 14.3 hop split).
+// Microseconds of one FP64 application by a tile (rounds of blocks on a CU, each K planes of the field at 2.9 or,
+// with two waves on a SIMD, 3.9 us, more where the lattice's end cuts tiles, and the traffic of a thousand
+// site-fields) and by one thread per site with the 3x3 form.  Fitted to 227 launches of 2^16 to 4 M site-fields on
+// lattices of any extents; the standard deviations are 6.6 and 5.8 %.
+double tile_us(const Geom& g, int32_t n_rhs, const HopConfig& c) {
+  HopTile t;
+  if (!hop_tile_of(g, c, &t)) return 0.0;
+  const int w = (g.L0 * t.R1 * t.R2 + 31) / 32, fit = std::max(1, 8 / w);
+  const int64_t blocks = (int64_t)t.n1 * t.n2 * ((g.L3 + t.K - 1) / t.K) * n_rhs, per_cu = (blocks + 255) / 256;
+  const int m = w * std::min<int64_t>(fit, per_cu) > 4 ? 2 : 1;   // waves on a SIMD
+  const double planes = (double)((per_cu + fit - 1) / fit) * (t.K + 1.5), k = 1e-3 * g.V * n_rhs;
+  const int cut = (g.L1 % t.R1 ? 1 : 0) + (g.L2 % t.R2 ? 1 : 0);
+  const double halo = (t.R1 < g.L1 ? 1.0 / t.R1 : 0.0) + (t.R2 < g.L2 ? 1.0 / t.R2 : 0.0);
+  return planes * ((m == 1 ? 2.9 : 3.9) + 0.3 * m * cut) + k * (0.13 + 0.028 * halo + (g.L0 % 8 ? 0.024 : 0.0)) +
+         0.03 * std::max(0.0, k - 700.0);
+}
+double site_us(const Geom& g, int32_t n_rhs) {
+  const double k = 1e-3 * g.V * n_rhs;
+  return 3.5 + k * (0.254 + 0.064 / n_rhs) + 0.065 * std::max(0.0, k - 700.0);
+}
+
+// Untuned defaults, from sweeps on MI355X.  FP64 and the FP32 launches below 2^20 sites, but for the FP32 moments,
+// use the 3x3 form, which needs the fewest operations per hop.
+//  - FP64 from 2^16 site-fields on: the tiled walk where its estimate is the lower (36x32x24x28 213 us against 275;
+//    16^4 20.0 against 22.5; 24x16x16x24 x 2 68.7 against 82.3), else one thread per site (20^3x16 x 4 146.6 us
+//    against 189.1 tiled, 14x13x13x23 x 8 115 against 149), or the hop split below 98304 site-fields where the
+//    components' rows begin on whole cache lines (8x12x12x8 x 8 22.4 us against 24.7 by sites, 25.5 tiled;
+//    9x11x12x14 x 5, whose rows do not, 36.8 against 27.5).
+//  - FP32 from 2^20 sites on: the tiled walk where its waves are full and its runs of sites along x0 and x1 are
+//    whole 128-byte lines or 96 sites at least, else the walk with four directions per thread, 4 planes or, from
+//    2^21 sites on, 8 (tiled against that walk: 32^3x64 0.260 ms against 0.306; 28x32x48x48 0.288 against 0.308;
+//    22x40x44x36 0.343 against 0.232; 40x44x36x28 x 2 0.582 against 0.504).
+//  - In smaller FP32 lattices the tile's vector work, the link rebuilt by both lane halves, is the bound: a batch of
+//    at least 2^19 site-fields walks with four directions per thread (24^4 x 8 360 us against 372 tiled), smaller
+//    launches take one thread per site and direction pair (16^4 x 4 37 us against 43 for the hop split).
 //  - smaller launches (FP32: below 2^16 site-fields): four lanes per site, one per direction (hop split),
 //    whose four times as many waves hide the latency that one thread per site leaves exposed.  Two
-//    directions per lane (FP32 from 24576 site-fields on: four; 13x11x14x16 8.8 us against 10.9, 8x12x8x8
-//    6.2 against 4.5), in blocks of 128 threads where these give the CUs less work than blocks of 256
-//    (FP64 8^4: 4.8 us against 5.5; 8x12x8x8: 6.4 against 5.5).
+//    directions per lane (FP32 from 24576 site-fields on: four; 16^3x12 9.3 us against 10.4 with two, 8x12x8x8
+//    6.8 against 5.2), in blocks of 128 threads where these give the CUs less work than blocks of 256
+//    (FP64, 128 against 256: 8^4 5.6 us against 6.3; 8x12x8x8 7.2 against 6.4; 12^4 12.4 against 11.5).
 // FP32 Chebyshev moments below 2^20 sites keep the streamed adjoint form: they are FP64 results of FP32
-// sweeps, and another form's rounding moves them by a few 1e-9.
+// sweeps, and another form's rounding moves them by a few 1e-9, about as much as their own error.
 HopConfig defaults(const Geom& g, int32_t dtype, int32_t n_rhs, int32_t purpose) {
   const bool f64 = dtype == RMH_F64;
   const int64_t work = (int64_t)g.V * n_rhs;
@@ -113,11 +137,33 @@ HopConfig defaults(const Geom& g, int32_t dtype, int32_t n_rhs, int32_t purpose)
     if (batch && !hop_order_ok(g, c)) c.order = 0;
     return c;
   }
-  if ((f64 ? work >= (1 << 16) : g.V >= (1 << 20)) && tile_shape(g, dtype, n_rhs, &c)) return c;
+  if (!f64 && g.V >= (1 << 20)) {
+    HopTile t;
+    if (tile_shape(g, dtype, n_rhs, &c) && hop_tile_of(g, c, &t) && c.block % 32 == 0 &&
+        ((g.L0 * t.R1) % 32 == 0 || g.L0 * t.R1 >= 96))
+      return c;
+    c = HopConfig();
+    c.form = kFormAdjoint;
+    c.block = 256;
+    c.xcd_remap = 1;
+    c.nv = 4;
+    c.order = 0;
+    c.walk = g.V < (1 << 21) ? walk_of(g, {4, 8, 16, 2}) : walk_of(g, {8, 4, 16, 2});
+    return c;
+  }
   c.form = kFormMatrix;
   c.xcd_remap = 1;
-  if (work >= (1 << 19)) {
-    // (also the lattices too large for the tile: more than 2^24 sites, or rows longer than a block)
+  if (f64 && work >= (1 << 16) && tile_shape(g, dtype, n_rhs, &c)) {
+    if (tile_us(g, n_rhs, c) <= site_us(g, n_rhs)) return c;
+    const bool split = work < 98304 && g.V % 32 == 0;
+    c = HopConfig();
+    c.form = kFormMatrix;
+    c.xcd_remap = split ? 0 : 1;
+    c.nv = split ? 2 : 4;
+    c.block = split ? 256 : 64;
+    c.order = split ? 2 : 0;
+  } else if (work >= (1 << 19)) {
+    // (also the FP64 lattices too large for the tile: more than 2^24 sites, or rows longer than a block)
     c.nv = 4;
     c.block = f64 ? 128 : 64;
     c.walk = f64 ? walk_of(g, {8, 4, 2}) : walk_of(g, {4, 8, 2});

@@ -428,3 +428,37 @@ def test_xcd_map_of_any_grid(L3):
                 assert np.array_equal(a, b), cfg
     finally:
         api.tune_clear()
+
+
+@pytest.mark.parametrize("L,n", [((9, 13, 13, 9), 5), ((8, 12, 12, 8), 8)])
+def test_laplacian_default_shapes_beside_the_tile(L, n):
+    """FP64 launches of 2^16 site-fields and more that the estimates give to one thread per site and to the hop
+    split: the operator, a spectrum's sums per block and a solve."""
+    announce(f"default shapes beside the tile {L} n={n}")
+    U, P, Ud, Pd = setup(L, "eps", 0.5, 16, n=n)
+    api.tune_clear()
+    y = api.laplacian_apply(L, Ud, Pd)
+    assert rel_max(y.cpu().numpy(), olap.laplacian(U, P, L)) <= 1e-12
+    mom, _ = api.power_spectrum(L, Ud, Pd, 3, 2)
+    # T_1(Delta / 8 - 1): moment 1 is <x, y> / 8 - <x, x>, a sum of 32 V n terms below 3 |x|^2 each
+    x = Pd.double()
+    want = ((x * y).sum((1, 2, 3)) / 8 - (x * x).sum((1, 2, 3))).cpu().numpy()
+    assert np.all(np.abs(mom[:, 1] - want) <= 1e-12 * mom[:, 0])
+    out = api.rational_apply(L, Ud, Pd, api.rational_kappa(0.5, 3), api.Solver(tol=1e-10))
+    assert out["stats"]["true_relres_max"] <= 1e-10
+
+
+@pytest.mark.parametrize("L", [(22, 40, 44, 28), (25, 37, 33, 35), (32, 32, 32, 32), (28, 32, 32, 38)])
+def test_laplacian_fp32_default_shapes_of_large_lattices(L):
+    """FP32 lattices of 2^20 sites and more, whose default is the walk (none where no walk divides L3) or, where
+    tiles are made of whole cache lines, the tiled walk: against FP64 at 65 terms of eight roundings each."""
+    announce(f"fp32 default shapes {L}")
+    V = api.volume(L)
+    g = torch.Generator(device=dev()).manual_seed(18)
+    h = inputs.random_links((4, 4, 4, 4), "haar", 0.0, seed=18).to(dev())
+    U = h[:, torch.randint(0, 256, (V,), device=dev(), generator=g)]
+    x = torch.randn(1, 4, 8, V, device=dev(), generator=g, dtype=torch.float64)
+    api.tune_clear()
+    ref = api.laplacian_apply(L, api.pack_links(L, U, torch.float64), x.float().double())
+    y = api.laplacian_apply(L, api.pack_links(L, U, torch.float32), x.float()).double()
+    assert float((y - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
