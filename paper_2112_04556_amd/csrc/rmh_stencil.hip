@@ -81,11 +81,11 @@ __device__ __forceinline__ void link_row2(T* u) {
   su3_row2<T, sizeof(T) == 8 || FORM == kFormMatrix>(u);
 }
 
-// The link at site s (component c at Um[c V + s]): rows 0 and 1 are loaded, row 2 is rebuilt
-// from them (SU(3)), so a hop moves 12 link reals instead of 18.  kUni: Um is the same for the
-// whole wave.
-template <typename T, int FORM, bool kUni = true>
-__device__ __forceinline__ void load_link(const T* __restrict__ Um, int32_t s, int32_t V, T (&u)[18]) {
+// Rows 0 and 1 of the link at site s (component c at Um[c V + s]): row 2 is rebuilt from them (link_row2, SU(3)),
+// so a hop moves 12 link reals instead of 18.  kUni: Um is the same for the whole wave.  The callers load the
+// field before they rebuild row 2, so that all of a hop's loads are in flight together.
+template <typename T, bool kUni = true, int N>
+__device__ __forceinline__ void load_rows(const T* __restrict__ Um, int32_t s, int32_t V, T (&u)[N]) {
   if (kUni) {
     Rows<T> r(Um, V, byte_off<T>(s));
 #pragma unroll
@@ -94,15 +94,6 @@ __device__ __forceinline__ void load_link(const T* __restrict__ Um, int32_t s, i
 #pragma unroll
     for (int c = 0; c < 12; ++c) u[c] = (Um + (size_t)c * V)[s];
   }
-  link_row2<T, FORM>(u);
-}
-
-// The 12 stored reals of rows 0 and 1.
-template <typename T>
-__device__ __forceinline__ void load_rows(const T* __restrict__ Um, int32_t s, int32_t V, T (&u)[12]) {
-  Rows<T> r(Um, V, byte_off<T>(s));
-#pragma unroll
-  for (int c = 0; c < 12; ++c) u[c] = r.get();
 }
 
 // Directions nu0 .. nu0 + NV - 1 of the field at site s.  kScalar false: addressed per lane (the streamed form
@@ -222,6 +213,14 @@ __device__ __forceinline__ void hop_store(const HopArgs<T>& A, int32_t v, const 
   }
 }
 
+// The FP32 streamed form's link and field loads go out before any of the hop's arithmetic: left to itself the
+// scheduler starts on the link and issues the field's loads between, a second exposed latency per hop (moments at
+// 24^4, two fields: 134 us with all loads first, 141 without).
+template <typename T, int FORM>
+__device__ __forceinline__ void all_loads_first() {
+  if constexpr (sizeof(T) == 4 && FORM == kFormStream) __builtin_amdgcn_sched_barrier(0);
+}
+
 // out[v] = a (H x)[v] + b x[v] + c z[v]: a block of B threads covers B * NV / 4 sites; the
 // 4 / NV thread groups of a site (direction subsets) are wave-aligned slices of the block.
 // One backward hop: link and field both read at the neighbour site sb.
@@ -229,8 +228,10 @@ template <typename T, int FORM, int NV, bool kT, bool kUni = true>
 __device__ __forceinline__ void hop_term(const T* __restrict__ Um, int32_t sb, const T* __restrict__ xf,
                                          int nu0, int32_t V, T (&acc)[NV][8]) {
   T u[18], phi[NV][8];
-  load_link<T, FORM, kUni>(Um, sb, V, u);
+  load_rows<T, kUni>(Um, sb, V, u);
   load_field<T, NV, kUni || FORM == kFormMatrix>(xf, sb, nu0, V, phi);
+  all_loads_first<T, FORM>();
+  link_row2<T, FORM>(u);
   hop_apply<T, FORM, NV, kT>(u, phi, acc);
 }
 
@@ -240,8 +241,10 @@ __device__ __forceinline__ void hop_term_fwd(const T* __restrict__ Um, int32_t s
                                              const T* __restrict__ xf, int nu0, int32_t V,
                                              T (&acc)[NV][8]) {
   T u[18], phi[NV][8];
-  load_link<T, FORM, kUni>(Um, s, V, u);
+  load_rows<T, kUni>(Um, s, V, u);
   load_field<T, NV, kUni || FORM == kFormMatrix>(xf, sf, nu0, V, phi);
+  all_loads_first<T, FORM>();
+  link_row2<T, FORM>(u);
   hop_apply<T, FORM, NV, false>(u, phi, acc);
 }
 
@@ -515,7 +518,7 @@ k_hop_walk(const HopArgs<T> A, int32_t xcd, int32_t K, int32_t tile2, int32_t la
         // x0 hops from the other lanes of this x0 row (a row of L0 lanes lies within the wave):
         // the field at x +- 0 is that lane's carried centre, and the backward link U_0(x - 0) is
         // the forward link that lane loads, passed as its 12 loaded reals (row 2 rebuilt here, as
-        // load_link does) -- the same values the loads would give, in the same order of terms
+        // a hop of its own does) -- the same values the loads would give, in the same order of terms
         const int32_t lane = threadIdx.x & 63;
         const int32_t x0 = xc[0];
         const int32_t row = lane - x0;
@@ -596,9 +599,10 @@ template <typename T, int FORM, int NS, bool kT>
 __device__ __forceinline__ void hop_term_ns(const T* __restrict__ Um, int32_t sl, int32_t sn,
                                             const T* const (&xf)[NS], int32_t V, T (&acc)[NS * 4][8]) {
   T u[18];
-  load_link<T, FORM>(Um, sl, V, u);
+  load_rows<T>(Um, sl, V, u);
   if (FORM == kFormAdjoint) {
     T R[64];
+    link_row2<T, FORM>(u);
     adjoint_matrix<T>(u, R);
 #pragma unroll
     for (int f = 0; f < NS; ++f) {
@@ -617,6 +621,7 @@ __device__ __forceinline__ void hop_term_ns(const T* __restrict__ Um, int32_t sl
 #pragma unroll
     for (int f = 0; f < NS; ++f)
       load_field<T, 4>(xf[f], sn, 0, V, phi + f * 4);
+    link_row2<T, FORM>(u);
     adj_stream<T, NS * 4, kT>(u, phi, acc);
   }
 }
