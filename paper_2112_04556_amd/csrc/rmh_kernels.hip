@@ -1270,13 +1270,14 @@ struct M3 {
 // Rows 0 and 1 of the links at a block's 64 sites, by direction and component.
 using OwnLinks = double[4][12][64];
 
-// U_mu at site s: rows 0 and 1 (12 reals) from LDS where s is one of the block's sites (from s0 on), else from
-// memory; row 2 rebuilt from them (SU(3)).
+// U_mu at site s: rows 0 and 1 (12 reals) from LDS where it holds the block's own links (kOwn) and s is one of the
+// block's sites (from s0 on), else from memory; row 2 rebuilt from them (SU(3)).
+template <bool kOwn>
 __device__ __forceinline__ void load_link(const double* __restrict__ U, const OwnLinks& own, int32_t mu, int32_t s,
                                           int32_t s0, int32_t V, M3& m) {
   double u[18];
   const int32_t d = s - s0;
-  if (d >= 0 && d < 64) {
+  if (kOwn && d >= 0 && d < 64) {
 #pragma unroll
     for (int c = 0; c < 12; ++c) u[c] = own[mu][c][d];
   } else {
@@ -1323,6 +1324,10 @@ __device__ __forceinline__ void mul3(const M3& A, const M3& B, M3& C) {
 // registers (32 bytes per clock and CU), 0.85 ms at 32^3x64: so the block's own links go to LDS once, and a
 // link at one of the block's sites (all x0 neighbours and half the x1 neighbours there) is read from it: 46
 // links, 552 reals, 1140 -> 1040 us.  With row 2 in LDS too the kernel needs 290 registers: one wave per SIMD, 1680 us.
+// Where the lattice gives a CU one block at most, latency alone counts: with rows of x0 across wave and block ends
+// a wave goes through both paths link by link, and every link from memory (kOwn false) is the faster (7x6x8x5 10.8 us
+// against 12.0; 8^4, whose rows fit, 11.9 against 10.8 from LDS).
+template <bool kOwn>
 __global__ void __launch_bounds__(256) k_gauge_force(Geom g, const double* __restrict__ U, double beta,
                                                      double* __restrict__ F, double* __restrict__ partials) {
   __shared__ OwnLinks own;
@@ -1331,15 +1336,15 @@ __global__ void __launch_bounds__(256) k_gauge_force(Geom g, const double* __res
   const int32_t s0 = blockIdx.x * 64, lane = threadIdx.x & 63;
   const int32_t s = s0 + lane;
   double tr[1] = {0.0};
-  {
+  if (kOwn) {
     Rows<double> r(U + (int64_t)mu * 18 * V, V, byte_off<double>(min(s, V - 1)));
     double u[12];
 #pragma unroll
     for (int c = 0; c < 12; ++c) u[c] = r.get();
 #pragma unroll
     for (int c = 0; c < 12; ++c) own[mu][c][lane] = u[c];
+    __syncthreads();
   }
-  __syncthreads();
   if (s < V) {
     int32_t xc[4];
     site_coords(g, s, xc);
@@ -1357,20 +1362,20 @@ __global__ void __launch_bounds__(256) k_gauge_force(Geom g, const double* __res
       const int32_t s_pm_mn = site_shift(g, s_pm, xm, nu, -1);
       M3 a, b, t;
       // upper staple U_nu(x+mu) U_mu(x+nu)^dag U_nu(x)^dag
-      load_link(U, own, nu, s_pm, s0, V, a);
-      load_link(U, own, mu, s_pn, s0, V, b);
+      load_link<kOwn>(U, own, nu, s_pm, s0, V, a);
+      load_link<kOwn>(U, own, mu, s_pn, s0, V, b);
       mul3<false, true>(a, b, t);
-      load_link(U, own, nu, s, s0, V, a);
+      load_link<kOwn>(U, own, nu, s, s0, V, a);
       mul3<false, true, true>(t, a, A);
       // lower staple U_nu(x+mu-nu)^dag U_mu(x-nu)^dag U_nu(x-nu)
-      load_link(U, own, nu, s_pm_mn, s0, V, a);
-      load_link(U, own, mu, s_mn, s0, V, b);
+      load_link<kOwn>(U, own, nu, s_pm_mn, s0, V, a);
+      load_link<kOwn>(U, own, mu, s_mn, s0, V, b);
       mul3<true, true>(a, b, t);
-      load_link(U, own, nu, s_mn, s0, V, a);
+      load_link<kOwn>(U, own, nu, s_mn, s0, V, a);
       mul3<false, false, true>(t, a, A);
     }
     M3 u, m;
-    load_link(U, own, mu, s, s0, V, u);
+    load_link<kOwn>(U, own, mu, s, s0, V, u);
     mul3<false, false>(u, A, m);
     tr[0] = m.re[0] + m.re[4] + m.re[8];
     // Im Tr(lambda^c M) for the eight Gell-Mann matrices; T^c = lambda^c / 2
@@ -1401,7 +1406,9 @@ int gauge_force_blocks(const Geom& g) { return (g.V + 63) / 64; }
 
 hipError_t launch_gauge_force(const Geom& g, const double* U, double beta, double* F, double* partials,
                               hipStream_t s) {
-  hipLaunchKernelGGL(k_gauge_force, dim3(gauge_force_blocks(g)), dim3(256), 0, s, g, U, beta, F, partials);
+  const int nblk = gauge_force_blocks(g);
+  const auto kernel = nblk <= 256 && 64 % g.L0 ? k_gauge_force<false> : k_gauge_force<true>;
+  hipLaunchKernelGGL(kernel, dim3(nblk), dim3(256), 0, s, g, U, beta, F, partials);
   return hipGetLastError();
 }
 

@@ -39,6 +39,18 @@ def test_gauge_force_block_edges(L):
     assert abs(S - So) <= 1e-12 * 5.5 * 6 * np.prod(L)
 
 
+@pytest.mark.parametrize("L", [(7, 6, 8, 5), (33, 16, 8, 4), (8, 8, 4, 4)])
+def test_gauge_force_small_and_large_grids(L):
+    """Rows across block ends on a grid of one block per CU at most, where every link comes from memory, on a larger
+    one, and whole rows on a small one, where the block's own come from LDS."""
+    announce(f"gauge force grids {L}")
+    U, _, Ud, _ = setup(L, "haar", 0.0, 76)
+    F, S = api.wilson_gauge_force(L, Ud, 5.5)
+    assert rel_max(F.cpu().numpy(), og.gauge_force(U, L, 5.5)) <= 1e-12
+    # a sum of 6 V terms of order 1 that may cancel: bounded by the terms, not by the sum
+    assert abs(S - og.wilson_action(U, L, 5.5)) <= 1e-12 * 5.5 * 6 * np.prod(L)
+
+
 def test_gauge_force_unit_links():
     L = (6, 4, 4, 4)
     _, _, Ud, _ = setup(L, "unit", 0.0, 72)
