@@ -411,7 +411,8 @@ rmh_status rmh_leapfrog_step(const int32_t L[4], const double* U0, const double*
  * with walk = K > 0, form 1 and nv = 2 is the tiled walk: a block walks up to K x3 sites with an
  * L0 x R1 x R2 tile of at most `block` columns (R2 <= tile2) whose plane of the field sits in LDS (used
  * up to 2^24 sites, where a row of x0 fits `block` and where the tiles number at most V / 16 + L3, else the
- * walk or one thread per site; K need not divide L3 nor the tile the plane).
+ * walk or one thread per site; K need not divide L3 nor the tile the plane).  On a lattice that takes it its
+ * block may be any number up to 256, its tile2 and K any number from 1 on.
  * Every configuration computes the same operator; a form fixes the per-site arithmetic, so results
  * are bitwise identical across block sizes, remaps, nv, ns, orders 0 and 1 and walks of one form
  * (orders 2 and 3 and the tiled walk sum the eight hops in another order: equal to rounding). */
@@ -437,8 +438,8 @@ typedef enum {
  * RMH_PURPOSE_ANY entry of that batch, else the nearest batch size of the purpose, else of
  * RMH_PURPOSE_ANY, else built-in defaults by lattice size, dtype and batch. */
 rmh_status rmh_tune_set(const int32_t L[4], int32_t dtype, int32_t n_rhs, int32_t purpose, const rmh_hop_config* cfg);
-/* Time every stencil configuration on the caller's buffers and keep the fastest for (L, dtype, n_rhs,
- * purpose).  The timing unit: for RMH_PURPOSE_MOMENTS, _FILTER and _CHEB_BWD the recursion step
+/* Time the built-in and every other stencil configuration on the caller's buffers and keep the fastest for
+ * (L, dtype, n_rhs, purpose).  The timing unit: for RMH_PURPOSE_MOMENTS, _FILTER and _CHEB_BWD the recursion step
  * y = -H x / 4 - y (written over its z input, as the sweeps write t_{k+1} over t_{k-1}; y is zeroed
  * first); for _APPLY, _CG, _CG64 and _HEATBATH the plain y = (8 - H) x; for _ANY both (the
  * pair); with the per-block FP64 dot products that the purpose's drivers fuse into the launch

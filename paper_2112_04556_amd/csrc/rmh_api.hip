@@ -2357,7 +2357,7 @@ rmh_status rmh_tune_set(const int32_t L[4], int32_t dtype, int32_t n_rhs, int32_
   if (n_rhs < 1) return fail(RMH_E_ARG, "n_rhs must be >= 1");
   if (!cfg) return fail(RMH_E_ARG, "cfg is NULL");
   const HopConfig c = from_abi(*cfg);
-  if (const char* why = hop_config_error(c, dtype)) return fail(RMH_E_ARG, "%s", why);
+  if (const char* why = hop_config_error(g, c, dtype)) return fail(RMH_E_ARG, "%s", why);
   tune_store(g, dtype, n_rhs, purpose, c, 0.0);
   return RMH_OK;
 } catch (...) {   // no C++ exception crosses the C ABI
@@ -2432,17 +2432,16 @@ rmh_status rmh_autotune_laplacian(const int32_t L[4], const void* U, int32_t dty
   hipEvent_t e0, e1;
   HIP_TRY(hipEventCreate(&e0));
   HIP_TRY(hipEventCreate(&e1));
-  HopConfig bestc = tune_hop(g, dtype, n_rhs, purpose);
-  float bt = 1e30f;
-  rmh_status st = RMH_OK;
-  for (int form = 0; form < 3 && st == RMH_OK; ++form)
+  // the built-in shape first (a tile of any size, which the grid of the others need not hold)
+  std::vector<HopConfig> cand{tune_default(g, dtype, n_rhs, purpose)};
+  for (int form = 0; form < 3; ++form)
     for (int nv : {4, 2, 1})
     for (int ns : {1, 2, 4})
     for (int tile2 : {1, 2, 4})
     for (int block : {64, 128, 256})
     for (int walk : {0, 1, 2, 4, 8, 12, 16, 24, 32})
-    for (int order = 0; order < 4 && st == RMH_OK; ++order) {
-      for (int xcd = 0; xcd < 2 && st == RMH_OK; ++xcd) {
+    for (int order = 0; order < 4; ++order)
+      for (int xcd = 0; xcd < 2; ++xcd) {
         HopConfig c;
         c.form = form;
         c.block = block;
@@ -2452,7 +2451,7 @@ rmh_status rmh_autotune_laplacian(const int32_t L[4], const void* U, int32_t dty
         c.walk = walk;
         c.ns = ns;
         c.tile2 = tile2;
-        if (hop_config_error(c, dtype)) continue;
+        if (hop_config_error(g, c, dtype)) continue;
         if (ns > 1 && n_rhs % ns) continue;
         HopTile tile;
         if (hop_tile_of(g, c, &tile)) {
@@ -2461,41 +2460,45 @@ rmh_status rmh_autotune_laplacian(const int32_t L[4], const void* U, int32_t dty
           if ((order == 1 || order == 3) && !hop_order_ok(g, c)) continue;
           if (walk && (order || !hop_walk_ok(g, c) || (walk != 4 && walk != 8 && walk != 16))) continue;
         }
-        tune_store(g, dtype, n_rhs, purpose, c, 0.0);
-        auto unit = [&]() -> rmh_status {
-          const hipError_t e =
-              dtype == RMH_F64
-                  ? tune_unit<double>(g, (const double*)U, (const double*)x, (double*)y, n_rhs, c, unit_kind,
-                                      partials, dot_mask, s)
-                  : tune_unit<float>(g, (const float*)U, (const float*)x, (float*)y, n_rhs, c, unit_kind,
-                                     partials, dot_mask, s);
-          return e == hipSuccess ? RMH_OK : fail(RMH_E_HIP, "stencil launch: %s", hipGetErrorString(e));
-        };
-        st = unit();  // warm-up
-        if (st != RMH_OK) break;
-        if (hipEventRecord(e0, s) != hipSuccess) st = fail(RMH_E_HIP, "hipEventRecord");
-        for (int r = 0; r < reps && st == RMH_OK; ++r) st = unit();
-        if (st != RMH_OK) break;
-        if (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess) {
-          st = fail(RMH_E_HIP, "hipEventRecord/Synchronize");
-          break;
-        }
-        float ms = 0.f;
-        if (hipEventElapsedTime(&ms, e0, e1) != hipSuccess) ms = 1e30f;
-        ms /= reps;
-        if (log_level() > 0)
-          fprintf(stderr, "[rmh] tune L=%dx%dx%dx%d dtype=%d n=%d purpose=%d form=%d nv=%d ns=%d block=%d order=%d walk=%d tile2=%d xcd=%d: %.4f ms\n",
-                  g.L0, g.L1, g.L2, g.L3, dtype, n_rhs, purpose, form, nv, ns, block, order, walk, tile2, xcd, ms);
-        if (ms < bt) {
-          bt = ms;
-          bestc = c;
-        }
+        cand.push_back(c);
       }
+  HopConfig bestc = tune_hop(g, dtype, n_rhs, purpose);
+  float bt = 1e30f;
+  rmh_status st = RMH_OK;
+  for (const HopConfig& c : cand) {
+    auto unit = [&]() -> rmh_status {
+      const hipError_t e =
+          dtype == RMH_F64
+              ? tune_unit<double>(g, (const double*)U, (const double*)x, (double*)y, n_rhs, c, unit_kind,
+                                  partials, dot_mask, s)
+              : tune_unit<float>(g, (const float*)U, (const float*)x, (float*)y, n_rhs, c, unit_kind,
+                                 partials, dot_mask, s);
+      return e == hipSuccess ? RMH_OK : fail(RMH_E_HIP, "stencil launch: %s", hipGetErrorString(e));
+    };
+    st = unit();  // warm-up
+    if (st != RMH_OK) break;
+    if (hipEventRecord(e0, s) != hipSuccess) st = fail(RMH_E_HIP, "hipEventRecord");
+    for (int r = 0; r < reps && st == RMH_OK; ++r) st = unit();
+    if (st != RMH_OK) break;
+    if (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess) {
+      st = fail(RMH_E_HIP, "hipEventRecord/Synchronize");
+      break;
     }
+    float ms = 0.f;
+    if (hipEventElapsedTime(&ms, e0, e1) != hipSuccess) ms = 1e30f;
+    ms /= reps;
+    if (log_level() > 0)
+      fprintf(stderr, "[rmh] tune L=%dx%dx%dx%d dtype=%d n=%d purpose=%d form=%d nv=%d ns=%d block=%d order=%d walk=%d tile2=%d xcd=%d: %.4f ms\n",
+              g.L0, g.L1, g.L2, g.L3, dtype, n_rhs, purpose, c.form, c.nv, c.ns, c.block, c.order, c.walk, c.tile2,
+              c.xcd_remap, ms);
+    if (ms < bt) {
+      bt = ms;
+      bestc = c;
+    }
+  }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  // the candidates were stored one by one while they were timed: leave the best one measured (or,
-  // after a failure before any was, the configuration looked up at the start) in the table
+  // the best one measured (or, after a failure before any was, the configuration looked up at the start)
   tune_store(g, dtype, n_rhs, purpose, bestc, bt < 1e30f ? bt : 0.0);
   if (st != RMH_OK) return st;
   if (best) *best = to_abi(bestc);

@@ -217,7 +217,12 @@ HopConfig fit_batch(HopConfig c, int32_t n_rhs) {
 }
 }  // namespace
 
-const char* hop_config_error(const HopConfig& c, int32_t dtype) {
+const char* hop_config_error(const Geom& g, const HopConfig& c, int32_t dtype) {
+  // The tiled walk's block counts columns and its tile and walk fit any extents, so on a lattice that takes it their
+  // whole range is valid (the built-in shapes are among it); anywhere else the launch would be one of the others.
+  HopTile t;
+  if (c.block >= 1 && c.block <= 256 && c.tile2 >= 1 && hop_tile_of(g, c, &t))
+    return c.xcd_remap == 0 || c.xcd_remap == 1 ? nullptr : "xcd_remap must be 0 or 1";
   if (c.form < kFormAdjoint || c.form > kFormStream) return "form must be 0, 1 or 2";
   if (c.block != 64 && c.block != 128 && c.block != 256) return "block must be 64, 128 or 256";
   if (c.nv != 1 && c.nv != 2 && c.nv != 4) return "nv must be 1, 2 or 4";
@@ -246,6 +251,11 @@ HopConfig tune_hop(const Geom& g, int32_t dtype, int32_t n_rhs, int32_t purpose)
   if (const HopConfig* c = nearest(g, dtype, n_rhs, purpose)) return fit_batch(*c, n_rhs);
   if (const HopConfig* c = nearest(g, dtype, n_rhs, RMH_PURPOSE_ANY)) return fit_batch(*c, n_rhs);
   return defaults_kept(g, dtype, n_rhs, purpose);  // under the lock
+}
+
+HopConfig tune_default(const Geom& g, int32_t dtype, int32_t n_rhs, int32_t purpose) {
+  std::lock_guard<std::mutex> lk(g_mu);
+  return defaults_kept(g, dtype, n_rhs, purpose);
 }
 
 void tune_clear() {
@@ -377,9 +387,13 @@ int tune_load_file(const char* path, const std::string& arch, int32_t runtime, i
     if ((dtype != RMH_F64 && dtype != RMH_F32) || v[5] < 1 || v[5] > (1L << 24) || v[6] < RMH_PURPOSE_ANY ||
         v[6] > RMH_PURPOSE_HEATBATH)
       return -2;
-    for (int i = 0; i < 4; ++i)
+    int64_t V = 1;   // (saturated: an entry for more sites than any call takes is kept like the others)
+    for (int i = 0; i < 4; ++i) {
       if (v[i] < 2 || v[i] > (1 << 20)) return -2;
-    if (hop_config_error(c, dtype)) return -2;
+      V = std::min<int64_t>(V * v[i], INT32_MAX);
+    }
+    const Geom g{(int32_t)v[0], (int32_t)v[1], (int32_t)v[2], (int32_t)v[3], (int32_t)V};
+    if (hop_config_error(g, c, dtype)) return -2;
     add[Key((int32_t)v[0], (int32_t)v[1], (int32_t)v[2], (int32_t)v[3], dtype, (int32_t)v[5], (int32_t)v[6])] =
         Entry{c, 0.0};
     p = cb + 1;

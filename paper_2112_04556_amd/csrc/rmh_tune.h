@@ -11,8 +11,10 @@ namespace rmh {
 HopConfig tune_hop(const Geom& g, int32_t dtype, int32_t n_rhs, int32_t purpose);
 void tune_store(const Geom& g, int32_t dtype, int32_t n_rhs, int32_t purpose, const HopConfig& cfg, double ms);
 void tune_clear();
-// why a configuration is invalid for dtype, or nullptr
-const char* hop_config_error(const HopConfig& cfg, int32_t dtype);
+// the built-in configuration, whatever is stored
+HopConfig tune_default(const Geom& g, int32_t dtype, int32_t n_rhs, int32_t purpose);
+// why a configuration is invalid for dtype on a lattice, or nullptr
+const char* hop_config_error(const Geom& g, const HopConfig& cfg, int32_t dtype);
 // the cache as a JSON file stamped with the device architecture and HIP runtime version:
 // 0 on success, -1 when the file cannot be written / read, -2 (load) when it is malformed or holds an
 // invalid entry; a file of another architecture or runtime loads nothing

@@ -268,6 +268,46 @@ def test_tune_set_validation():
     assert _lib.lib().rmh_tune_clear() == 0
 
 
+def test_tune_tiled_walk_shapes(tmp_path):
+    """The tiled walk (form 1, nv 2, order 1, a walk) takes any block up to 256 columns, any tile2 and any walk on a
+    lattice that fits it, and such entries survive the tuning file; everywhere else the other shapes' rules hold."""
+    lib_ = _lib.lib()
+    assert lib_.rmh_tune_clear() == 0
+
+    def put(L, cfg):
+        return lib_.rmh_tune_set(_lib.lattice_arg(L), 0, 1, 0, ctypes.byref(_lib.RmhHopConfig(*cfg)))
+
+    big, long_, wide, tiny = (24, 24, 24, 24), (8, 8, 8, 128), (300, 4, 4, 4), (2, 4, 8, 8)
+    ok = [(big, (1, 216, 1, 2, 1, 6, 1, 3)), (big, (1, 24, 0, 2, 1, 24, 1, 1)), (long_, (1, 64, 1, 2, 1, 100, 1, 8)),
+          (big, (1, 256, 1, 2, 1, 12, 1, 2))]
+    bad = [(big, (1, 216, 1, 2, 0, 6, 1, 1)),      # the plain walk
+           (big, (1, 216, 1, 2, 1, 0, 1, 1)),      # no walk
+           (big, (2, 216, 1, 2, 1, 6, 1, 1)),      # another form
+           (big, (1, 216, 1, 4, 1, 6, 1, 1)),      # four directions a thread
+           (big, (1, 216, 1, 2, 1, 6, 2, 1)),      # two fields a thread
+           (big, (1, 257, 1, 2, 1, 6, 1, 1)), (big, (1, 0, 1, 2, 1, 6, 1, 1)), (big, (1, 23, 1, 2, 1, 6, 1, 1)),
+           (big, (1, 216, 2, 2, 1, 6, 1, 3)), (big, (1, 216, 1, 2, 1, 6, 1, 0)), (big, (1, 216, 1, 2, 1, -1, 1, 3)),
+           (wide, (1, 216, 1, 2, 1, 2, 1, 1)),     # a row of x0 longer than the block
+           (tiny, (1, 100, 1, 2, 1, 1, 1, 1)),     # more tiles than the partial sums hold
+           (long_, (1, 128, 1, 2, 0, 100, 1, 1))]  # the plain walk over more than 64 planes
+    for L, cfg in bad:
+        assert put(L, cfg) == 1, (L, cfg)
+    for L, cfg in ok:
+        assert put(L, cfg) == 0, (L, cfg)
+    p1, p2 = str(tmp_path / "a.json"), str(tmp_path / "b.json")
+    n = ctypes.c_int32(0)
+    assert lib_.rmh_tune_save(p1.encode(), ctypes.byref(n)) == 0 and n.value == 2     # one entry per lattice
+    assert lib_.rmh_tune_clear() == 0
+    assert lib_.rmh_tune_load(p1.encode(), ctypes.byref(n)) == 0 and n.value == 2
+    assert lib_.rmh_tune_save(p2.encode(), ctypes.byref(n)) == 0 and n.value == 2
+    assert open(p1).read() == open(p2).read()
+    doc = json.load(open(p1))
+    for key, value in (("L0", 300), ("block", 300), ("order", 0), ("walk", 0)):
+        json.dump(dict(doc, entries=[dict(doc["entries"][0], **{"block": 216, key: value})]), open(p2, "w"))
+        assert lib_.rmh_tune_load(p2.encode(), ctypes.byref(n)) == 1, key
+    assert lib_.rmh_tune_clear() == 0
+
+
 def test_tune_file_round_trip(tmp_path):
     """The launch cache survives a save / clear / load round trip through its JSON file (keyed by
     lattice, dtype, batch and purpose, stamped with the device architecture and HIP runtime); a

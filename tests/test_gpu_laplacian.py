@@ -462,3 +462,37 @@ def test_laplacian_fp32_default_shapes_of_large_lattices(L):
     ref = api.laplacian_apply(L, api.pack_links(L, U, torch.float64), x.float().double())
     y = api.laplacian_apply(L, api.pack_links(L, U, torch.float32), x.float()).double()
     assert float((y - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
+
+
+AUTOTUNE_24 = """
+import sys
+sys.path.insert(0, sys.argv[1])
+import torch
+from paper_2112_04556_amd import api, inputs
+L = (24, 24, 24, 24)
+U = inputs.random_links((4, 4, 4, 4), "eps", 0.3, seed=3).cuda()[:, torch.arange(24 ** 4, device="cuda") % 256]
+x = torch.randn(1, 4, 8, 24 ** 4, dtype=torch.float64, device="cuda")
+Ud = api.pack_links(L, U, torch.float64)
+cfg, ms = api.autotune_laplacian(L, Ud, x, reps=3, purpose="apply")
+assert api.tune_save(sys.argv[2]) == 1
+api.tune_clear()
+assert api.tune_load(sys.argv[2]) == 1
+print("best", *cfg, ms)
+"""
+
+
+def test_autotune_times_the_built_in_shape(tmp_path):
+    """24^4 in FP64, whose built-in tile (216 columns) is not on the grid of the other candidates: the autotuner times
+    it too, first, and keeps none that was slower; what it stores survives the tuning file."""
+    import os
+    import subprocess
+    import sys
+    announce("autotune times the built-in shape")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(api.__file__)))
+    r = subprocess.run([sys.executable, "-c", AUTOTUNE_24, root, str(tmp_path / "tune.json")], capture_output=True,
+                       text=True, timeout=100, env=dict(os.environ, RMH_LOG="1"))
+    assert r.returncode == 0, r.stderr[-2000:]
+    lines = [ln for ln in r.stderr.splitlines() if ln.startswith("[rmh] tune ")]
+    assert "block=216 " in lines[0] and "tile2=3 " in lines[0], lines[0]
+    best = float(r.stdout.split()[-1])
+    assert best <= min(float(ln.split()[-2]) for ln in lines) + 1e-4
