@@ -443,7 +443,9 @@ rmh_status rmh_tune_set(const int32_t L[4], int32_t dtype, int32_t n_rhs, int32_
  * y = -H x / 4 - y (written over its z input, as the sweeps write t_{k+1} over t_{k-1}; y is zeroed
  * first); for _APPLY, _CG, _CG64 and _HEATBATH the plain y = (8 - H) x; for _ANY both (the
  * pair); with the per-block FP64 dot products that the purpose's drivers fuse into the launch
- * (_CG, _CG64: one, _MOMENTS: three), written into the workspace ws (device, ws_bytes >=
+ * (_CG64: one, _MOMENTS: three; _CG: three and a read of y as the residual, or, for the shapes whose
+ * iterations take their update in two launches, one and a pass over y as that second launch's),
+ * written into the workspace ws (device, ws_bytes >=
  * rmh_workspace_bytes(RMH_OP_AUTOTUNE, L, dtype, n_rhs, 0, 0, 0)); reps units each, HIP events on
  * the stream, y overwritten.  best (optional, host) receives the configuration, best_ms (optional)
  * the mean time of one unit.  RMH_E_ARG for null pointers or y or ws overlapping x, U or each

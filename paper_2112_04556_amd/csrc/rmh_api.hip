@@ -1279,10 +1279,12 @@ rmh_status cheb_bwd(const Geom& g, const double* U, const double* x, int32_t n_r
 // y = (8 - H) x of the CG and the Chebyshev recursion step y = -H x / 4 - z with z = y (the sweeps
 // write t_{k+1} over t_{k-1}), so the pick fits the solves and the spectra alike.
 // partials/dot_mask (optional): the per-block FP64 dot products the drivers of a purpose fuse into
-// the same launch (the CG's <p, Ap>, the moments' three), so the unit runs the kernel they run.
+// the same launch (the moments' three), so the unit runs the kernel they run.  cg_flags (kind 1): the unit of a
+// CG iteration, whose update takes one launch or two by the stencil's shape, and the flags of a running field at
+// ring slot 0.
 template <typename T>
 static hipError_t tune_unit(const Geom& g, const T* U, const T* x, T* y, int32_t n_rhs, const HopConfig& cfg,
-                            int32_t kind, double* partials, int32_t dot_mask, hipStream_t s) {
+                            int32_t kind, double* partials, int32_t dot_mask, const int32_t* cg_flags, hipStream_t s) {
   HopArgs<T> h{};
   h.g = g;
   h.U = U;
@@ -1297,8 +1299,17 @@ static hipError_t tune_unit(const Geom& g, const T* U, const T* x, T* y, int32_t
   if (kind & 1) {   // the plain application y = (8 - H) x
     h.a = -1.0;
     h.b = 8.0;
+    const bool one = cg_flags && hop_ring_ok(g, cfg, sizeof(T));
+    if (one) {   // a CG iteration's three dots, y (read and written by the same threads) in the residual's place
+      h.ring = y;
+      h.ring_slots = 1;
+      h.run = cg_flags + kFlRun;
+      h.dot_mask = 7;
+    }
     hipError_t e = launch_hop<T>(h, cfg, s);
     if (e != hipSuccess) return e;
+    // else the update's second launch, which reads a residual again: a pass over one vector per field
+    if (cg_flags && !one) return launch_dot<T>(y, y, field_reals(g), n_rhs, partials, s);
   }
   if (kind & 2) {   // the recursion step y = -H x / 4 - y, written over its z input as the sweeps do
     h.a = -0.25;
@@ -2421,14 +2432,25 @@ rmh_status rmh_autotune_laplacian(const int32_t L[4], const void* U, int32_t dty
                              purpose == RMH_PURPOSE_CHEB_BWD)
                                 ? 2
                                 : (purpose == RMH_PURPOSE_ANY ? 3 : 1);
-  // the dot products fused into the purpose's launches: <p, Ap> in the CG iterations and the FP64
-  // residuals, the three moment sums in the power-spectrum sweeps
+  // the dot products fused into the purpose's launches: <p, Ap> in the CG iterations (three where one launch
+  // does the update, tune_unit), one in the FP64 residuals, the three moment sums in the power-spectrum sweeps
   const int32_t dot_mask = (purpose == RMH_PURPOSE_CG || purpose == RMH_PURPOSE_CG64) ? 2
                            : purpose == RMH_PURPOSE_MOMENTS                           ? 7
                                                                                       : 0;
   hipStream_t s = (hipStream_t)stream;
   // y is the recursion unit's z input: start it from zeros (it then stays bounded, y <- A x - y)
   HIP_TRY(launch_zero(y, (size_t)n_rhs * 32 * g.V * dsize(dtype), s));
+  // a CG unit's flags, the same for every field, go ahead of the partial sums
+  constexpr size_t kCgFlagBytes = 48;
+  int32_t* cg_flags = nullptr;
+  if (purpose == RMH_PURPOSE_CG) {
+    int32_t fl[kCgFlagBytes / 4] = {};
+    static_assert(kFlN <= kCgFlagBytes / 4, "the flags of a field");
+    fl[kFlRun] = 1;
+    cg_flags = (int32_t*)partials;
+    partials += kCgFlagBytes / 8;
+    RMH_TRY(h2d(cg_flags, fl, sizeof fl, s));
+  }
   hipEvent_t e0, e1;
   HIP_TRY(hipEventCreate(&e0));
   HIP_TRY(hipEventCreate(&e1));
@@ -2466,13 +2488,15 @@ rmh_status rmh_autotune_laplacian(const int32_t L[4], const void* U, int32_t dty
   float bt = 1e30f;
   rmh_status st = RMH_OK;
   for (const HopConfig& c : cand) {
+    // (a grid that leaves the flags no room is of the smallest tiles and no candidate)
+    if (cg_flags && kCgFlagBytes + (size_t)n_rhs * 3 * hop_num_blocks(g, c) * 8 > cw.off) continue;
     auto unit = [&]() -> rmh_status {
       const hipError_t e =
           dtype == RMH_F64
               ? tune_unit<double>(g, (const double*)U, (const double*)x, (double*)y, n_rhs, c, unit_kind,
-                                  partials, dot_mask, s)
+                                  partials, dot_mask, cg_flags, s)
               : tune_unit<float>(g, (const float*)U, (const float*)x, (float*)y, n_rhs, c, unit_kind,
-                                 partials, dot_mask, s);
+                                 partials, dot_mask, cg_flags, s);
       return e == hipSuccess ? RMH_OK : fail(RMH_E_HIP, "stencil launch: %s", hipGetErrorString(e));
     };
     st = unit();  // warm-up

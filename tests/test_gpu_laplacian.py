@@ -496,3 +496,21 @@ def test_autotune_times_the_built_in_shape(tmp_path):
     assert "block=216 " in lines[0] and "tile2=3 " in lines[0], lines[0]
     best = float(r.stdout.split()[-1])
     assert best <= min(float(ln.split()[-2]) for ln in lines) + 1e-4
+
+
+@pytest.mark.parametrize("L,n", [((2, 2, 2, 2), 1), ((4, 4, 4, 4), 2), ((8, 4, 6, 8), 3)])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_autotune_cg(L, n, dtype):
+    """The CG unit (three dot products and a residual, or one and a second pass) from the smallest workspace on: the shape it finds
+    solves, and the configuration is one that the setter accepts."""
+    announce(f"autotune cg {L} n={n} {dtype}")
+    U, P, Ud, Pd = setup(L, "eps", 0.4, 19, n=n)
+    api.tune_clear()
+    try:
+        cfg, ms = api.autotune_laplacian(L, Ud.to(dtype), Pd.to(dtype), reps=2, purpose="cg")
+        assert ms > 0
+        api.tune_set(L, dtype, n, *cfg[:7], "cg", cfg[7])
+        out = api.rational_apply(L, Ud, Pd, api.rational_kappa(0.8, 4), api.Solver(tol=1e-10, mode=0 if dtype == torch.float64 else 1))
+        assert out["stats"]["true_relres_max"] <= 1e-10
+    finally:
+        api.tune_clear()
