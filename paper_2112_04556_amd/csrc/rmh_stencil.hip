@@ -215,10 +215,11 @@ __device__ __forceinline__ void hop_store(const HopArgs<T>& A, int32_t v, const 
 
 // The FP32 streamed form's link and field loads go out before any of the hop's arithmetic: left to itself the
 // scheduler starts on the link and issues the field's loads between, a second exposed latency per hop (moments at
-// 24^4, two fields: 134 us with all loads first, 141 without).
-template <typename T, int FORM>
+// 24^4, two fields: 134 us with all loads first, 141 without).  With two directions a thread the loads are half as
+// many and all of them at once would cost a wave per SIMD.
+template <typename T, int FORM, int NV>
 __device__ __forceinline__ void all_loads_first() {
-  if constexpr (sizeof(T) == 4 && FORM == kFormStream) __builtin_amdgcn_sched_barrier(0);
+  if constexpr (sizeof(T) == 4 && FORM == kFormStream && NV == 4) __builtin_amdgcn_sched_barrier(0);
 }
 
 // out[v] = a (H x)[v] + b x[v] + c z[v]: a block of B threads covers B * NV / 4 sites; the
@@ -230,7 +231,7 @@ __device__ __forceinline__ void hop_term(const T* __restrict__ Um, int32_t sb, c
   T u[18], phi[NV][8];
   load_rows<T, kUni>(Um, sb, V, u);
   load_field<T, NV, kUni || FORM == kFormMatrix>(xf, sb, nu0, V, phi);
-  all_loads_first<T, FORM>();
+  all_loads_first<T, FORM, NV>();
   link_row2<T, FORM>(u);
   hop_apply<T, FORM, NV, kT>(u, phi, acc);
 }
@@ -243,7 +244,7 @@ __device__ __forceinline__ void hop_term_fwd(const T* __restrict__ Um, int32_t s
   T u[18], phi[NV][8];
   load_rows<T, kUni>(Um, s, V, u);
   load_field<T, NV, kUni || FORM == kFormMatrix>(xf, sf, nu0, V, phi);
-  all_loads_first<T, FORM>();
+  all_loads_first<T, FORM, NV>();
   link_row2<T, FORM>(u);
   hop_apply<T, FORM, NV, false>(u, phi, acc);
 }
