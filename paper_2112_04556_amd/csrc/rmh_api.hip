@@ -584,6 +584,7 @@ rmh_status engine_solve(Engine& e, const double* U64, const float* U32, const do
   h32.dot_mask = one32 ? 7 : 2;
   h32.ring = one32 ? e.ring32 : nullptr;
   h32.ring_slots = e.nslot32;
+  h32.ring_ru = e.r64;
   // FP64 true residual of the seed for reliable updates: r64 = b - (Delta + sigma0) x_seed
   HopArgs<double> hr{};
   hr.g = g;

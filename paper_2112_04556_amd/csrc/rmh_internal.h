@@ -79,6 +79,9 @@ struct HopArgs {
   // CG's ring of T, ring_slots slots of 32 V reals per field
   const T* ring;            // (hop_ring_ok)
   int32_t ring_slots;
+  // FP32, with ring: the FP64 residuals [n_rhs][32 V] that take the ring's place for the fields whose reliable update
+  // is pending (kFlNeedRU), as in the update that follows
+  const double* ring_ru;
   // optional, FP64 without dots (hop_ring_ok): out += sum_{y < src_n} src_coef[(v src_n + y) src_stride] src[y][v]
   // for the fields v < src_rhs, src [src_n][src_rhs][4][8][V]
   const T* src;

@@ -278,8 +278,10 @@ hipError_t launch_cg_init(const CgDev& cg, const double* bn2_partials, int32_t n
 // update of r and p.  beta = <r', r'> / <r, r> needs the norm of a residual that the same launch computes;
 // it is taken from <r', r'> = <r, r> - 2 alpha <r, Ap> + alpha^2 <Ap, Ap>, which holds for the vectors at
 // hand whatever their conjugacy (a form without <r, Ap>, which the exact recurrences would allow, doubles
-// its error every iteration), and the residual that was computed gives alpha and the next prediction their
-// <r, r>, so a prediction's rounding, a few ulps of <r, r>, is not handed on.  Where <r', r'> comes out below
+// its error every iteration).  r is the residual that this update takes: after a reliable update the FP64 one,
+// which the stencil's dot then reads too (with the recursive one there, solves that reach FP32's digits in a
+// few iterations broke down).  The residual that was computed gives alpha and the next prediction their <r, r>,
+// so a prediction's rounding, a few ulps of <r, r>, is not handed on.  Where <r', r'> comes out below
 // 1e-4 <r, r> more than four digits have cancelled: convergence is then decided by the next update from the
 // sum (Defer), and until then the norm counts as 1e-2 |r|.
 // Against residual and direction updates of their own, which read r' and p again (16^4, one field: 11.8 and

@@ -114,13 +114,26 @@ __device__ __forceinline__ void load_field(const T* __restrict__ xf, int32_t s, 
   }
 }
 
-// The current residual of field v in the CG's ring (HopArgs::ring), of which dot 0 is taken.
+// The residual of field v that dot 0 is taken with: the current one in the CG's ring (HopArgs::ring) or, after a
+// reliable update, the FP64 one (HopArgs::ring_ru); neither without a ring.
 template <typename T>
-__device__ __forceinline__ const T* hop_ring_field(const HopArgs<T>& A, int32_t v) {
-  if (!A.ring) return nullptr;
+struct HopRing {
+  const T* r;
+  const double* ru;
+  __device__ __forceinline__ explicit operator bool() const { return r || ru; }
+};
+template <typename T>
+__device__ __forceinline__ HopRing<T> hop_ring_field(const HopArgs<T>& A, int32_t v) {
+  HopRing<T> f{nullptr, nullptr};
+  if (!A.ring) return f;
   const int32_t* fl = A.run - kFlRun + (int64_t)v * A.run_stride;
+  if (sizeof(T) == 4 && A.ring_ru && fl[kFlNeedRU]) {
+    f.ru = A.ring_ru + (int64_t)v * 32 * A.g.V;
+    return f;
+  }
   const int32_t i = sizeof(T) == 8 ? fl[kFlBase] + fl[kFlM] : fl[kFlBase32] + fl[kFlM] - fl[kFlK0];
-  return A.ring + ((int64_t)v * A.ring_slots + i % A.ring_slots) * 32 * (int64_t)A.g.V;
+  f.r = A.ring + ((int64_t)v * A.ring_slots + i % A.ring_slots) * 32 * (int64_t)A.g.V;
+  return f;
 }
 
 // The epilogue at one site: out = a h + b x + c z for NV directions from nu0 on, and the partial dot
@@ -138,7 +151,8 @@ __device__ __forceinline__ void hop_store(const HopArgs<T>& A, int32_t v, const 
   const T cc = T(A.c);
   const T* zf = A.z ? A.z + (int64_t)(v / A.z_div) * FV : nullptr;  // may alias out
   T* outf = A.out + (int64_t)v * FV;
-  const T* rf = DOTS && kRing ? hop_ring_field(A, v) : nullptr;   // z is null with it
+  HopRing<T> rf{nullptr, nullptr};
+  if (DOTS && kRing) rf = hop_ring_field(A, v);   // z is null with it
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
     T xs[8], zv[8];
@@ -203,10 +217,16 @@ __device__ __forceinline__ void hop_store(const HopArgs<T>& A, int32_t v, const 
       }
     }
     if (DOTS && kRing && rf) {   // last, where the fewest registers are in use
-      Rows<T> rr(rf + r0, V, byte_off<T>(s));
       T rv[8];
+      if (sizeof(T) == 4 && rf.ru) {
+        Rows<double> rr(rf.ru + r0, V, byte_off<double>(s));
 #pragma unroll
-      for (int a = 0; a < 8; ++a) rv[a] = rr.get();
+        for (int a = 0; a < 8; ++a) rv[a] = (T)rr.get();
+      } else {
+        Rows<T> rr(rf.r + r0, V, byte_off<T>(s));
+#pragma unroll
+        for (int a = 0; a < 8; ++a) rv[a] = rr.get();
+      }
 #pragma unroll
       for (int a = 0; a < 8; ++a) dsum[0] = fma((double)w[a], (double)rv[a], dsum[0]);
     }
@@ -377,7 +397,8 @@ __global__ void __launch_bounds__(256) k_hop_split(const HopArgs<T> A, int32_t x
     const T* zf = A.z ? A.z + (int64_t)(v / A.z_div) * FV : nullptr;  // may alias out
     T* outf = A.out + (int64_t)v * FV;
     constexpr bool kRing = sizeof(T) == 8 || FORM == kFormMatrix;   // the FP32 moments' form does without
-    const T* rf = DOTS && kRing ? hop_ring_field(A, v) : nullptr;   // z is null with it
+    HopRing<T> rf{nullptr, nullptr};
+    if (DOTS && kRing) rf = hop_ring_field(A, v);   // z is null with it
     using Bits = typename std::conditional<sizeof(T) == 8, uint64_t, uint32_t>::type;
     const Bits m0 = mu == 0 ? ~Bits(0) : Bits(0), m1 = mu == 1 ? ~Bits(0) : Bits(0);
     const Bits m2 = mu == 2 ? ~Bits(0) : Bits(0), m3 = mu == 3 ? ~Bits(0) : Bits(0);
@@ -393,8 +414,13 @@ __global__ void __launch_bounds__(256) k_hop_split(const HopArgs<T> A, int32_t x
       zv[q] = !zf ? T(0) : A.z_div == 1 ? __builtin_nontemporal_load(&zf[e]) : zf[e];
     }
     if (kRing && rf) {
+      if (sizeof(T) == 4 && rf.ru) {
 #pragma unroll
-      for (int q = 0; q < 2 * NV; ++q) zv[q] = rf[(int64_t)(nu0 * 8 + 4 * q + mu) * V + s];
+        for (int q = 0; q < 2 * NV; ++q) zv[q] = (T)rf.ru[(int64_t)(nu0 * 8 + 4 * q + mu) * V + s];
+      } else {
+#pragma unroll
+        for (int q = 0; q < 2 * NV; ++q) zv[q] = rf.r[(int64_t)(nu0 * 8 + 4 * q + mu) * V + s];
+      }
     }
 #pragma unroll
     for (int q = 0; q < 2 * NV; ++q) {
@@ -875,7 +901,8 @@ k_hop_tile(const HopArgs<T> A, const HopTile S, int32_t xcd) {
   const T ca = T(A.a), cb = T(A.b_rhs ? A.b_rhs[v] : A.b), cc = T(A.c);
   const T* zf = Z ? A.z + (int64_t)(v / A.z_div) * FV : nullptr;   // may alias out
   T* outf = A.out + (int64_t)v * FV;
-  const T* rf = DOTS && !Z ? hop_ring_field(A, v) : nullptr;
+  HopRing<T> rf{nullptr, nullptr};
+  if (DOTS && !Z) rf = hop_ring_field(A, v);
   const uint32_t buf = (uint32_t)(S.R1 * S.R2 * L0) * PB;          // one plane of the tile in LDS
   double dsum[3] = {0.0, 0.0, 0.0};
   uint32_t pl = (uint32_t)x3_0 * plane;
@@ -945,7 +972,15 @@ k_hop_tile(const HopArgs<T> A, const HopTile S, int32_t xcd) {
         zr.next();
       }
     }
-    if (DOTS && !Z && rf) get_half(rf, V, hf + gc + pl, q);
+    if (DOTS && !Z && rf) {
+      if (sizeof(T) == 4 && rf.ru) {
+        Rows<double> rr(rf.ru, V, 2 * (hf + gc + pl));   // (at most 34 V bytes of FP32, 2^24 sites)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) q[i >> 3][i & 7] = (T)rr.get();
+      } else {
+        get_half(rf.r, V, hf + gc + pl, q);
+      }
+    }
     whole_link(la, u);
     hop_pair<T, false>(u, p, acc);    // x3 forward; phi(x+3) is the next plane
     if (live) lds_put<T>(nxt + lc, p);

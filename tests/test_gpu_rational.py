@@ -163,6 +163,47 @@ def test_rational_apply_update_forms(mode, shape):
         assert np.linalg.norm(r) <= 1.01 * tol * float(torch.linalg.norm(Pd[2])), j
 
 
+# Sources of a few plane waves on the free field: FP32 iterations reach the digits of FP32 within as many steps, and the
+# reliable updates that follow replace a residual by one of another size and direction
+RELIABLE = [((1.0, 0.25), 0.1), ((1.0, 0.25), 0.01), ((1.0, 1e-3), 0.01), ((1.0, 0.3, 0.1), 0.01)]
+
+
+@pytest.mark.parametrize("amps,delta", RELIABLE)
+def test_mixed_reliable_updates_of_short_solves(amps, delta):
+    """Mixed solves in FP32 from the first iteration: the stencils whose update takes one launch, its residual norm
+    predicted from their dots, against the walk's, summed: at most twice the iterations and every pole's solution."""
+    L, tol = (8, 6, 4, 4), 1e-11
+    announce(f"mixed reliable updates {amps} delta={delta}")
+    _, _, Ud, _ = setup(L, "unit", 0.0, 5, n=1)
+    i = torch.arange(api.volume(L), device=dev())
+    x = [i % 8, (i // 8) % 6, (i // 48) % 4, i // 192]
+    waves = []
+    for k in ((1, 0, 0, 0), (0, 1, 0, 0), (2, 0, 1, 0))[:len(amps)]:
+        lam = sum(2.0 - 2.0 * np.cos(2 * np.pi * kk / ll) for kk, ll in zip(k, L))
+        waves.append((lam, torch.cos(sum(2 * torch.pi * kk * c.double() / ll for kk, c, ll in zip(k, x, L)))))
+    b = sum(a * w for a, (_, w) in zip(amps, waves)).expand(1, 4, 8, -1).contiguous()
+    rat = _rat_kappa(0.97, 4)
+    shapes = {"walk": (1, 64, 4, 1, 2, 1), "site": (1, 64, 4, 0, 0, 1), "split": (1, 256, 2, 2, 0, 1),
+              "tile": (1, 128, 2, 1, 2, 2)}
+    iters = {}
+    try:
+        for name, (form, block, nv, order, walk, tile2) in shapes.items():
+            api.tune_clear()
+            for dt in (torch.float64, torch.float32):
+                api.tune_set(L, dt, 1, form, block, 1, nv, order, walk, 1, "cg", tile2)
+            out = api.rational_apply(L, Ud, b, rat, api.Solver(tol=tol, mode=1, delta=delta, mixed_switch=-1.0),
+                                     want_poles=True)
+            iters[name] = out["stats"]["iters"]
+            assert out["stats"]["true_relres_max"] <= tol, name
+            for j, sj in enumerate(rat.sigma):
+                want = sum(a * w / (lam + sj) for a, (lam, w) in zip(amps, waves)).expand_as(b[0])
+                err = float(torch.linalg.norm(out["x_poles"][0, j] - want))
+                assert err <= 1.01 * tol * float(torch.linalg.norm(b)) / sj, (name, j)
+    finally:
+        api.tune_clear()
+    assert max(iters.values()) <= 2 * iters["walk"], iters
+
+
 @pytest.mark.parametrize("switch", [-1.0, 1e-2, 1e-4, 1e-7])
 @pytest.mark.parametrize("basis", [3, 16, 32])
 def test_mixed_switch_points(switch, basis):
