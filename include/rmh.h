@@ -104,7 +104,8 @@ typedef struct {
  * CG; mode 1: mixed precision -- FP64 iterations while the seed residual is above
  * mixed_switch * ||x|| (0 = default 1e-4, negative = none), then FP32 stencil and vectors with
  * FP64 reliable updates of the seed residual (delta = reliable-update threshold in (0, 1): an update
- * once the seed residual fell below delta times its largest value since the last one, e.g. 0.01).
+ * once the seed residual fell below delta times its largest value since the last one, e.g. 0.01, or
+ * by a factor of 100 in one iteration).
  * check_every: at most this many iterations between host convergence checks (0 = 8); after the
  * first, each check is placed where the seed's convergence rate so far predicts the next threshold
  * (the switch to FP32, then tol).  basis: iterations per

@@ -283,7 +283,8 @@ hipError_t launch_cg_init(const CgDev& cg, const double* bn2_partials, int32_t n
 // few iterations broke down).  The residual that was computed gives alpha and the next prediction their <r, r>,
 // so a prediction's rounding, a few ulps of <r, r>, is not handed on.  Where <r', r'> comes out below
 // 1e-4 <r, r> more than four digits have cancelled: convergence is then decided by the next update from the
-// sum (Defer), and until then the norm counts as 1e-2 |r|.
+// sum (Defer), until then the norm counts as 1e-2 |r|, and mixed solves take a reliable update, which a smaller
+// delta would ask for on the true norm (one iteration later the two residuals have parted, and solves broke down).
 // Against residual and direction updates of their own, which read r' and p again (16^4, one field: 11.8 and
 // 11.0 us; 12^4: 6.9 and 7.8), one pass over five streams takes 17.5 and 10.6 us, and the stencil 1 us more.
 //
@@ -359,10 +360,11 @@ __device__ __forceinline__ CgStep cg_scalars(const CgDev& cg, int32_t v, bool ru
   r.defer = !kNext && rrn < 1e-4 * r.rr;
   r.beta = (rrn < 0.0 ? 0.0 : rrn) / r.rr;
   r.rrn = r.defer ? 1e-4 * r.rr : rrn;
-  // a reliable update once the residual norm fell below delta times its largest value since the last one
+  // a reliable update once the residual norm fell below delta times its largest value since the last one, or further
+  // than the prediction tells
   r.maxr = ru ? sqrt(r.rr) : sc[kScMaxR];
   const double rnorm = sqrt(r.rrn);
-  r.need_ru = mixed && rnorm < sc[kScDelta] * (rnorm > r.maxr ? rnorm : r.maxr);
+  r.need_ru = mixed && (r.defer || rnorm < sc[kScDelta] * (rnorm > r.maxr ? rnorm : r.maxr));
   return r;
 }
 

@@ -165,7 +165,9 @@ def test_rational_apply_update_forms(mode, shape):
 
 # Sources of a few plane waves on the free field: FP32 iterations reach the digits of FP32 within as many steps, and the
 # reliable updates that follow replace a residual by one of another size and direction
-RELIABLE = [((1.0, 0.25), 0.1), ((1.0, 0.25), 0.01), ((1.0, 1e-3), 0.01), ((1.0, 0.3, 0.1), 0.01)]
+RELIABLE = [((1.0, 0.25), 0.1), ((1.0, 0.25), 0.01), ((1.0, 1e-3), 0.01), ((1.0, 0.3, 0.1), 0.01),
+            # norms that fall by more than the predicted one tells, past the threshold in the same step
+            ((1.0, 0.25), 1e-3), ((1.0, 0.25), 1e-5), ((1.0, 0.3, 0.1), 1e-3), ((1.0, 1e-2, 1e-4), 1e-5)]
 
 
 @pytest.mark.parametrize("amps,delta", RELIABLE)
