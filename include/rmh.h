@@ -109,13 +109,13 @@ typedef struct {
  * check_every: at most this many iterations between host convergence checks (0 = 8); after the
  * first, each check is placed where the seed's convergence rate so far predicts the next threshold
  * (the switch to FP32, then tol).  basis: iterations per
- * segment of the shift solutions (0 = 32 in mode 0, 16 in mode 1, up to 47 in all on lattices of at
- * most 2^17 sites; at most 32): the shifts other
- * than the seed are carried as coefficients over the stored seed residuals of a segment and
+ * segment of the shift solutions (0 = 32 in mode 0, 16 in mode 1, on lattices of at most 2^17 sites up
+ * to 47 in all, as many as the refinement's part of the workspace has room for; at most 32): the shifts
+ * other than the seed are carried as coefficients over the stored seed residuals of a segment and
  * folded into their FP64 vectors once per segment, so the workspace holds basis + 1 extra link
  * fields per source
- * (mode 1: plus min(2 (basis + 1), 33), or 48, FP32 residuals, where the FP32 phase, and the segment open
- * at the switch of precision, go on).  multishift_target: the multi-shift recursion stops once every
+ * (mode 1: plus min(2 (basis + 1), 33), or up to 48, FP32 residuals, where the FP32 phase, and the segment
+ * open at the switch of precision, go on).  multishift_target: the multi-shift recursion stops once every
  * shift's recursive residual is below multishift_target * tol (0 = default 0.5); every pair whose
  * FP64 true residual is then above tol is refined by its own correction solve (targets above 1
  * leave pairs for that refinement on purpose; range [0, 1e6] with multishift_target * tol < 1). */

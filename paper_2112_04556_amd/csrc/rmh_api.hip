@@ -347,53 +347,34 @@ size_t rup(size_t b) { return ((b + 255) / 256) * 256; }
 // keep only the current and the next residual), and in mixed engines min(2 (basis + 1), 33) in FP32.
 // Default segments: 32 iterations in FP64 engines (a solve of up to 32 iterations folds its shifts
 // once), 16 in mixed ones (whose FP64 phase ends near there; the open segment then goes on in the
-// FP32 ring).  On small lattices, where 15 more residuals are cheap, 47: a fold writes and reads back
-// the solution and direction of every shift, and the usual solves to 1e-10 take 31 to 36 iterations
-// (16^4, 12 poles, FP64: 35 iterations in one fold of 185 us instead of two of 333 together).
-int32_t ring_slots(const Geom& g, int32_t n_shift, int32_t basis, int32_t mode) {
-  if (n_shift <= 1) return 2;
-  const int32_t m = basis > 0 ? basis : mode ? 16 : g.V <= kLongSegmentSites ? kMaxSlots - 1 : 32;
-  return std::min<int32_t>(m, basis > 0 ? kMaxBasis : kMaxSlots - 1) + 1;
-}
-int32_t ring_slots32(const Geom& g, int32_t nslot, int32_t n_shift, int32_t basis) {
-  if (n_shift > 1 && basis <= 0 && g.V <= kLongSegmentSites) return kMaxSlots;
-  return std::min<int32_t>(2 * nslot, kMaxBasis + 1);
+// FP32 ring); plan_solve makes them longer on small lattices.
+struct RingSlots {
+  int32_t f64, f32;
+};
+RingSlots ring_slots(int32_t n_shift, int32_t basis, int32_t mode) {
+  const int32_t m = basis > 0 ? basis : mode ? 16 : 32;
+  const int32_t f64 = n_shift <= 1 ? 2 : std::min(m, kMaxBasis) + 1;
+  return {f64, std::min<int32_t>(2 * f64, kMaxBasis + 1)};
 }
 
 // coefficient slots per shift: the entries a segment can hold, in whole groups of eight (the fold reads
 // groups; slots past the segment's end hold zeros)
 int32_t coef_slots(const Engine& e) { return (std::max(e.nslot, e.nslot32) + 7) / 8 * 8; }
 
-void plan_engine(Carver& c, Engine& e, const Geom& g, int32_t n_rhs, int32_t n_shift, int32_t mode,
-                 int32_t basis) {
+// Returns the offset behind what is read after engine_solve: the parameters, the solver state and the true
+// residuals' sums.  From there on the engine's memory is free again.
+size_t plan_engine(Carver& c, Engine& e, const Geom& g, int32_t n_rhs, int32_t n_shift, int32_t mode,
+                   RingSlots slots) {
   e.g = g;
   e.n_rhs = n_rhs;
   e.n_shift = n_shift;
   e.mode = mode;
-  e.nslot = ring_slots(g, n_shift, basis, mode);
-  e.nslot32 = ring_slots32(g, e.nslot, n_shift, basis);
+  e.nslot = slots.f64;
+  e.nslot32 = slots.f32;
   const int64_t n = field_reals(g);
   const size_t nr = n_rhs, np = (size_t)n_rhs * n_shift;
-  e.p64 = c.take<double>(nr * n);
-  e.Ap64 = c.take<double>(nr * n);
-  if (mode) {
-    e.p32 = c.take<float>(nr * n);
-    e.Ap32 = c.take<float>(nr * n);
-    e.r64 = c.take<double>(nr * n);
-    e.x_lo = c.take<float>(nr * n);
-  }
-  e.ring = c.take<double>(nr * e.nslot * n);
-  if (mode) e.ring32 = c.take<float>(nr * e.nslot32 * n);
-  if (n_shift > 1) e.pj = c.take<double>(np * n);
-  e.coef = c.take<double>(np * (2 + 2 * coef_slots(e)));
-  const size_t scb = rup(nr * kScN * 8), flb = rup(nr * kFlN * 4);
-  e.state_bytes = 2 * (scb + flb);
-  char* st = c.take<char>(e.state_bytes);
-  e.sc = (double*)st;
-  e.flags = st ? (int32_t*)(st + scb) : nullptr;
-  e.sh = c.take<double>(np * kShN);
-  e.act = c.take<int32_t>(np);
-  e.act_next = c.take<int32_t>(np);
+  e.nblk_hop = hop_max_blocks(g);
+  e.nblk_e = cg_num_blocks(n);
   const size_t pb = rup(np * 8) * 2 + rup(nr * 8) * 3 + rup(nr * 4);
   e.params = c.take<char>(pb);
   e.params_bytes = pb;
@@ -406,13 +387,33 @@ void plan_engine(Carver& c, Engine& e, const Geom& g, int32_t n_rhs, int32_t n_s
     e.tol_rhs = (double*)q; q += rup(nr * 8);
     e.seed = (int32_t*)q;
   }
-  e.nblk_hop = hop_max_blocks(g);
-  e.nblk_e = cg_num_blocks(n);
+  const size_t scb = rup(nr * kScN * 8), flb = rup(nr * kFlN * 4);
+  e.state_bytes = 2 * (scb + flb);
+  char* st = c.take<char>(e.state_bytes);
+  e.sc = (double*)st;
+  e.flags = st ? (int32_t*)(st + scb) : nullptr;
+  e.part_true = c.take<double>(np * 3 * e.nblk_hop);
+  e.sums_true = c.take<double>(np * 3);
+  const size_t lasting = c.off;
+  e.p64 = c.take<double>(nr * n);
+  e.Ap64 = c.take<double>(nr * n);
+  if (mode) {
+    e.p32 = c.take<float>(nr * n);
+    e.Ap32 = c.take<float>(nr * n);
+    e.r64 = c.take<double>(nr * n);
+    e.x_lo = c.take<float>(nr * n);
+  }
+  e.ring = c.take<double>(nr * e.nslot * n);
+  if (mode) e.ring32 = c.take<float>(nr * e.nslot32 * n);
+  if (n_shift > 1) e.pj = c.take<double>(np * n);
+  e.coef = c.take<double>(np * (2 + 2 * coef_slots(e)));
+  e.sh = c.take<double>(np * kShN);
+  e.act = c.take<int32_t>(np);
+  e.act_next = c.take<int32_t>(np);
   e.part = c.take<double>(nr * std::max<int64_t>(3 * e.nblk_hop, red_num_blocks(n)));
   e.part_e = c.take<double>(2 * nr * e.nblk_e);
   if (mode) e.part_ru = c.take<double>(nr * 3 * e.nblk_hop);
-  e.part_true = c.take<double>(np * 3 * e.nblk_hop);
-  e.sums_true = c.take<double>(np * 3);
+  return lasting;
 }
 
 CgDev cg_view(const Engine& e, int32_t nblk_hop, bool fp32) {
@@ -823,7 +824,7 @@ void plan_refine(Carver& c, RefinePlan& rp, const Geom& g, int32_t nb, int32_t m
   char* q = c.take<char>(rup((size_t)nb * 4) + rup((size_t)nb * 8));
   rp.idx = (int32_t*)q;
   rp.bneg = q ? (double*)(q + rup((size_t)nb * 4)) : nullptr;
-  plan_engine(c, rp.eng, g, nb, 1, mode, 0);
+  plan_engine(c, rp.eng, g, nb, 1, mode, ring_slots(1, 0, mode));
 }
 
 struct SolvePlan {
@@ -832,10 +833,29 @@ struct SolvePlan {
   float* U32 = nullptr;
 };
 
+// The refinement starts when the multi-shift solve has ended, in the memory of its vectors.  The default segments of
+// small lattices take what that leaves: a fold writes and reads back the solution and direction of every shift, and the
+// usual solves to 1e-10 take 31 to 36 iterations (16^4, 12 poles, FP64: 35 iterations in one fold of 185 us instead of
+// two of 333 together).  So the whole stays within the segments of 32 (16) iterations and a refinement beside them, the
+// workspace that callers have: 47 iterations for up to two sources, 35 for eight.
 void plan_solve(Carver& c, SolvePlan& sp, const Geom& g, int32_t n_rhs, int32_t n_shift, int32_t mode,
                 int32_t basis) {
-  plan_engine(c, sp.eng, g, n_rhs, n_shift, mode, basis);
+  RingSlots slots = ring_slots(n_shift, basis, mode);
+  if (n_shift > 1 && basis <= 0 && g.V <= kLongSegmentSites) {
+    // less the coefficients of the longer segments, and one field a source for the engine's smaller buffers
+    Carver refine(nullptr);
+    plan_refine(refine, sp.ref, g, refine_batch(n_rhs, n_shift), mode);
+    const size_t coefs = (size_t)n_rhs * n_shift * 2 * (kMaxSlots - kMaxBasis - 1) * 8;
+    const size_t spare = refine.off > coefs ? refine.off - coefs : 0;
+    const size_t field = (size_t)n_rhs * field_reals(g) * (mode ? 4 : 8);
+    int32_t& last = mode ? slots.f32 : slots.f64;
+    last = (int32_t)std::min<size_t>(kMaxSlots, last + std::max<size_t>(spare / field, 1) - 1);
+  }
+  const size_t lasting = plan_engine(c, sp.eng, g, n_rhs, n_shift, mode, slots);
+  const size_t end = c.off;
+  c.off = lasting;
   plan_refine(c, sp.ref, g, refine_batch(n_rhs, n_shift), mode);
+  c.off = std::max(c.off, end);
   if (mode) sp.U32 = c.take<float>((size_t)72 * g.V);
 }
 

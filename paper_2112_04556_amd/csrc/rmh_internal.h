@@ -193,7 +193,7 @@ struct CgDev {
 // K64 = kAllFp64; at the switch to FP32 the segment goes on, K64 = M + 1 and the current FP64
 // residual is copied to FP32 slot Base32 as entry K0 = M; after an FP32-phase flush K64 = K0 = 0.
 // A segment holds up to 32 iterations where the caller sets its length; the default on small
-// lattices (fields of at most 32 MiB) goes up to 47.
+// lattices (fields of at most 32 MiB) goes up to 47, within the workspace of 32.
 constexpr int kMaxBasis = 32;
 constexpr int kMaxSlots = 48;
 constexpr int32_t kLongSegmentSites = 1 << 17;

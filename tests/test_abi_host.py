@@ -149,6 +149,34 @@ def test_validation_rational():
     assert st == 3                                                                # RMH_E_WORKSPACE
 
 
+# (op, L, n_rhs, n_poles, basis, mode) and the bytes that a solve of that shape took before its default segments grew
+@pytest.mark.parametrize("op,L,n,n_poles,basis,mode,nbytes", [
+    (4, (8, 8, 8, 8), 2, 12, 0, 0, 157526784), (4, (8, 8, 8, 8), 8, 2, 0, 1, 406235392),
+    (4, (4, 4, 4, 6), 8, 2, 0, 1, 38107648), (4, (2, 2, 2, 2), 1, 1, 0, 0, 62208),
+    (4, (2, 2, 2, 2), 3, 64, 0, 0, 2280960),
+    (5, (6, 4, 10, 4), 3, 1, 0, 0, 11086592), (6, (12, 12, 12, 12), 8, 12, 0, 0, 3231144192),
+    (10, (16, 16, 16, 16), 8, 12, 0, 1, 9325890048), (11, (5, 3, 6, 7), 1, 2, 0, 0, 10339840),
+    (4, (4, 4, 4, 4), 2, 3, 20, 0, 5918208), (6, (4, 4, 4, 4), 1, 12, 7, 1, 7144192)])
+def test_workspaces_of_earlier_sizes(op, L, n, n_poles, basis, mode, nbytes):
+    """A solve takes a workspace of the size that it always took: the calls get as far as the check of their
+    overlapping arguments (RMH_E_ARG), which comes after that of the size (RMH_E_WORKSPACE)."""
+    lib, La = _lib.lib(), _lib.lattice_arg(L)
+    need = lib.rmh_workspace_bytes(op, La, 0, n, n_poles, basis, mode)
+    assert 0 < need <= nbytes
+    r, sg = np.ones(n_poles), np.linspace(0.5, 8.0, n_poles)
+    rat = ctypes.byref(_lib.RmhRational(0.0, n_poles, r.ctypes.data_as(_lib.P_f64), sg.ctypes.data_as(_lib.P_f64)))
+    sv = ctypes.byref(_lib.RmhSolver(1e-10, 100, mode, 0.1, 8, 0.0, basis))
+    far, ws = FAKE + 2**36, FAKE + 2**37
+    lf = ctypes.byref(_lib.RmhLeapfrog(6.0, 0.01, 1e-10, 20))
+    call = {4: lambda b: lib.rmh_rational_apply(La, FAKE, far, n, rat, sv, far, None, None, None, ws, b, None),
+            5: lambda b: lib.rmh_rational_apply_bwd(La, FAKE, far, far, n, rat, sv, None, far, 0, None, ws, b, None),
+            6: lambda b: lib.rmh_kinetic_force(La, FAKE, far, n, rat, sv, None, None, far, 0, None, ws, b, None),
+            10: lambda b: lib.rmh_heatbath_momenta(La, FAKE, far, n, 0.5, rat, sv, far, None, ws, b, None),
+            11: lambda b: lib.rmh_leapfrog_step(La, FAKE, far, rat, sv, lf, FAKE, far, None, ws, b, None)}[op]
+    assert call(nbytes) == 1 and call(need) == 1
+    assert call(need - 256) == 3
+
+
 def test_workspace_query():
     L = _lib.lattice_arg((4, 4, 4, 4))
     n1 = _lib.lib().rmh_workspace_bytes(4, L, 0, 1, 12, 0, 0)
