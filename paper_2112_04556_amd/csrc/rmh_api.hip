@@ -734,7 +734,7 @@ rmh_status engine_solve(Engine& e, const double* U64, const float* U32, const do
     if (it > maxiter + 2 * check_every) break;  // safety net; the device sets NoConv first
   }
   RMH_TRY(flush(true));
-  if (fp32_phase) HIP_TRY(launch_cg_xfold(cg32, e.x_lo, x_hi, 1, n, s));
+  if (fp32_phase) HIP_TRY(launch_cg_xfold(cg32, e.x_lo, x_hi, n, s));
   RMH_TRY(fetch());
   if (log_level() > 0) {
     for (int v = 0; v < nr; ++v)

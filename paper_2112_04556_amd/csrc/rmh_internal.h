@@ -233,9 +233,8 @@ hipError_t launch_cg_step(const CgDev& cg, const T* Ap, T* p, float* x_lo, doubl
 template <typename T>
 hipError_t launch_cg_step2(const CgDev& cg, const T* Ap, T* p, float* x_lo, double* x_hi, const double* r64,
                            int32_t mixed, int64_t n_reals, hipStream_t s);
-// x_hi[seed] += x_lo, x_lo = 0 for every rhs (all, the end of a mixed solve) or those with a
-// pending reliable update
-hipError_t launch_cg_xfold(const CgDev& cg, float* x_lo, double* x_hi, int32_t all, int64_t n_reals, hipStream_t s);
+// x_hi[seed] += x_lo, x_lo = 0 for every rhs, at the end of a mixed solve
+hipError_t launch_cg_xfold(const CgDev& cg, float* x_lo, double* x_hi, int64_t n_reals, hipStream_t s);
 // fold the segment (FP64 and FP32 entries alike) into x_j (and p_j unless final) of every shift
 // updated in it (p_j0 is read only where its coefficient is nonzero: before the first flush it
 // holds nothing); then, unless seed_only, reset the coefficients and restart the segment at the

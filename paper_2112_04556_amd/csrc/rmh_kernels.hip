@@ -705,10 +705,9 @@ RMH_CG(double)
 RMH_CG(float)
 #undef RMH_CG
 
-// x_hi[seed] += x_lo, x_lo = 0: for the rhs with a pending reliable update, or for all
-__global__ void k_cg_xfold(CgDev cg, float* __restrict__ x_lo, double* __restrict__ x_hi, int32_t all, int64_t n) {
+// x_hi[seed] += x_lo, x_lo = 0, at the end of an FP32 phase
+__global__ void k_cg_xfold(CgDev cg, float* __restrict__ x_lo, double* __restrict__ x_hi, int64_t n) {
   const int32_t v = blockIdx.y;
-  if (!all && cg.flags[(int64_t)v * kFlN + kFlNeedRU] == 0) return;
   const int64_t i0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
   if (i0 >= n) return;
   float* xl = x_lo + (int64_t)v * n;
@@ -720,9 +719,9 @@ __global__ void k_cg_xfold(CgDev cg, float* __restrict__ x_lo, double* __restric
   }
 }
 
-hipError_t launch_cg_xfold(const CgDev& cg, float* x_lo, double* x_hi, int32_t all, int64_t n_reals, hipStream_t s) {
+hipError_t launch_cg_xfold(const CgDev& cg, float* x_lo, double* x_hi, int64_t n_reals, hipStream_t s) {
   dim3 grid(elem_num_blocks(n_reals), cg.n_rhs);
-  hipLaunchKernelGGL(k_cg_xfold, grid, dim3(kBlock), 0, s, cg, x_lo, x_hi, all, n_reals);
+  hipLaunchKernelGGL(k_cg_xfold, grid, dim3(kBlock), 0, s, cg, x_lo, x_hi, n_reals);
   return hipGetLastError();
 }
 
