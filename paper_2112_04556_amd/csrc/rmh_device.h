@@ -214,8 +214,7 @@ RMH_HD void adjoint_columns(const T* u, T* c1, T* c2) {
 // unit determinant each row is the complex conjugate of the cross product of the other two,
 // U_2j = conj(U_0k U_1l - U_0l U_1k) with (j, k, l) a cyclic permutation of (0, 1, 2).
 // kFused: each element as one chain of multiply-adds (4 operations instead of 7).  The adjoint forms
-// in FP32 keep the separate products: their Chebyshev moments come back in FP64, where a change of
-// FP32 rounding would show.
+// in FP32 keep the separate products, and with them their results to the bit.
 template <typename T, bool kFused = (sizeof(T) == 8)>
 RMH_HD void su3_row2(T* u) {
 #pragma unroll

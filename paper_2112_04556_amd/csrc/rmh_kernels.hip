@@ -1022,8 +1022,9 @@ __device__ __forceinline__ void force_cross_cols(const double* u, const double* 
 // for the rest of the launch.  So the four waves load A and B at x once, a quarter each, into LDS, where a
 // neighbour inside the block is read too: at 16^4 208 reals per site and pair.  One step is one nu of one
 // pair; the loads of the next step are in flight during the 128 multiply-adds of this one (two steps ahead
-// they spill: four pairs in 133 us instead of 71).  12 pairs 168 -> 111 us, at 12^4 111 -> 82 us; the two pairs of
-// two reverse Chebyshev steps 43 us, against 38 for one.  What is left is the latency of a step, two waves per SIMD.
+// they spill: four pairs in 133 us instead of 71).  12 pairs 168 -> 111 us in a loop and 261 -> 172 after a solve
+// (their 400 MB then come from HBM), at 12^4 111 -> 82 us; the two pairs of two reverse Chebyshev steps 41 to 43 us,
+// against 38 for one.  What is left is the latency of a step, two waves per SIMD.
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 k_force(const ForceArgs F, int32_t xcd) {
   __shared__ double own[2][16][64];   // A and B at the block's sites, by turns

@@ -748,12 +748,13 @@ __global__ void __launch_bounds__(256) k_hop_ns(const HopArgs<T> A, int32_t xcd,
 // hops, which would need more registers than there are).  The x3 hop uses its link both ways:
 // U phi(x+3) U^dag for this plane, U^dag phi(x) U for the next.  The x1 and x2 hops come first in a
 // step and phi(x+3) is loaded last: the halo rows of a plane were then loaded by the neighbouring blocks
-// moments ago and are still in the XCD's L2 (at 32^3x64 17.6 M misses of 128 bytes instead of 21.0 M with
-// the opposite order, 1.2 times the algorithmic bytes).
+// moments ago and are still in the XCD's L2 (at 32^3x64 17.6 to 18.2 M misses of 128 bytes instead of 21.0 M
+// with the opposite order; 1.24 times the algorithmic bytes).
 //
 // Measured per application against the walk (same card, both warm): FP64 32^3x64 494 us against 568,
 // 24^4 x 4 fields (recursion step) 357 against 434, 16^4 x 2 35.5 against 41.4, 16^4 x 8 115 against 123;
-// FP32 32^3x64 273 against 292.  At 16^4 x 8 it issues vector instructions 77 % of the time.
+// FP32 32^3x64 273 against 292.  In FP64 the unit that returns loaded data is busy 89 % of the time at
+// 32^3x64 (78 % at 16^4 x 8) and vector instructions issue 63 % of it (58 %).
 
 // Keeps x in registers here: later arithmetic is not moved before, earlier not after.
 template <typename T, int N>

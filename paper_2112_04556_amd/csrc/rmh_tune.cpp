@@ -121,8 +121,9 @@ double site_us(const Geom& g, int32_t n_rhs) {
 //    directions per lane (FP32 from 24576 site-fields on: four; 16^3x12 9.3 us against 10.4 with two, 8x12x8x8
 //    6.8 against 5.2), in blocks of 128 threads where these give the CUs less work than blocks of 256
 //    (FP64, 128 against 256: 8^4 5.6 us against 6.3; 8x12x8x8 7.2 against 6.4; 12^4 12.4 against 11.5).
-// FP32 Chebyshev moments below 2^20 sites keep the streamed adjoint form: they are FP64 results of FP32
-// sweeps, and another form's rounding moves them by a few 1e-9, about as much as their own error.
+// FP32 Chebyshev moments below 2^20 sites keep the streamed adjoint form.  It is no loss of time (tuned, a batch of 32
+// sources at 24^4 takes it too, two fields a thread); another form would move the moments by a few 1e-9, which is
+// within their own error (8e-9 at 24^4) and so no gain either.
 HopConfig defaults(const Geom& g, int32_t dtype, int32_t n_rhs, int32_t purpose) {
   const bool f64 = dtype == RMH_F64;
   const int64_t work = (int64_t)g.V * n_rhs;
