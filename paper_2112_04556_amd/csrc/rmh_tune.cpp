@@ -114,7 +114,9 @@ double site_us(const Geom& g, int32_t n_rhs) {
 //    2^21 sites on, 8 (tiled against that walk: 32^3x64 0.260 ms against 0.306; 28x32x48x48 0.288 against 0.308;
 //    22x40x44x36 0.343 against 0.232; 40x44x36x28 x 2 0.582 against 0.504).
 //  - In smaller FP32 lattices the tile's vector work, the link rebuilt by both lane halves, is the bound: a batch of
-//    at least 2^19 site-fields walks with four directions per thread (24^4 x 8 360 us against 372 tiled), smaller
+//    at least 2^19 site-fields walks with four directions per thread (24^4 x 8 360 us against 372 tiled) where blocks
+//    of 64 columns fill the (x0, x1) planes (32x20x24x28 x 3 154 us against 169 by sites), else takes one thread per
+//    site in blocks of 256 (20x24x20x32 x 5 199 us against 225 walking, 20x24x24x24 x 2 74.7 against 82.5); smaller
 //    launches take one thread per site and direction pair (16^4 x 4 37 us against 43 for the hop split).
 //  - smaller launches (FP32: below 2^16 site-fields): four lanes per site, one per direction (hop split),
 //    whose four times as many waves hide the latency that one thread per site leaves exposed.  Two
@@ -165,9 +167,10 @@ HopConfig defaults(const Geom& g, int32_t dtype, int32_t n_rhs, int32_t purpose)
     c.order = split ? 2 : 0;
   } else if (work >= (1 << 19)) {
     // (also the FP64 lattices too large for the tile: more than 2^24 sites, or rows longer than a block)
+    const bool sites = !f64 && (int64_t)g.L0 * g.L1 % 64 != 0;
     c.nv = 4;
-    c.block = f64 ? 128 : 64;
-    c.walk = f64 ? walk_of(g, {8, 4, 2}) : walk_of(g, {4, 8, 2});
+    c.block = f64 ? 128 : sites ? 256 : 64;
+    c.walk = f64 ? walk_of(g, {8, 4, 2}) : sites ? 0 : walk_of(g, {4, 8, 2});
   } else if (!f64 && work >= (1 << 16)) {
     c.nv = 2;
     c.block = 128;

@@ -464,6 +464,25 @@ def test_laplacian_fp32_default_shapes_of_large_lattices(L):
     assert float((y - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
 
 
+@pytest.mark.parametrize("L,n", [((20, 24, 28, 8), 5), ((23, 19, 12, 21), 5), ((16, 16, 16, 16), 8)])
+def test_laplacian_fp32_default_shapes_of_batches(L, n):
+    """FP32 batches of 2^19 site-fields and more on smaller lattices: the walk where blocks of 64 columns fill the
+    (x0, x1) planes, else one thread per site.  Against FP64 at 65 terms of eight roundings each, and a mixed solve."""
+    announce(f"fp32 default shapes {L} n={n}")
+    V = api.volume(L)
+    g = torch.Generator(device=dev()).manual_seed(19)
+    h = inputs.random_links((4, 4, 4, 4), "haar", 0.0, seed=19).to(dev())
+    U = h[:, torch.randint(0, 256, (V,), device=dev(), generator=g)]
+    x = torch.randn(n, 4, 8, V, device=dev(), generator=g, dtype=torch.float64)
+    api.tune_clear()
+    Ud = api.pack_links(L, U, torch.float64)
+    ref = api.laplacian_apply(L, Ud, x.float().double())
+    y = api.laplacian_apply(L, api.pack_links(L, U, torch.float32), x.float()).double()
+    assert float((y - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
+    out = api.rational_apply(L, Ud, x, api.rational_kappa(0.5, 3), api.Solver(tol=1e-10, mode=1))
+    assert out["stats"]["true_relres_max"] <= 1e-10
+
+
 AUTOTUNE_24 = """
 import sys
 sys.path.insert(0, sys.argv[1])
