@@ -361,8 +361,8 @@ RingSlots ring_slots(int32_t n_shift, int32_t basis, int32_t mode) {
 // groups; slots past the segment's end hold zeros)
 int32_t coef_slots(const Engine& e) { return (std::max(e.nslot, e.nslot32) + 7) / 8 * 8; }
 
-// Returns the offset behind what is read after engine_solve: the parameters, the solver state and the true
-// residuals' sums.  From there on the engine's memory is free again.
+// Returns the offset of the vectors, whose memory is free after engine_solve.  The small buffers lie together: an update
+// begins with reads of most of them, and on pages apart took 18.2 us instead of 17.1 at 16^4.
 size_t plan_engine(Carver& c, Engine& e, const Geom& g, int32_t n_rhs, int32_t n_shift, int32_t mode,
                    RingSlots slots) {
   e.g = g;
@@ -373,8 +373,15 @@ size_t plan_engine(Carver& c, Engine& e, const Geom& g, int32_t n_rhs, int32_t n
   e.nslot32 = slots.f32;
   const int64_t n = field_reals(g);
   const size_t nr = n_rhs, np = (size_t)n_rhs * n_shift;
-  e.nblk_hop = hop_max_blocks(g);
-  e.nblk_e = cg_num_blocks(n);
+  e.coef = c.take<double>(np * (2 + 2 * coef_slots(e)));
+  const size_t scb = rup(nr * kScN * 8), flb = rup(nr * kFlN * 4);
+  e.state_bytes = 2 * (scb + flb);
+  char* st = c.take<char>(e.state_bytes);
+  e.sc = (double*)st;
+  e.flags = st ? (int32_t*)(st + scb) : nullptr;
+  e.sh = c.take<double>(np * kShN);
+  e.act = c.take<int32_t>(np);
+  e.act_next = c.take<int32_t>(np);
   const size_t pb = rup(np * 8) * 2 + rup(nr * 8) * 3 + rup(nr * 4);
   e.params = c.take<char>(pb);
   e.params_bytes = pb;
@@ -387,14 +394,14 @@ size_t plan_engine(Carver& c, Engine& e, const Geom& g, int32_t n_rhs, int32_t n
     e.tol_rhs = (double*)q; q += rup(nr * 8);
     e.seed = (int32_t*)q;
   }
-  const size_t scb = rup(nr * kScN * 8), flb = rup(nr * kFlN * 4);
-  e.state_bytes = 2 * (scb + flb);
-  char* st = c.take<char>(e.state_bytes);
-  e.sc = (double*)st;
-  e.flags = st ? (int32_t*)(st + scb) : nullptr;
+  e.nblk_hop = hop_max_blocks(g);
+  e.nblk_e = cg_num_blocks(n);
+  e.part = c.take<double>(nr * std::max<int64_t>(3 * e.nblk_hop, red_num_blocks(n)));
+  e.part_e = c.take<double>(2 * nr * e.nblk_e);
+  if (mode) e.part_ru = c.take<double>(nr * 3 * e.nblk_hop);
   e.part_true = c.take<double>(np * 3 * e.nblk_hop);
   e.sums_true = c.take<double>(np * 3);
-  const size_t lasting = c.off;
+  const size_t vectors = c.off;
   e.p64 = c.take<double>(nr * n);
   e.Ap64 = c.take<double>(nr * n);
   if (mode) {
@@ -406,14 +413,7 @@ size_t plan_engine(Carver& c, Engine& e, const Geom& g, int32_t n_rhs, int32_t n
   e.ring = c.take<double>(nr * e.nslot * n);
   if (mode) e.ring32 = c.take<float>(nr * e.nslot32 * n);
   if (n_shift > 1) e.pj = c.take<double>(np * n);
-  e.coef = c.take<double>(np * (2 + 2 * coef_slots(e)));
-  e.sh = c.take<double>(np * kShN);
-  e.act = c.take<int32_t>(np);
-  e.act_next = c.take<int32_t>(np);
-  e.part = c.take<double>(nr * std::max<int64_t>(3 * e.nblk_hop, red_num_blocks(n)));
-  e.part_e = c.take<double>(2 * nr * e.nblk_e);
-  if (mode) e.part_ru = c.take<double>(nr * 3 * e.nblk_hop);
-  return lasting;
+  return vectors;
 }
 
 CgDev cg_view(const Engine& e, int32_t nblk_hop, bool fp32) {
@@ -851,9 +851,9 @@ void plan_solve(Carver& c, SolvePlan& sp, const Geom& g, int32_t n_rhs, int32_t 
     int32_t& last = mode ? slots.f32 : slots.f64;
     last = (int32_t)std::min<size_t>(kMaxSlots, last + std::max<size_t>(spare / field, 1) - 1);
   }
-  const size_t lasting = plan_engine(c, sp.eng, g, n_rhs, n_shift, mode, slots);
+  const size_t vectors = plan_engine(c, sp.eng, g, n_rhs, n_shift, mode, slots);
   const size_t end = c.off;
-  c.off = lasting;
+  c.off = vectors;
   plan_refine(c, sp.ref, g, refine_batch(n_rhs, n_shift), mode);
   c.off = std::max(c.off, end);
   if (mode) sp.U32 = c.take<float>((size_t)72 * g.V);
